@@ -16,8 +16,10 @@
 //               trajectory record per env-step, then writes the state back.
 //               Its serving variant also admits and resets new requests.
 // Both stage the first-person observations of a wave through LDS so that
-// the wave's records leave as one contiguous, 16-byte-vectorised block;
-// whole-grid observations leave the same way, packed like the grids.
+// the wave's records leave as one contiguous block: k_plain as bytes, in
+// 16-byte stores; k_fused as one code per cell, decoded on the way out, in
+// 12-byte stores.  Whole-grid observations leave the same way, packed like
+// the grids.
 //
 // All arithmetic is integer except the reward, which is three separately
 // rounded fp32 operations (built with -ffp-contract=off).
@@ -33,10 +35,6 @@ constexpr int kWave = 64;
 constexpr int kView = 7;
 constexpr int kObsBytes = kView * kView * 3;        // 147
 constexpr int kStageBytes = kWave * kObsBytes;      // 9408, a multiple of 16
-constexpr int kHalfStageBytes = kStageBytes / 2;    // 4704, a multiple of 16
-// the fused kernel's record stage: 32 records behind up to 48 bytes carried
-// over from the previous piece (see k_fused)
-constexpr int kRecStageBytes = kHalfStageBytes + 48;
 constexpr int kObsWords = 37;                       // ceil(147 / 4)
 constexpr int kCatBytes = kView * kView;            // categorical record: 49
 constexpr int kCatWords = 13;                       // ceil(49 / 4)
@@ -1450,85 +1448,122 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
 // ---------------------------------------------------------------------------
 // Fused kernel
 // ---------------------------------------------------------------------------
-// One byte per cell in LDS: four times the cell's kind, i.e. the byte
-// offset of its entry in 64-entry tables of triples, so a cell costs one byte
-// read and one table read.  There is one table per view column i, whose
-// entries carry the see-through flag at bit 31 - i.  Kinds: 0 empty;
-// 1-6 wall, 7-12 goal, 13-18 key, 19-24 ball, 25-30 box by colour; 31-48
-// door by state and colour; 49 lava; 50 anything else (read as unseen);
-// 51-54 the agent by heading (whole-grid records only).
+// One byte per cell in LDS.  Bits 0-3 hold the type, bits 4-6 the colour and
+// bit 7 is set on cells that block sight.  A door's state is in bits 7 and 0:
+// open 0x04, closed 0x84, locked 0x85 (a key, type 5, never blocks sight);
+// only doors have a state.  A word of four codes turns into the four cells'
+// types, colours and states with byte-parallel integer operations
+// (decode_cells), so neither the view nor the records need a table read per
+// cell.  Whole-grid records draw the agent as type 10 with its heading in the
+// colour bits.
+constexpr uint32_t kCodeEmpty = kEmpty;
+constexpr uint32_t kCodeWall = 0x80u | (kGrey << 4) | kWall;
+constexpr uint32_t kCodeGoal = (kGreen << 4) | kGoal;
+constexpr uint32_t kCodeLava = kLava;
+constexpr uint32_t kCodeBall = (kBlue << 4) | kBall;
+constexpr uint32_t kCodeWall4 = kCodeWall * 0x01010101u;
+
+__device__ __forceinline__ uint32_t key_code(uint32_t colour) { return (colour << 4) | kKey; }
+__device__ __forceinline__ uint32_t door_code(uint32_t colour, uint32_t state) {
+  return (colour << 4) | kDoor | (state != kOpen ? 0x80u : 0u) | (state == kLocked ? 1u : 0u);
+}
+
+__device__ __forceinline__ uint32_t perm(uint32_t hi, uint32_t lo, uint32_t sel) {
+  return __builtin_amdgcn_perm(hi, lo, sel);
+}
+
+// The cells of four codes: types, colours and states, one byte each.
+// kAgents: type 10 carries its state (the heading) in the colour bits.
+struct Cells4 {
+  uint32_t type, colour, state;
+};
+
+__device__ __forceinline__ uint32_t types4(uint32_t w) {
+  // bit 2 set where a door is closed or locked (blocks sight, type bit 2)
+  const uint32_t shut = (w >> 5) & w & 0x04040404u;
+  return w & 0x0F0F0F0Fu & ~(shut >> 2);
+}
+
+template <bool kAgents>
+__device__ __forceinline__ Cells4 decode_cells(uint32_t w) {
+  const uint32_t shut = ((w >> 5) & w & 0x04040404u) >> 2;
+  Cells4 c;
+  c.type = w & 0x0F0F0F0Fu & ~shut;
+  c.colour = (w >> 4) & 0x07070707u;
+  c.state = shut + (w & shut);
+  if (kAgents) {
+    const uint32_t a8 = (w << 2) & w & 0x08080808u;   // only type 10 has bits 3 and 1
+    const uint32_t m = a8 - (a8 >> 3);
+    c.state |= c.colour & m;
+    c.colour &= ~m;
+  }
+  return c;
+}
+
+// the 12 triple bytes of four cells
+__device__ __forceinline__ void interleave(const Cells4& c, uint32_t (&w)[3]) {
+  const uint32_t a = perm(c.state, c.colour, 0x05010400u);   // C0 S0 C1 S1
+  const uint32_t b = perm(c.colour, c.type, 0x07030602u);    // T2 C2 T3 C3
+  w[0] = perm(a, c.type, 0x01050400u);
+  w[1] = perm(b, a, 0x05040302u);
+  w[2] = perm(b, c.state, 0x03070602u);
+}
+
+// codes of the four cells whose 12 triple bytes are w0, w1, w2; a state
+// counts on doors only
+__device__ __forceinline__ uint32_t encode_cells(uint32_t w0, uint32_t w1, uint32_t w2) {
+  const uint32_t t = perm(w2, perm(w1, w0, 0x0C060300u), 0x05020100u) & 0x0F0F0F0Fu;
+  const uint32_t c = perm(w2, perm(w1, w0, 0x0C070401u), 0x06020100u) & 0x07070707u;
+  const uint32_t s = perm(w2, perm(w1, w0, 0x0C0C0502u), 0x07040100u);
+  const uint32_t t1 = t >> 1, t2 = t >> 2;
+  const uint32_t door = t2 & ~t & ~t1 & 0x01010101u;   // type 4
+  const uint32_t wall = t1 & ~t2 & 0x01010101u;       // type 2
+  const uint32_t s1 = s >> 1;
+  const uint32_t shut = (s | s1) & door, locked = s1 & door;
+  return t | (c << 4) | ((shut | wall) << 7) | locked;
+}
+
+// code of one triple (the carried object)
 __device__ __forceinline__ uint32_t code_of(uint32_t tri) {
-  const uint32_t type = tri & 0xFF, colour = (tri >> 8) & 0xFF, state = (tri >> 16) & 0xFF;
-  // first kind of each type, as two 8-entry byte tables read with v_perm:
-  // types 0-3 {50, 0, 1, 50}, 4-7 {31, 13, 19, 25}, 8-11 {7, 49, 50, 50}, 12-15 all 50
-  const uint32_t lo = __builtin_amdgcn_perm(0x19130D1Fu, 0x32010032u, type & 7);
-  const uint32_t hi = __builtin_amdgcn_perm(0x32323232u, 0x32323107u, type & 7);
-  uint32_t kind = (type < 8 ? lo : hi) & 0xFF;
-  kind = type > 15 ? 50u : kind;
-  // walls, doors, keys, balls, boxes and goals come in colours; doors in states
-  kind += ((0x1F4u >> (type & 15)) & 1u) ? colour : 0u;
-  kind += type == kDoor ? 6u * state : 0u;
-  return (kind << 2) & 0xFFu;
+  return encode_cells(tri & 0xFFFFFFu, 0u, 0u) & 0xFFu;
 }
 
-// kinds 51-54: the agent facing east, south, west, north; they exist only
-// while whole-grid records are written
-constexpr uint32_t kAgentKind = 51;
-
-__device__ __forceinline__ uint32_t triple_of_kind(uint32_t kind) {
-  uint32_t tri;
-  if (kind == 0) tri = kCellEmpty;
-  else if (kind <= 6) tri = kWall | ((kind - 1) << 8);
-  else if (kind <= 12) tri = kGoal | ((kind - 7) << 8);
-  else if (kind <= 18) tri = kKey | ((kind - 13) << 8);
-  else if (kind <= 24) tri = kBall | ((kind - 19) << 8);
-  else if (kind <= 30) tri = kBox | ((kind - 25) << 8);
-  else if (kind <= 48) tri = kDoor | (((kind - 31) % 6) << 8) | (((kind - 31) / 6) << 16);
-  else if (kind == 49) tri = 9;
-  else if (kind >= kAgentKind && kind < kAgentKind + 4) return kAgent | ((kind - kAgentKind) << 16);
-  else return 0;
-  return tri | see_through(tri);
-}
-
-constexpr int kKinds = 64;
-
-// code of cell (x, y) of a freshly generated layout (grey walls, green
-// goal, key and locked door of the layout's colour, red lava); equals
+// code of cell (x, y) of a freshly generated layout; equals
 // code_of(layout_cell(L, x, y)) without the general switch
 __device__ __forceinline__ uint32_t layout_code(const Layout& L, int x, int y) {
-  constexpr uint32_t kWallCode = 4 * (1 + kGrey), kGoalCode = 4 * (7 + kGreen), kLavaCode = 4 * 49;
   const int S = L.S;
   if (L.fam == kFamKeyCorridor) return code_of(keycorridor_cell(L, x, y));
-  uint32_t code = 0;
+  uint32_t code = kCodeEmpty;
   if (L.fam == kFamTwoRoom) {   // the family is uniform across the wave here
-    code = (x == L.kx && y == L.ky) ? 4u * (13u + (uint32_t)L.colour) : code;
-    code = x == L.a ? (y == L.b ? 4u * (31u + 6u * kLocked + (uint32_t)L.colour) : kWallCode) : code;
+    code = (x == L.kx && y == L.ky) ? key_code((uint32_t)L.colour) : code;
+    code = x == L.a ? (y == L.b ? door_code((uint32_t)L.colour, kLocked) : kCodeWall) : code;
   } else if (L.fam == kFamFourRooms) {
     const int m = S / 2;
-    code = (y == m && x != L.c && x != L.d) ? kWallCode : code;
-    code = (x == m && y != L.a && y != L.b) ? kWallCode : code;
+    code = (y == m && x != L.c && x != L.d) ? kCodeWall : code;
+    code = (x == m && y != L.a && y != L.b) ? kCodeWall : code;
   } else if (L.fam == kFamLavaGap) {
-    code = (x == L.a && y != L.b) ? kLavaCode : code;
+    code = (x == L.a && y != L.b) ? kCodeLava : code;
   } else if (L.fam == kFamCrossings) {
-    code = crossings_lava(L, x, y) ? kLavaCode : code;
+    code = crossings_lava(L, x, y) ? kCodeLava : code;
   } else if (L.fam == kFamDistShift) {
-    code = ((y == 1 || y == L.a) && x >= 3 && x <= S - 3) ? kLavaCode : code;
+    code = ((y == 1 || y == L.a) && x >= 3 && x <= S - 3) ? kCodeLava : code;
   } else if (L.fam == kFamDynObs) {
-    code = is_ball(L, x, y) ? 4u * (19u + kBlue) : code;
+    code = is_ball(L, x, y) ? kCodeBall : code;
   } else if (L.fam == kFamGoToDoor) {
     const int dc = gotodoor_door(L, x, y);
     const bool wall = x == 0 || y == 0 || x >= L.kx - 1 || y >= L.ky - 1;
-    return dc >= 0 ? 4u * (31u + 6u * kClosed + (uint32_t)dc) : (wall ? kWallCode : 0u);
+    return dc >= 0 ? door_code((uint32_t)dc, kClosed) : (wall ? kCodeWall : kCodeEmpty);
   }
-  code = (x == L.gx && y == L.gy) ? kGoalCode : code;
+  code = (x == L.gx && y == L.gy) ? kCodeGoal : code;
   const bool border = x == 0 || y == 0 || x == S - 1 || y == S - 1;
-  return border ? kWallCode : code;
+  return border ? kCodeWall : code;
 }
 // A view reaches at most 6 cells ahead and 3 to the side of an interior
 // agent, i.e. at most 5 rows and 5 columns outside an S <= 32 grid: with
 // row-major indexing that is within 5 * 32 + 5 = 165 bytes before or after
-// the grid.  Such cells are never visible (the wall border blocks sight),
-// so only their addresses must stay inside the allocation.
+// the grid, read in whole words (8 bytes further at most).  Such cells are
+// never visible (the wall border blocks sight), so only their addresses must
+// stay inside the allocation; what they hold does not matter.
 constexpr int kMargin = 192;
 
 // dynamic LDS of a fused workgroup: the largest tile's grids plus both margins
@@ -1537,65 +1572,49 @@ __host__ __device__ inline size_t tile_lds_bytes(int32_t max_tile_cells) {
   return (b + 15) & ~(size_t)15;
 }
 
-__device__ __forceinline__ uint32_t table_at(const uint32_t* table, uint32_t code4) {
-  return *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(table) + code4);
-}
-
-// View rows from the LDS code grid: the view's row and column steps are
-// +-1 or +-S in the row-major grid, so each cell is one add away.  All 49
-// codes are read before any table lookup, so the lookups wait on the code
-// reads in bulk rather than one dependent pair at a time.
-struct LdsRows {
-  const uint32_t* table;
-  const uint8_t* center;   // the agent's cell
-  int R, F;                // linear steps to the agent's right and ahead
-  __device__ __forceinline__ void load_all(uint32_t (&c)[kView][kView]) const {
-    uint32_t code[kView][kView];
-#pragma unroll
-    for (int j = kView - 1; j >= 0; --j) {
-      const uint8_t* p = center + (6 - j) * F - 3 * R;
-#pragma unroll
-      for (int i = 0; i < kView; ++i) {
-        code[j][i] = p[0];
-        p += R;
-      }
-    }
-#pragma unroll
-    for (int j = kView - 1; j >= 0; --j)
-#pragma unroll
-      for (int i = 0; i < kView; ++i) c[j][i] = table_at(table + kKinds * i, code[j][i]);
-  }
+// The intervention of `intervene` on codes, as integer selects: every lane
+// holds its own action, and comparisons combined as booleans would go through
+// the scalar unit.  front is the code ahead, carry_code the held object's
+// (kCodeEmpty: an empty hand); act >= 6 changes nothing.
+struct CodeAction {
+  uint32_t new_front;
+  uint32_t ok;        // ~0 if the action succeeded (a walk, pickup, drop, toggle), else 0
+  uint32_t goal;      // 1: walked onto the goal
+  uint32_t lava;      // 1: walked into lava
 };
 
-__device__ __forceinline__ LdsRows lds_rows(const uint32_t* table, const uint8_t* codes, int S, int x,
-                                            int y, int dir) {
-  // heading 0: ahead +1, right +S; 1: ahead +S, right -1; 2: -1, -S; 3: -S, +1
-  const int F = (dir & 1) ? ((dir == 1) ? S : -S) : ((dir == 0) ? 1 : -1);
-  const int R = (dir & 1) ? ((dir == 1) ? -1 : 1) : ((dir == 0) ? S : -S);
-  return LdsRows{table, codes + y * S + x, R, F};
+__device__ __forceinline__ CodeAction act_on_code(uint32_t act, uint32_t carry_code, uint32_t front) {
+  // kind of the cell: its type, + 16 if it blocks sight
+  const uint32_t kind = (front & 15u) | ((front >> 3) & 16u);
+  constexpr uint32_t kOpenKinds = (1u << kEmpty) | (1u << kDoor) | (1u << kGoal) | (1u << kLava);
+  constexpr uint32_t kThings = (1u << kKey) | (1u << kBall) | (1u << kBox);
+  constexpr uint32_t kFlips = (1u << kDoor) | (1u << (16 + kDoor)), kLockedKind = 1u << (16 + kKey);
+  // a locked door's code less bit 7 is the code of its colour's key
+  const uint32_t toggles = kFlips | (carry_code == (front & 0x7Fu) ? kLockedKind : 0u);
+  const uint32_t things = carry_code == kCodeEmpty ? kThings : 0u;
+  const uint32_t empties = carry_code == kCodeEmpty ? 0u : 1u << kEmpty;
+  uint32_t kinds = act == kForward ? kOpenKinds : 0u;   // the kinds the action works on
+  kinds = act == kPickup ? things : kinds;
+  kinds = act == kDrop ? empties : kinds;
+  kinds = act == kToggle ? toggles : kinds;
+  CodeAction r;
+  r.ok = (uint32_t)((int32_t)(kinds << (31u - kind)) >> 31);
+  const uint32_t walked = act == kForward ? r.ok : 0u;
+  r.goal = walked & (kind == kGoal ? 1u : 0u);
+  r.lava = walked & (kind == kLava ? 1u : 0u);
+  r.new_front = (front ^ 0x80u) & ~1u;   // open <-> closed, locked -> open
+  r.new_front = act == kDrop ? carry_code : r.new_front;
+  r.new_front = act == kPickup ? kCodeEmpty : r.new_front;
+  return r;
 }
 
-// View rows from the LDS codes with every cell bounds-checked, cells outside
-// the grid read as walls: for the rare step whose view can leave the grid,
-// through a door on the outer ring that the step itself opened (GoToDoor
-// rooms use the grid's border as walls).  The views of such a step are
-// computed a second time with these rows.
-struct LdsCheckedRows {
-  const uint32_t* table;
-  const uint8_t* g;   // the env's codes
-  int S, x, y, dir;
-  __device__ __forceinline__ void load_all(uint32_t (&c)[kView][kView]) const {
-    const int fx = dir_dx(dir), fy = dir_dy(dir), rx = -fy, ry = fx;
-#pragma unroll
-    for (int j = kView - 1; j >= 0; --j)
-#pragma unroll
-      for (int i = 0; i < kView; ++i) {
-        const int wx = x + (i - 3) * rx + (6 - j) * fx, wy = y + (i - 3) * ry + (6 - j) * fy;
-        const bool in = (unsigned)wx < (unsigned)S && (unsigned)wy < (unsigned)S;
-        c[j][i] = in ? table_at(table + kKinds * i, g[in ? wy * S + wx : 0]) : kCellWall;
-      }
-  }
-};
+// triple of a carried object's code (objects have no state)
+__device__ __forceinline__ uint32_t carry_triple(uint32_t code) { return (code & 15u) | ((code << 4) & 0x700u); }
+
+// whether the code is a door's (any state)
+__device__ __forceinline__ bool is_door_code(uint32_t code) {
+  return (code & 15u) == kDoor || (code & 0x8Fu) == (0x80u | kKey);
+}
 
 struct LdsGrid {
   uint8_t* g;
@@ -1605,171 +1624,362 @@ struct LdsGrid {
     const uint8_t* p = g + (y - 1) * S + (x - 1);
     const uint8_t* q = p + S;
     const uint8_t* r = q + S;
-    return (p[0] == 0 ? 1u : 0u) | (p[1] == 0 ? 2u : 0u) | (p[2] == 0 ? 4u : 0u) | (q[0] == 0 ? 8u : 0u) |
-           (q[2] == 0 ? 16u : 0u) | (r[0] == 0 ? 32u : 0u) | (r[1] == 0 ? 64u : 0u) | (r[2] == 0 ? 128u : 0u);
+    return (p[0] == kCodeEmpty ? 1u : 0u) | (p[1] == kCodeEmpty ? 2u : 0u) | (p[2] == kCodeEmpty ? 4u : 0u) |
+           (q[0] == kCodeEmpty ? 8u : 0u) | (q[2] == kCodeEmpty ? 16u : 0u) | (r[0] == kCodeEmpty ? 32u : 0u) |
+           (r[1] == kCodeEmpty ? 64u : 0u) | (r[2] == kCodeEmpty ? 128u : 0u);
   }
-  __device__ __forceinline__ void put_empty(int x, int y) const { g[y * S + x] = 0; }
-  __device__ __forceinline__ void put_ball(int x, int y) const { g[y * S + x] = (uint8_t)(4u * (19u + kBlue)); }
+  __device__ __forceinline__ void put_empty(int x, int y) const { g[y * S + x] = (uint8_t)kCodeEmpty; }
+  __device__ __forceinline__ void put_ball(int x, int y) const { g[y * S + x] = (uint8_t)kCodeBall; }
 };
 
-// Whole-grid records straight from the tile's LDS codes (the fused kernel).
-// The agents are drawn into the codes beforehand (kinds 51-54, one per
-// heading) and removed afterwards, so every output byte is a function of
-// the codes alone and needs no staging: the lanes walk the tile's record
-// block [0, n) in aligned units held in registers and store each once.
-// Symbolic: 16-byte units, at most 6 cells each (18 triple bytes, taken
-// from offset r < 3); categorical: 4-byte units of 4 cells, so that
-// neighbouring lanes read neighbouring code words.  The units start on the
-// 64-byte boundary at or below the block, so that every store instruction
-// covers whole 64-byte units of HBM (which writes a partial one as a
-// read-modify-write).  Units at the block's two ends store only their bytes
-// inside [0, n) (the rest belong to the neighbouring tiles' records); their
-// reads reach at most 64 cells before the tile (21 for symbolic units) and
-// 7 after it, inside the cleared margins.
-// kNT: non-temporal stores (trajectory records); the state write-back
-// (emit_dirty_grids) uses ordinary ones, since the next launch reads it again.
-// The output bytes of a categorical unit q (4 cells) or a symbolic one (16
-// bytes of at most 6 cells), from the LDS codes.
-__device__ __forceinline__ uint32_t cat_unit(int o, const uint32_t* table, const uint8_t* codes) {
-  // the unit's 4 codes: one aligned word, or two and a byte shift
-  const int lo = o & ~3, sh = o & 3;
-  const uint32_t* cw = reinterpret_cast<const uint32_t*>(codes + lo);
-  const uint32_t c4 = __builtin_amdgcn_alignbyte(cw[1], cw[0], (uint32_t)sh);
-  uint32_t ty[4];
-#pragma unroll
-  for (int k = 0; k < 4; ++k) ty[k] = table_at(table, (c4 >> (8 * k)) & 0xFFu);
-  // bytes 0 of the four entries
-  return __builtin_amdgcn_perm(__builtin_amdgcn_perm(ty[3], ty[2], 0x0c0c0400u),
-                               __builtin_amdgcn_perm(ty[1], ty[0], 0x0c0c0400u), 0x05040100u);
-}
+// ---------------------------------------------------------------------------
+// The first-person view from the LDS codes.
+//
+// Whatever the heading, the view is a 7x7 square of the world, i.e. 7 grid
+// rows of 7 consecutive bytes: three aligned words a row instead of 49 byte
+// reads, which at random banks cost 14-20 cycles each.  The rows are loaded in
+// the order of the view's rows (north, south) or columns (east, west); south
+// and east views run backwards along a grid row, so their bytes are reversed
+// by one permute a word; east and west views are then transposed (26
+// permutes) and every lane picks its form.
+//
+// Sight blocked by a row's cells is bit 7 of their codes, gathered by dot
+// products with powers of two.  Row masks are kept in a dual form: the 7
+// column bits in bits 7-13 and the same bits reversed in bits 18-24.  One add
+// then fills runs towards higher columns in the low field and towards lower
+// columns in the high field (a carry out of either lands in an unused bit),
+// and one bit reversal merges the two.  Per view row the visible cells are
+// the seeds plus the see-through runs that touch a see-through seed, widened
+// by one cell on each side; the next row's seeds are the three cells ahead of
+// every visible see-through cell.  A row's 7 visibility bits become byte
+// masks through a 128-entry table.
+// ---------------------------------------------------------------------------
+constexpr uint32_t kDual = 0x01FC3F80u;
+constexpr uint32_t kDualCentre = (1u << 10) | (1u << 21);   // column 3
+constexpr int kMaskEntries = 128;
 
-__device__ __forceinline__ u32x4 sym_unit(int o, const uint32_t* table, const uint8_t* codes) {
-  const int c = (o + 66) / 3 - 22;   // floor(o / 3) for o >= -66
-  const uint32_t r = (uint32_t)(o - 3 * c);
-  uint32_t t[6];
+// entry v: bytes 0-6 are 0xFF where bit 0-6 of v is set, byte 7 is 0
+__device__ __forceinline__ void build_mask_table(uint2* table, int lane) {
 #pragma unroll
-  for (int k = 0; k < 6; ++k) t[k] = table_at(table, codes[c + k]) & 0xFFFFFFu;
-  // the 18 bytes t0..t5 as words, then bytes r..r+15 of them
-  const uint32_t s0 = t[0] | (t[1] << 24), s1 = (t[1] >> 8) | (t[2] << 16),
-                 s2 = (t[2] >> 16) | (t[3] << 8), s3 = t[4] | (t[5] << 24), s4 = t[5] >> 8;
-  u32x4 w;
-  w.x = __builtin_amdgcn_alignbyte(s1, s0, r);
-  w.y = __builtin_amdgcn_alignbyte(s2, s1, r);
-  w.z = __builtin_amdgcn_alignbyte(s3, s2, r);
-  w.w = __builtin_amdgcn_alignbyte(s4, s3, r);
-  return w;
-}
-
-template <bool kCat, bool kNT>
-__device__ __forceinline__ void store_unit(uintptr_t a, uintptr_t d0, uintptr_t d1, u32x4 w) {
-  constexpr int kUnit = kCat ? 4 : 16;
-  if (a >= d0 && a + kUnit <= d1) {
-    if (kCat) {
-      if (kNT) __builtin_nontemporal_store(w.x, reinterpret_cast<uint32_t*>(a));
-      else *reinterpret_cast<uint32_t*>(a) = w.x;
-    } else {
-      if (kNT) __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(a));
-      else *reinterpret_cast<u32x4*>(a) = w;
+  for (int k = 0; k < kMaskEntries / kWave; ++k) {
+    const uint32_t v = (uint32_t)(lane + k * kWave);
+    uint32_t lo = 0, hi = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+      lo |= ((v >> b) & 1u) ? 0xFFu << (8 * b) : 0u;
+      hi |= (b < 3 && ((v >> (4 + b)) & 1u)) ? 0xFFu << (8 * b) : 0u;
     }
-  } else {
-#pragma unroll
-    for (int b = 0; b < kUnit; ++b)
-      if (a + b >= d0 && a + b < d1) reinterpret_cast<uint8_t*>(a)[b] = (uint8_t)(w[b >> 2] >> (8 * (b & 3)));
+    table[v] = make_uint2(lo, hi);
   }
 }
 
-template <bool kCat, bool kNT = true>
-__device__ __forceinline__ void emit_tile_grids(uint8_t* dst, int n_cells, const uint32_t* table,
-                                                const uint8_t* codes, int lane) {
-  constexpr int kUnit = kCat ? 4 : 16;
-  // units per lane in flight: all their LDS reads are issued before the
-  // first of their stores, so the reads' latency overlaps
-  constexpr int kDepth = 4;
-  const int64_t n = kCat ? n_cells : 3 * (int64_t)n_cells;
-  const uintptr_t d0 = reinterpret_cast<uintptr_t>(dst), d1 = d0 + (uintptr_t)n;
-  const uintptr_t A = d0 & ~(uintptr_t)63;
-  const int rel = (int)((int64_t)A - (int64_t)d0);   // in [-63, 0]
-  const int units = (int)((d1 - A + kUnit - 1) / kUnit);
-  for (int q0 = lane; q0 < units; q0 += kDepth * kWave) {
-    // a unit past the block's last one reads that last unit's cells again
-    u32x4 w[kDepth];
+// transposes the 4x4 bytes of a, b, c, d (rows) into columns
+__device__ __forceinline__ void transpose4(uint32_t a, uint32_t b, uint32_t c, uint32_t d, uint32_t (&t)[4]) {
+  const uint32_t ab0 = perm(b, a, 0x05010400u), ab1 = perm(b, a, 0x07030602u);
+  const uint32_t cd0 = perm(d, c, 0x05010400u), cd1 = perm(d, c, 0x07030602u);
+  t[0] = perm(cd0, ab0, 0x05040100u);
+  t[1] = perm(cd0, ab0, 0x07060302u);
+  t[2] = perm(cd1, ab1, 0x05040100u);
+  t[3] = perm(cd1, ab1, 0x07060302u);
+}
+
+// the first three bytes of each column of a, b, c (rows); byte 3 is c's next
+__device__ __forceinline__ void transpose3(uint32_t a, uint32_t b, uint32_t c, uint32_t (&t)[4]) {
+  const uint32_t ab0 = perm(b, a, 0x05010400u), ab1 = perm(b, a, 0x07030602u);
+  t[0] = perm(c, ab0, 0x0C040100u);
+  t[1] = perm(c, ab0, 0x0C050302u);
+  t[2] = perm(c, ab1, 0x0C060100u);
+  t[3] = perm(c, ab1, 0x0C070302u);
+}
+
+// The lane's view as 13 words of codes f[0..12], cell j * 7 + i (view row j,
+// column i) at byte j * 7 + i, unseen cells and the bytes past the 49th 0.
+// at: the agent's cell's byte offset in `lds` (its grid's rows are S bytes
+// apart).  check (wave-uniform): cells outside the grid are taken as walls on
+// lanes with `edge` set, for the rare step whose view can leave the grid,
+// through a door on the outer ring that the step itself opened (GoToDoor
+// rooms use the grid's border as walls).
+__device__ __forceinline__ void view_codes(const uint8_t* lds, int at, int S, int x, int y, int dir,
+                                           uint32_t carry_code, const uint2* masks, bool check, bool edge,
+                                           uint32_t (&f)[13]) {
+  const bool vert = (dir & 1) != 0;            // south, north
+  const bool back = dir == 1 || dir == 2;      // rows loaded bottom up
+  const bool flip = dir < 2;                   // rows read backwards
+  const int step = back ? -S : S;
+  int idx = at - (vert ? 3 : (dir == 0 ? 0 : 6)) - (vert ? 6 : 3) * step;
+  const uint32_t sel_lo = flip ? 0x03040506u : 0x03020100u;
+  const uint32_t sel_hi = flip ? 0x0C000102u : 0x0C060504u;
+  uint32_t lo[kView], hi[kView], raw[kView][3];
+  int at_row = idx;
 #pragma unroll
-    for (int u = 0; u < kDepth; ++u) {
-      const int o = rel + kUnit * min(q0 + u * kWave, units - 1);   // output byte of the unit's first byte
-      if (kCat) w[u] = u32x4{cat_unit(o, table, codes), 0u, 0u, 0u};
-      else w[u] = sym_unit(o, table, codes);
-    }
+  for (int r = 0; r < kView; ++r) {
+    const uint32_t* p = reinterpret_cast<const uint32_t*>(lds + (at_row & ~3));
 #pragma unroll
-    for (int u = 0; u < kDepth; ++u) {
-      const int q = q0 + u * kWave;
-      if (q < units) store_unit<kCat, kNT>(A + (uintptr_t)(kUnit * q), d0, d1, w[u]);
+    for (int k = 0; k < 3; ++k) raw[r][k] = p[k];
+    at_row += step;
+  }
+  __builtin_amdgcn_sched_barrier(0);   // all reads in flight before the first is used
+#pragma unroll
+  for (int r = 0; r < kView; ++r) {
+    const uint32_t sh = (uint32_t)idx & 3u;
+    const uint32_t l = __builtin_amdgcn_alignbyte(raw[r][1], raw[r][0], sh);
+    const uint32_t h = __builtin_amdgcn_alignbyte(raw[r][2], raw[r][1], sh);
+    lo[r] = perm(h, l, sel_lo);
+    hi[r] = perm(h, l, sel_hi);
+    idx += step;
+  }
+  {
+    uint32_t a[4], b[4], c[4], d[4];
+    transpose4(lo[0], lo[1], lo[2], lo[3], a);
+    transpose4(hi[0], hi[1], hi[2], hi[3], b);
+    transpose3(lo[4], lo[5], lo[6], c);
+    transpose3(hi[4], hi[5], hi[6], d);
+#pragma unroll
+    for (int r = 0; r < kView; ++r) {
+      lo[r] = vert ? lo[r] : (r < 4 ? a[r & 3] : b[r & 3]);
+      hi[r] = vert ? hi[r] : (r < 4 ? c[r & 3] : d[r & 3]);
     }
   }
+  if (check) {
+    const int e = S - 1 - x, s = S - 1 - y;   // cells to the east and south
+    const int ahead = dir == 0 ? e : (dir == 1 ? s : (dir == 2 ? x : y));
+    const int left = dir == 0 ? y : (dir == 1 ? e : (dir == 2 ? s : x));
+    const int right = dir == 0 ? s : (dir == 1 ? x : (dir == 2 ? y : e));
+    const uint32_t cols = (0x7Fu << max(3 - left, 0)) & (0x7Fu >> max(3 - right, 0)) & 0x7Fu;
+    const uint2 m = masks[cols];
+#pragma unroll
+    for (int r = 0; r < kView; ++r) {
+      const bool in = 6 - r <= ahead;
+      const uint32_t ml = edge ? (in ? m.x : 0u) : ~0u, mh = edge ? (in ? m.y : 0u) : ~0u;
+      lo[r] = (lo[r] & ml) | (kCodeWall4 & ~ml);
+      hi[r] = (hi[r] & mh) | (kCodeWall4 & ~mh);
+    }
+  }
+  uint32_t seeds = kDualCentre;
+#pragma unroll
+  for (int j = kView - 1; j >= 0; --j) {
+    const uint32_t o = __builtin_amdgcn_udot4(lo[j] & 0x80808080u, 0x08040201u,
+                                              __builtin_amdgcn_udot4(hi[j] & 0x80808080u, 0x00402010u, 0u, false),
+                                              false);
+    const uint32_t p = ~(o | __builtin_bitreverse32(o)) & kDual;   // see-through, dual form
+    const uint32_t g = seeds & p;
+    const uint32_t fill = (((p + g) ^ p) | g) & p;
+    const uint32_t run = fill | __builtin_bitreverse32(fill);
+    const uint32_t next = (run | (run << 1) | (run >> 1)) & kDual;
+    const uint32_t vis = seeds | next;
+    seeds = next;
+    const uint2 m = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(masks) + ((vis >> 4) & 0x3F8u));
+    lo[j] &= m.x;
+    hi[j] &= m.y;
+  }
+  lo[6] = (lo[6] & 0x00FFFFFFu) | (carry_code << 24);   // the agent's cell shows what it carries
+  f[0] = lo[0];
+  f[1] = perm(lo[1], hi[0], 0x04020100u);
+  f[2] = perm(hi[1], lo[1], 0x04030201u);
+  f[3] = perm(lo[2], hi[1], 0x05040201u);
+  f[4] = perm(hi[2], lo[2], 0x05040302u);
+  f[5] = perm(lo[3], hi[2], 0x06050402u);
+  f[6] = perm(hi[3], lo[3], 0x06050403u);
+  f[7] = lo[4];
+  f[8] = perm(lo[5], hi[4], 0x04020100u);
+  f[9] = perm(hi[5], lo[5], 0x04030201u);
+  f[10] = perm(lo[6], hi[5], 0x05040201u);
+  f[11] = perm(hi[6], lo[6], 0x05040302u);
+  f[12] = (hi[6] >> 16) & 0xFFu;
+}
+
+// Writes the first n lanes' views (49 codes each) one after another at
+// `stage`.  Lane l's start 49 l mod 4 = l mod 4 bytes into a word, which then
+// holds the last cells of lane l - 1 as well: that word is the higher lane's,
+// with the lower one's last word received by a lane shift.
+__device__ __forceinline__ void store_view(uint32_t* stage, const uint32_t (&f)[13], int lane, int n) {
+  const uint32_t k = (uint32_t)lane & 3u;
+  const uint32_t sel = 0x07060504u - k * 0x01010101u;
+  uint32_t g[13];
+  g[0] = perm(f[0], 0u, sel);
+#pragma unroll
+  for (int q = 1; q < 13; ++q) g[q] = perm(f[q], f[q - 1], sel);
+  const uint32_t tail = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)g[12], 0x138, 0xF, 0xF, true);   // lane - 1's
+  g[0] |= k != 0 ? tail : 0u;
+  if (lane < n) {
+    uint32_t* p = stage + ((uint32_t)(kCatBytes * lane) >> 2);
+#pragma unroll
+    for (int q = 0; q < 12; ++q) p[q] = g[q];
+    if (k == 3 || lane == n - 1) p[12] = g[12];
+  }
+}
+
+// ---------------------------------------------------------------------------
+// Records and grids from codes.
+//
+// n consecutive cells at `cells` (LDS) leave as 3 n triple bytes (or n type
+// bytes, kCat) at dst, any alignment.  A wave pass takes 256 cells, four a
+// lane: one word read, a dozen byte-parallel operations and one 12-byte store,
+// 768 contiguous bytes a pass.  Passes start c0 cells in, where 3 c0 bytes
+// reach dst's next 64-byte boundary (3 * 43 = 1 mod 64), so every pass covers
+// whole 64-byte units of HBM (which writes a partial one as a
+// read-modify-write); the c0 cells before are the last of an extra first
+// pass.  Stores of a constant in this pattern reach 5.2 TB/s, 16-byte stores
+// of the same bytes 5.1, and passes off the boundary 3.9-4.7, at 262 144
+// tiles' rows of 9408 bytes.
+// Groups cut by either end store their bytes one by one.  Reads reach at
+// most 4 bytes before the cells and 8 past them.
+// ---------------------------------------------------------------------------
+typedef uint32_t u32x3 __attribute__((ext_vector_type(3)));
+typedef u32x3 u32x3_any __attribute__((aligned(1)));
+typedef u32x4 u32x4_any __attribute__((aligned(1)));
+
+// first cell of pass 0 (in (-64, 0]) for an output at dst
+template <bool kCat>
+__device__ __forceinline__ int first_cell(const uint8_t* dst) {
+  const uint32_t d = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)reinterpret_cast<uintptr_t>(dst));
+  const int c0 = (int)((0u - d) * (kCat ? 1u : 43u)) & 63;
+  return c0 ? c0 - 64 : 0;
+}
+
+// word of codes at cell c (kShift: c is not a multiple of 4, c mod 4 = sh)
+template <bool kShift>
+__device__ __forceinline__ uint32_t load_cells(const uint8_t* cells, int c, uint32_t sh) {
+  const uint32_t* p = reinterpret_cast<const uint32_t*>(cells + (c & ~3));
+  return kShift ? __builtin_amdgcn_alignbyte(p[1], p[0], sh) : p[0];
+}
+
+template <bool kAgents, bool kNT>
+__device__ __forceinline__ void store_cells(uint8_t* dst, uint32_t w) {
+  uint32_t o[3];
+  interleave(decode_cells<kAgents>(w), o);
+  const u32x3 v = {o[0], o[1], o[2]};
+  if (kNT) __builtin_nontemporal_store(v, reinterpret_cast<u32x3_any*>(dst));
+  else *reinterpret_cast<u32x3_any*>(dst) = v;
+}
+
+// the whole groups of the pass from cell p on that lie inside [0, n)
+template <bool kAgents, bool kShift, bool kNT>
+__device__ __forceinline__ void emit_some(uint8_t* dst, const uint8_t* cells, int n, int p, uint32_t sh, int lane,
+                                          bool keep = true) {
+  const int c = p + 4 * lane;
+  const uint32_t w = load_cells<kShift>(cells, min(max(c, 0), n), sh);
+  if (keep && c >= 0 && c + 4 <= n) store_cells<kAgents, kNT>(dst + 3 * c, w);
+}
+
+// the triples (kCat: types) of the first `head` and the last `tail` cells, at
+// most 15 each, a byte per lane
+template <bool kAgents, bool kCat>
+__device__ __forceinline__ void emit_ends(uint8_t* dst, const uint8_t* cells, int n, int head, int tail, int lane) {
+  constexpr int kPer = kCat ? 1 : 3;
+  const int half = lane >> 5, b = lane & 31, cell = kCat ? b : b / 3;
+  const int at = half ? n - tail + cell : cell;
+  if (b < kPer * (half ? tail : head) && at < n) {
+    const Cells4 v = decode_cells<kAgents>(cells[at]);
+    const int ch = kCat ? 0 : b - 3 * cell;
+    dst[kPer * at + ch] = (uint8_t)(ch == 0 ? v.type : (ch == 1 ? v.colour : v.state));
+  }
+}
+
+// kDepth passes from cell p on, their LDS reads issued together.  kWhole: all
+// inside [0, n), so that no group needs a bounds test.
+template <bool kAgents, bool kShift, int kDepth, bool kWhole>
+__device__ __forceinline__ void emit_block(uint8_t* dst, const uint8_t* cells, int n, int p, uint32_t sh, int lane) {
+  constexpr int kPass = 4 * kWave;
+  uint32_t w[kDepth], o[kDepth][3];
+  const int c0 = p + 4 * lane;
+#pragma unroll
+  for (int u = 0; u < kDepth; ++u) {
+    const int c = c0 + u * kPass;
+    w[u] = load_cells<kShift>(cells, kWhole ? c : min(max(c, 0), n), sh);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int u = 0; u < kDepth; ++u) {
+    interleave(decode_cells<kAgents>(w[u]), o[u]);
+    // not to be moved under the store's bounds test
+    if (!kWhole) asm volatile("" : "+v"(o[u][0]), "+v"(o[u][1]), "+v"(o[u][2]));
+  }
+#pragma unroll
+  for (int u = 0; u < kDepth; ++u) {
+    const int c = c0 + u * kPass;
+    const u32x3 q = {o[u][0], o[u][1], o[u][2]};
+    if (kWhole || (c >= 0 && c + 4 <= n))
+      __builtin_nontemporal_store(q, reinterpret_cast<u32x3_any*>(dst + 3 * c));
+  }
+}
+
+template <bool kAgents, bool kShift>
+__device__ __forceinline__ void emit_passes(uint8_t* dst, const uint8_t* cells, int n, int start, int lane) {
+  constexpr int kPass = 4 * kWave;
+  constexpr int kDeep = 4;
+  const uint32_t sh = (uint32_t)start & 3u;
+  int p = start;
+  if (p < 0 && n > kDeep * kPass) {
+    emit_block<kAgents, kShift, 1, false>(dst, cells, n, p, sh, lane);
+    p += kPass;
+  }
+  for (; p + kPass < n; p += kDeep * kPass) {
+    if (p >= 0 && p + kDeep * kPass <= n) emit_block<kAgents, kShift, kDeep, true>(dst, cells, n, p, sh, lane);
+    else emit_block<kAgents, kShift, kDeep, false>(dst, cells, n, p, sh, lane);
+  }
+  if (p < n) emit_block<kAgents, kShift, 1, false>(dst, cells, n, p, sh, lane);
+  const int head = start & 3, tail = (n - start) & 3;
+  if (head | tail) emit_ends<kAgents, false>(dst, cells, n, min(head, n), tail, lane);
+}
+
+template <bool kAgents>
+__device__ __forceinline__ void emit_triples(uint8_t* dst, const uint8_t* cells, int n, int lane) {
+  const int start = first_cell<false>(dst);
+  if (start & 3) emit_passes<kAgents, true>(dst, cells, n, start, lane);
+  else emit_passes<kAgents, false>(dst, cells, n, start, lane);
+}
+
+// types alone: 16 cells a lane and store
+__device__ __forceinline__ void emit_types(uint8_t* dst, const uint8_t* cells, int n, int lane) {
+  const int start = first_cell<true>(dst);
+  const uint32_t sh = (uint32_t)start & 3u;
+  for (int p = start; p < n; p += 16 * kWave) {
+    const int c = p + 16 * lane;
+    const uint32_t* q = reinterpret_cast<const uint32_t*>(cells + (min(max(c, 0), n) & ~3));
+    uint32_t w[5];
+#pragma unroll
+    for (int k = 0; k < 5; ++k) w[k] = q[k];
+    u32x4 v;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] = types4(__builtin_amdgcn_alignbyte(w[k + 1], w[k], sh));
+    if (c >= 0 && c + 16 <= n) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any*>(dst + c));
+  }
+  const int head = start & 15, tail = (n - start) & 15;
+  if (head | tail) emit_ends<true, true>(dst, cells, n, min(head, n), tail, lane);
 }
 
 // Write-back of the grids that changed in a launch (the lanes with `dirty`
 // set; every other env's grid in HBM still holds the bytes staged in, so
-// writing it again would change nothing).  The dirty lanes mark the 64-byte
-// lines of the tile's block that their grids touch, in a bitmap in `lines`
-// (LDS, one bit per line), and the symbolic units of emit_tile_grids are
-// then stored for the marked lines only: a line's other bytes belong to
-// neighbouring envs and are rewritten with their current cells, which equal
-// what HBM holds, and the units at the block's two ends store only their
-// bytes inside it.
+// writing it again would change nothing).  The dirty lanes mark the blocks
+// of 64 cells (192 bytes, on 64-byte boundaries of the output) that their
+// grids touch, in a bitmap in `marks` (LDS), and the passes of emit_triples
+// store the marked blocks only: a block's other cells belong to neighbouring
+// envs and are rewritten with their current values, which equal what HBM
+// holds.  Ordinary stores, since the next launch reads the grids again.
 __device__ __forceinline__ void emit_dirty_grids(uint8_t* dst, int n_cells, bool dirty, int my_off, int my_cells,
-                                                 const uint32_t* table, const uint8_t* codes, uint32_t* lines,
-                                                 int lane) {
-  const uintptr_t d0 = reinterpret_cast<uintptr_t>(dst), d1 = d0 + 3 * (uintptr_t)(uint32_t)n_cells;
-  const uintptr_t A = d0 & ~(uintptr_t)63;
-  const int rel = (int)((int64_t)A - (int64_t)d0);   // in [-63, 0]
-  const int units = (int)((d1 - A + 15) / 16);
-  const int n_words = (((units + 3) >> 2) + 31) >> 5;
-  for (int w = lane; w < n_words; w += kWave) lines[w] = 0u;
+                                                 const uint8_t* codes, uint32_t* marks, int lane) {
+  if (!__ballot(dirty)) return;
+  const int start = first_cell<false>(dst);
+  const int blocks = (n_cells - start + 63) >> 6;
+  for (int w = lane; w < (blocks + 31) >> 5; w += kWave) marks[w] = 0u;
   wave_sync();
   if (dirty && my_cells > 0) {
-    // lines [l0, l1) hold this grid's bytes; at most 49 lines, so 3 words
-    const int l0 = (3 * my_off - rel) >> 6, l1 = (3 * (my_off + my_cells) - rel + 63) >> 6;
-    for (int w = l0 >> 5; w <= (l1 - 1) >> 5; ++w) {
-      const int lo = max(l0 - 32 * w, 0), hi = min(l1 - 32 * w, 32);
-      atomicOr(&lines[w], (hi - lo == 32 ? ~0u : ((1u << (hi - lo)) - 1u)) << lo);
+    const int b0 = (my_off - start) >> 6, b1 = (my_off + my_cells - 1 - start) >> 6;   // at most 17 blocks
+    for (int w = b0 >> 5; w <= b1 >> 5; ++w) {
+      const int lo = max(b0 - 32 * w, 0), hi = min(b1 - 32 * w, 31);
+      atomicOr(&marks[w], (~0u >> (31 - (hi - lo))) << lo);
     }
   }
   wave_sync();
-  constexpr int kDepth = 4;
-  for (int qb = lane; qb < units; qb += kDepth * kWave) {
-    u32x4 w[kDepth];
-    bool keep[kDepth];
-#pragma unroll
-    for (int u = 0; u < kDepth; ++u) {
-      const int q = qb + u * kWave;
-      keep[u] = q < units && ((lines[q >> 7] >> ((q >> 2) & 31)) & 1u) != 0;
-      w[u] = keep[u] ? sym_unit(rel + 16 * q, table, codes) : u32x4{0u, 0u, 0u, 0u};
-    }
-#pragma unroll
-    for (int u = 0; u < kDepth; ++u)
-      if (keep[u]) store_unit<false, false>(A + (uintptr_t)(16 * (qb + u * kWave)), d0, d1, w[u]);
+  const uint32_t sh = (uint32_t)start & 3u;
+  for (int p = 0; 4 * p < blocks; ++p) {   // a pass: four blocks
+    const uint32_t m = (marks[p >> 3] >> (4 * (p & 7))) & 15u;
+    if (__builtin_amdgcn_readfirstlane((int)m))
+      emit_some<false, true, false>(dst, codes, n_cells, start + 4 * kWave * p, sh, lane, (m >> (lane >> 4)) & 1u);
   }
-}
-
-// Kind codes of triples by table: entry type << 5 | colour << 2 | state
-// (types 0-15, colours 0-7, states 0-3) holds code_of of that triple.  A
-// valid grid holds only types 0-9, colours 0-5 and states 0-2, so its every
-// cell gets code_of's code for five instructions and one LDS read instead
-// of code_of's fifteen; bits of a triple beyond those fields are ignored.
-// The table lives in the record stage while a tile is staged in.
-constexpr int kCodeLutBytes = 512;
-
-__device__ __forceinline__ void build_code_lut(uint8_t* lut, int lane) {
-#pragma unroll
-  for (int k = 0; k < kCodeLutBytes / kWave; ++k) {
-    const uint32_t i = (uint32_t)(lane + k * kWave);
-    lut[i] = (uint8_t)code_of((i >> 5) | (((i >> 2) & 7u) << 8) | ((i & 3u) << 16));
-  }
-}
-
-__device__ __forceinline__ uint32_t lut_code(const uint8_t* lut, uint32_t tri) {
-  const uint32_t i = ((tri & 15u) << 5) | (((tri >> 8) & 7u) << 2) | ((tri >> 16) & 3u);
-  return lut[i];
+  const int head = start & 3, tail = (n_cells - start) & 3;
+  if (head | tail) emit_ends<false, false>(dst, codes, n_cells, min(head, n_cells), tail, lane);
 }
 
 // Stages a tile's grids, the 3 * n_cells bytes at src (any alignment), into
@@ -1780,10 +1990,9 @@ __device__ __forceinline__ uint32_t lut_code(const uint8_t* lut, uint32_t tri) {
 // conversion is instantiated per r / 4, so the realignment needs no
 // selects).  A chunk past the block's last one is read as that last chunk
 // (so every load lies in the block's own memory pages); the codes of the at
-// most 15 cells past n_cells land in the trailing LDS margin, which needs
-// nothing but valid codes, and every table entry is one.  The lane's next
-// run is loaded before its current run is converted, so the wave's reads
-// stay in flight while it converts.
+// most 15 cells past n_cells land in the trailing LDS margin.  The lane's
+// next run is loaded before its current run is converted, so the wave's
+// reads stay in flight while it converts.
 struct GridRun {
   u32x4 q[4];
 };
@@ -1793,13 +2002,13 @@ __device__ __forceinline__ GridRun load_run(uintptr_t a, uintptr_t last) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const uintptr_t c = a + 16 * (uintptr_t)k;
-    g.q[k] = *reinterpret_cast<const u32x4*>(c < last ? c : last);
+    g.q[k] = *(const __attribute__((address_space(1))) u32x4*)(c < last ? c : last);
   }
   return g;
 }
 
 template <int kRW>
-__device__ __forceinline__ void convert_run(const GridRun& g, uint32_t rb, const uint8_t* lut, uint8_t* dst) {
+__device__ __forceinline__ void convert_run(const GridRun& g, uint32_t rb, uint8_t* dst) {
   uint32_t w[16];
 #pragma unroll
   for (int k = 0; k < 4; ++k)
@@ -1810,20 +2019,15 @@ __device__ __forceinline__ void convert_run(const GridRun& g, uint32_t rb, const
 #pragma unroll
   for (int i = 0; i < 12; ++i)
     b[i] = i + kRW + 1 < 16 ? __builtin_amdgcn_alignbyte(w[i + kRW + 1], w[i + kRW], rb) : w[i + kRW] >> (8 * rb);
-  uint32_t out[4] = {0u, 0u, 0u, 0u};
+  u32x4 out;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) {
-    const int d = (3 * k) >> 2, off = (3 * k) & 3;
-    const uint32_t tri = d + 1 < 12 ? __builtin_amdgcn_alignbyte(b[d + 1], b[d], (uint32_t)off)
-                                    : b[d] >> (8 * off);
-    out[k >> 2] |= lut_code(lut, tri) << (8 * (k & 3));
-  }
-  *reinterpret_cast<u32x4*>(dst) = u32x4{out[0], out[1], out[2], out[3]};
+  for (int k = 0; k < 4; ++k) out[k] = encode_cells(b[3 * k], b[3 * k + 1], b[3 * k + 2]);
+  *reinterpret_cast<u32x4*>(dst) = out;
 }
 
 template <int kRW>
 __device__ __forceinline__ void stage_in_runs(uintptr_t a0, uintptr_t last, uint32_t rb, int units,
-                                              const uint8_t* lut, uint8_t* codes, int lane) {
+                                              uint8_t* codes, int lane) {
   int u = lane;
   if (u >= units) return;
   GridRun cur = load_run(a0 + 48 * (uintptr_t)u, last);
@@ -1832,26 +2036,24 @@ __device__ __forceinline__ void stage_in_runs(uintptr_t a0, uintptr_t last, uint
     const bool more = nu < units;
     GridRun nxt;
     if (more) nxt = load_run(a0 + 48 * (uintptr_t)nu, last);
-    convert_run<kRW>(cur, rb, lut, codes + 16 * u);
+    convert_run<kRW>(cur, rb, codes + 16 * u);
     if (!more) break;
     cur = nxt;
     u = nu;
   }
 }
 
-// lut: the code table (build_code_lut), visible to every lane
-__device__ __forceinline__ void stage_in_codes(const uint8_t* src, int n_cells, uint8_t* codes,
-                                               const uint8_t* lut, int lane) {
+__device__ __forceinline__ void stage_in_codes(const uint8_t* src, int n_cells, uint8_t* codes, int lane) {
   const uintptr_t s0 = reinterpret_cast<uintptr_t>(src);
   const uint32_t r = (uint32_t)__builtin_amdgcn_readfirstlane((int)(s0 & 15u));
   const uintptr_t end = s0 + 3 * (uintptr_t)(uint32_t)n_cells;
   const uintptr_t a0 = s0 - r, last = (end - 1) & ~(uintptr_t)15;
   const int units = (n_cells + 15) >> 4;
   switch (r >> 2) {
-    case 0: stage_in_runs<0>(a0, last, r & 3u, units, lut, codes, lane); break;
-    case 1: stage_in_runs<1>(a0, last, r & 3u, units, lut, codes, lane); break;
-    case 2: stage_in_runs<2>(a0, last, r & 3u, units, lut, codes, lane); break;
-    default: stage_in_runs<3>(a0, last, r & 3u, units, lut, codes, lane); break;
+    case 0: stage_in_runs<0>(a0, last, r & 3u, units, codes, lane); break;
+    case 1: stage_in_runs<1>(a0, last, r & 3u, units, codes, lane); break;
+    case 2: stage_in_runs<2>(a0, last, r & 3u, units, codes, lane); break;
+    default: stage_in_runs<3>(a0, last, r & 3u, units, codes, lane); break;
   }
 }
 
@@ -1880,6 +2082,14 @@ __device__ __forceinline__ void fill_layouts(uint64_t pending, const Layout& L, 
   }
 }
 
+// the stage of a wave's views: 64 of 49 codes, and what emit_* may read
+// before and past them
+constexpr int kStageMargin = 16;
+constexpr int kViewStageBytes = kStageMargin + kWave * kCatBytes + 32;
+// words of emit_dirty_grids's bitmap: one bit per 64 cells of at most 64
+// grids of side 32, starting up to 63 cells before the first
+constexpr int kMarkWords = ((kWave * 32 * 32 + 63 + 63) / 64 + 31) / 32;
+
 struct FusedArgs {
   EnvTables env;
   TileTables tiles;
@@ -1904,6 +2114,15 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
   return incl - v;
 }
 
+// What bounds a step: with few tiles (up to one wave per SIMD, 65 536 envs)
+// one wave's own instruction stream, 5 cycles per independent vector
+// instruction and 8 per dependent one, 14-20 per LDS read; with many, the
+// record stores.  Views and records computed on bytes (four cells a word)
+// instead of a table read per cell took the LDS instructions of a step from
+// 153 to about 60: 65 536 TwoRoom 8x8 envs 3.2 -> 2.6 us a step, 30 011 envs of
+// the uneven mix (rows off every alignment) 5.9 -> 3.5 us, 65 536 mixed
+// envs' whole grids 10.0 -> 7.7 us, 262 144 mixed envs' 20 steps 242 -> 222 us.
+//
 // kActions: actions come from a.actions; otherwise from the random policy.
 // kServe: tiles belong to requests described by a.serve (serving): each runs
 // min(K, steps it has left) steps from its own counter step0, writes to its
@@ -1917,10 +2136,12 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
 // the policy variant has no loads in its step loop at all.
 template <bool kActions, bool kServe, int kObs>
 __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
-  // static LDS (table and record stage) sits at fixed addresses, so table
-  // reads take their base as an immediate; the tile grids are dynamic
-  __shared__ __align__(16) uint32_t table[kKinds * kView];
-  __shared__ __align__(16) uint8_t stage[kRecStageBytes];
+  // first-person variants: the byte masks of a row's visibility bits, and the
+  // stage of the wave's views; whole-grid records need only the bitmap of
+  // emit_dirty_grids, which takes the stage's place after the last step
+  __shared__ __align__(16) uint2 masks[kObs == 2 ? 1 : kMaskEntries];
+  __shared__ __align__(16) uint32_t stage_words[kObs == 2 ? kMarkWords : kViewStageBytes / 4];
+  static_assert(kObs == 2 || kMarkWords * 4 <= kViewStageBytes, "the bitmap fits the view stage");
   // per lane: whether a pickup, drop or toggle changed a cell of its grid
   __shared__ uint8_t cell_changed[kWave];
   extern __shared__ __align__(16) uint8_t grids[];
@@ -1928,22 +2149,13 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
   const int lane = threadIdx.x;
   const int N = a.env.n;
 
-  {
-    const uint32_t t = triple_of_kind((uint32_t)lane);   // kKinds == kWave entries
-#pragma unroll
-    for (int i = 0; i < kView; ++i) table[kKinds * i + lane] = (t & ~kSeeBit) | ((t & kSeeBit) >> i);
+  // a view's first cell lies kStageMargin bytes in (emit_* read a little
+  // before and past their cells)
+  uint32_t* const stage = stage_words + kStageMargin / 4;
+  if (kObs != 2) {
+    build_mask_table(masks, lane);
+    wave_sync();
   }
-  // Every byte a view may read holds a code from here on: the margins and
-  // any space past a small tile are cleared once (code 0, an empty cell),
-  // and the kernel only ever writes codes.  An arbitrary byte would index
-  // the tables off an entry boundary and could set another column's
-  // see-through flag, which the row's combined flags would then pick up.
-  {
-    const uint32_t quads = (uint32_t)(tile_lds_bytes(a.tiles.max_tile_cells) >> 4);
-    for (uint32_t w = (uint32_t)lane; w < quads; w += kWave)
-      reinterpret_cast<u32x4*>(grids)[w] = u32x4{0u, 0u, 0u, 0u};
-  }
-  wave_sync();
 
   for (int it = blockIdx.x; it < a.tiles.n_tiles; it += gridDim.x) {
     // serving lists mark a newly admitted tile with the top bit: its
@@ -2048,16 +2260,18 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     if (fresh) {
       fill_layouts(__ballot(active), L0, codes, my_off, lane);
     } else {
-      // the record stage is idle until the first step: it holds the code table
-      build_code_lut(stage, lane);
-      wave_sync();
-      stage_in_codes(a.st.grid + g0, tile_cells, codes, stage, lane);
+      stage_in_codes(a.st.grid + g0, tile_cells, codes, lane);
     }
+    uint32_t carry_code = code_of(carry);
+    bool carry_changed = fresh;   // until then the state's own triple stays
+    const bool any_balls = __ballot(fam == kFamDynObs) != 0, any_missions = __ballot(fam == kFamGoToDoor) != 0;
+    int pos = y * S + x;          // the agent's cell in its grid
     wave_sync();
 
     uint4 pol = make_uint4(0, 0, 0, 0);
     uint32_t act_next = 0;
     if (kActions && active) act_next = a.actions[e];
+    int ring_row = kServe ? 0 : a.row0;   // output row of the next step
     for (int s = 0; s < steps; ++s) {
       // the env's call count; envs stepped together share it, so the policy
       // block refresh every 4 calls is uniform across the wave in practice
@@ -2078,8 +2292,10 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
         x = L.ax;
         y = L.ay;
         dir = L.dir;
+        pos = y * S + x;
         t = 0;
-        carry = kCellEmpty;
+        carry_code = kCodeEmpty;
+        carry_changed = true;
 #pragma unroll
         for (int i = 0; i < 4; ++i) ob[i] = L.ob[i];
       }
@@ -2089,104 +2305,86 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
         wave_sync();
       }
 
+      // lanes that reset, and lanes without an env, act as 6 (no effect)
+      const bool live = active && !do_reset;
       float reward = 0.0f;
-      uint32_t flags = 0, act_rec = kActionNone;
       bool edge_view = false;
-      if (active && !do_reset) {
-        uint32_t act = kActions ? act_now : bounded(pick4(pol, call & 3u), 7u);
-        const int fx = x + dir_dx(dir), fy = y + dir_dy(dir);
-        uint32_t front = table_at(table, my_codes[fy * S + fx]);
-        bool blocked = false;
-        if (fam == kFamDynObs) {
-          // three actions; the cell ahead is judged before the balls move
-          act = act > kForward ? kLeft : act;
-          blocked = (front & 0xFF) != kEmpty && (front & 0xFF) != kGoal;
-          move_obstacles(LdsGrid{my_codes, S}, (int)((meta >> 16) & 0xFF), x, y, ob, seed, rid, call);
-          front = table_at(table, my_codes[fy * S + fx]);
-        }
-        ActResult r = intervene(act, x, y, dir, carry, front, fx, fy);
-        r.penalty = r.penalty || (blocked && act == kForward);
-        r.terminated = r.terminated || r.penalty;
-        if (fam == kFamGoToDoor) {
-          gotodoor_rules(r, act, front, ob[0] & 0xFFu);
-          edge_view = r.front_changed;   // a door toggled, possibly on the outer ring
-        }
-        if (r.front_changed) {
-          my_codes[fy * S + fx] = (uint8_t)code_of(r.new_front);
-          cell_changed[lane] = 1;
-        }
-        t += 1;
-        const bool trunc = t >= T;
-        reward = step_reward(r, t, T, a.env.reward_mode);
-        flags = (r.terminated ? kFlagTerminated : 0u) | (trunc ? kFlagTruncated : 0u);
-        done_prev = r.terminated || trunc;
-        act_rec = act & 0xFF;
-      } else if (do_reset) {
-        flags = kFlagFirst;
-        done_prev = false;
+      uint32_t act = live ? (kActions ? act_now : bounded(pick4(pol, call & 3u), 7u)) : 6u;
+      // one cell ahead: (dx, dy) by heading from two-bit fields (dx + 1, dy + 1)
+      const uint32_t dir2 = 2u * (uint32_t)dir;
+      const int dx = (int)((0x46u >> dir2) & 3u) - 1, dy = (int)((0x19u >> dir2) & 3u) - 1;
+      const int ahead = pos + dy * S + dx;
+      uint32_t front = my_codes[ahead];
+      uint32_t penalty = 0;
+      if (any_balls && fam == kFamDynObs && live) {
+        // three actions; the cell ahead is judged before the balls move
+        act = act > kForward ? kLeft : act;
+        penalty = (act == kForward && front != kCodeEmpty && (front & 0x8Fu) != kGoal) ? 1u : 0u;
+        move_obstacles(LdsGrid{my_codes, S}, (int)((meta >> 16) & 0xFF), x, y, ob, seed, rid, call);
+        front = my_codes[ahead];
       }
+      const uint32_t a6 = min(act, 6u);
+      const CodeAction r = act_on_code(a6, carry_code, front);
+      dir = (dir + (int)((7u >> (2u * a6)) & 3u)) & 3;   // left 3, right 1
+      {
+        const uint32_t step = a6 == kForward ? r.ok : 0u;
+        x += (int)(step & (uint32_t)dx);
+        y += (int)(step & (uint32_t)dy);
+        pos = step ? ahead : pos;
+      }
+      penalty |= r.lava;
+      uint32_t goal = r.goal, ended = goal | penalty;
+      if (any_missions && fam == kFamGoToDoor && live) {
+        // (see gotodoor_rules)
+        const bool done_at = act >= 6u && is_door_code(front) && ((front >> 4) & 7u) == (ob[0] & 0xFFu);
+        goal |= done_at ? 1u : 0u;
+        ended |= (done_at || act == kToggle) ? 1u : 0u;
+        edge_view = a6 > kForward && r.ok != 0u;   // a door toggled, possibly on the outer ring
+      }
+      if (a6 > kForward && r.ok) {
+        my_codes[ahead] = (uint8_t)r.new_front;
+        cell_changed[lane] = 1;
+        const bool held = a6 != kToggle;
+        carry_code = held ? (a6 == kPickup ? front : kCodeEmpty) : carry_code;
+        carry_changed = carry_changed || held;
+      }
+      t += live ? 1 : 0;
+      const uint32_t trunc = (live && t >= T) ? 1u : 0u;
+      if (__ballot((goal | penalty) != 0u))
+        reward = penalty ? -1.0f : (goal ? goal_reward(t, T, a.env.reward_mode) : 0.0f);
+      const uint32_t flags = do_reset ? kFlagFirst : ended * kFlagTerminated | trunc * kFlagTruncated;
+      const uint32_t act_rec = live ? act : kActionNone;
+      done_prev = (ended | trunc) != 0u;
 
-      const size_t row = kServe ? (size_t)(step0 + s) : (size_t)((a.row0 + s) % a.out.rows);
+      const size_t row = kServe ? (size_t)(step0 + s) : (size_t)ring_row;
+      if (!kServe) ring_row = ring_row + 1 == a.out.rows ? 0 : ring_row + 1;
       const size_t rec = row * rec_stride;   // index of lane 0's record
       if (kObs == 2 && o_obs && !kServe) {
         // whole-grid records, packed like the tile's grids (from g0): the
         // agents are drawn into the codes for the copy and then removed
-        uint8_t* at = my_codes + y * S + x;
+        uint8_t* at = my_codes + pos;
         uint8_t under = 0;
         if (active) {
           under = *at;
-          *at = (uint8_t)(4u * (kAgentKind + (uint32_t)dir));
+          *at = (uint8_t)(kAgent | ((uint32_t)dir << 4));
         }
         wave_sync();   // every lane's grid writes of this step, and the agents
         uint8_t* dst = a.out.obs + row * a.out.obs_row;
-        if (a.env.obs_mode == 3) emit_tile_grids<true>(dst + g0 / 3, tile_cells, table, codes, lane);
-        else emit_tile_grids<false>(dst + g0, tile_cells, table, codes, lane);
+        if (a.env.obs_mode == 3) emit_types(dst + g0 / 3, codes, tile_cells, lane);
+        else emit_triples<true>(dst + g0, codes, tile_cells, lane);
         wave_sync();
         if (active) *at = under;
-      } else if (kObs == 1 && o_obs && !kServe) {
-        // categorical records (49 bytes): the stage holds all 64 at once
-        uint32_t u[kObsWords + 1];
-        observe_words<true>(lds_rows(table, my_codes, S, x, y, dir), carry, active, lane, u);
-        if (__ballot(edge_view))
-          observe_words<true>(LdsCheckedRows{table, my_codes, S, x, y, dir}, carry, active, lane, u);
-        store_words<true>(stage, lane, u);
-        wave_sync();
-        copy_out<kWave, kCatBytes>(stage, o_obs + rec * kCatBytes, n_here, lane);
-        wave_sync();
-      } else if (kObs == 0 && o_obs) {
+      } else if (kObs != 2 && o_obs) {
         // inactive lanes (S = 0, pose (1, 1)) read inside the guard margin
-        uint32_t u[kObsWords + 1];
-        observe_words<false>(lds_rows(table, my_codes, S, x, y, dir), carry, active, lane & 31, u);
-        if (__ballot(edge_view))
-          observe_words<false>(LdsCheckedRows{table, my_codes, S, x, y, dir}, carry, active, lane & 31, u);
-        // the stage holds 32 records: lanes 0-31, then lanes 32-63 (each half
-        // starts and ends on a word boundary, so the halves are independent).
-        // HBM writes whole 64-byte units: a store that covers only part of
-        // one costs a read-modify-write, and so does a unit that two pieces
-        // of the block share, since they leave at different times.  So the
-        // first piece ends on a 64-byte boundary of the output and its last
-        // `keep` bytes (< 64) are moved to the front of the stage, with the
-        // second half staged right behind them.
-        uint8_t* dst = o_obs + rec * kObsBytes;
-        const int n_first = min(32, n_here);
-        const int bytes0 = n_first * kObsBytes;
-        const uintptr_t d = reinterpret_cast<uintptr_t>(dst);
-        const int keep = (n_here > 32 && (d & 15) == 0) ? (int)((d + (uintptr_t)bytes0) & 63) : 0;
-        if (lane < 32) store_words<false>(stage, lane, u);
+        uint32_t f[13];
+        view_codes(grids, kMargin + my_off + pos, S, x, y, dir, carry_code, masks,
+                   __ballot(edge_view) != 0, edge_view, f);
+        __builtin_amdgcn_sched_barrier(0);   // no step of the view is put off into the stores
+        store_view(stage, f, lane, n_here);
         wave_sync();
-        copy_piece<kHalfStageBytes>(stage, dst, bytes0 - keep, lane);
-        if (n_here > 32) {
-          // source [bytes0 - keep, bytes0) and destination [0, keep) are disjoint
-          if (lane < (keep >> 4)) {
-            const u32x4 v = *reinterpret_cast<const u32x4*>(stage + bytes0 - keep + 16 * lane);
-            *reinterpret_cast<u32x4*>(stage + 16 * lane) = v;
-          }
-          wave_sync();
-          if (lane >= 32) store_words<false>(stage + keep, lane & 31, u);
-          wave_sync();
-          copy_piece<kRecStageBytes>(stage, dst + bytes0 - keep, keep + (n_here - 32) * kObsBytes, lane);
-        }
-        wave_sync();
+        const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
+        if (kObs == 1) emit_types(o_obs + rec * kCatBytes, cells, n_here * kCatBytes, lane);
+        else emit_triples<false>(o_obs + rec * kObsBytes, cells, n_here * kCatBytes, lane);
       }
       if (active) {
         o_reward[rec + lane] = reward;
@@ -2203,18 +2401,13 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     // holding balls, which move every step)
     const bool dirty = active && (fresh || fam == kFamDynObs || cell_changed[lane] != 0 ||
                                   episode != a.st.episode[e]);
-    // the record stage is idle after the last step: it holds the line bitmap
-    // (a tile of 64 grids of side 32 spans at most 3074 lines)
-    static_assert(((3 * kWave * 32 * 32 + 63 + 15) / 16 / 4 + 1 + 31) / 32 * 4 <= kRecStageBytes,
-                  "the line bitmap fits the record stage");
-    emit_dirty_grids(a.st.grid + g0, tile_cells, dirty, my_off, S * S, table, codes,
-                     reinterpret_cast<uint32_t*>(stage), lane);
+    emit_dirty_grids(a.st.grid + g0, tile_cells, dirty, my_off, S * S, codes, stage_words, lane);
     if (active) {
       a.st.x[e] = x;
       a.st.y[e] = y;
       a.st.dir[e] = dir;
       a.st.t[e] = t;
-      a.st.carry[e] = (int32_t)carry;
+      if (carry_changed) a.st.carry[e] = (int32_t)carry_triple(carry_code);
       a.st.episode[e] = episode;
       a.st.done_prev[e] = done_prev ? 1 : 0;
       a.st.calls[e] = calls + (uint32_t)steps;
@@ -2230,7 +2423,7 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
 size_t fused_dynamic_lds_bytes(int32_t max_tile_cells) { return tile_lds_bytes(max_tile_cells); }
 
 size_t fused_lds_bytes(int32_t max_tile_cells) {
-  return kKinds * kView * 4 + kRecStageBytes + kWave + fused_dynamic_lds_bytes(max_tile_cells);
+  return kMaskEntries * sizeof(uint2) + kViewStageBytes + kWave + fused_dynamic_lds_bytes(max_tile_cells);
 }
 
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
