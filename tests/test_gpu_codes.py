@@ -35,3 +35,38 @@ def test_records_at_any_alignment(n, offset, obs_mode):
     P.assert_state_equal(env, s, f"{n} envs at byte {offset}, mode {obs_mode}")
     assert bool((raw[:at] == 0xA5).all()) and bool((raw[at + whole.numel():] == 0xA5).all())
     env.close()
+
+
+# families at their smallest, odd, even and largest sides, with every parameter
+RESET_CASES = ([(wl.FAMILY_EMPTY, s, 0) for s in (4, 5, 32)] + [(wl.FAMILY_TWOROOM, s, 0) for s in (5, 8, 32)] +
+               [(wl.FAMILY_FOURROOMS, s, 0) for s in (7, 9, 31)] + [(wl.FAMILY_LAVAGAP, s, 0) for s in (5, 6, 32)] +
+               [(wl.FAMILY_CROSSINGS, 5, 1), (wl.FAMILY_CROSSINGS, 9, 3), (wl.FAMILY_CROSSINGS, 31, 8)] +
+               [(wl.FAMILY_DISTSHIFT, 6, 1), (wl.FAMILY_DISTSHIFT, 9, 2), (wl.FAMILY_DISTSHIFT, 32, 1)] +
+               [(wl.FAMILY_DYNOBS, 5, 1), (wl.FAMILY_DYNOBS, 5, 7), (wl.FAMILY_DYNOBS, 32, 8)] +
+               [(wl.FAMILY_GOTODOOR, s, 0) for s in (5, 11, 32)] +
+               [(wl.FAMILY_KEYCORRIDOR, 7, 1), (wl.FAMILY_KEYCORRIDOR, 10, 2), (wl.FAMILY_KEYCORRIDOR, 31, 3)])
+
+
+@pytest.mark.parametrize("case", [[c] for c in RESET_CASES] + [RESET_CASES],
+                         ids=[f"{wl.FAMILY_NAMES[f]}-{s}-{p}" for f, s, p in RESET_CASES] + ["all"])
+def test_resets_all_the_time(case):
+    """Step limits of 1 to 3, so that layouts are drawn and filled on most
+    steps, some lanes of a tile resetting while others do not."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    n, steps = 330, 24
+    rng = np.random.default_rng(len(case))
+    pick = np.array(case)[rng.integers(0, len(case), n)]
+    table = wl.EnvTable(pick[:, 0].astype(np.uint8), pick[:, 1].astype(np.uint8),
+                        rng.integers(1, 4, n).astype(np.int32), np.full(n, 99, np.uint64),
+                        np.arange(n, dtype=np.uint32), "resets", pick[:, 2].astype(np.uint8))
+    b, s, _ = P.oracle_reset(table, 0, 2)
+    ref = ox.rollout(b, s, steps, None, nthreads=8)
+    env = ge.GridEnv(table, obs_mode=2)
+    env.reset()
+    traj = env.traj(steps)
+    env.rollout(steps, traj, K=11)
+    torch.cuda.synchronize()
+    P.assert_rows_equal(traj, ref, what="resets")
+    P.assert_state_equal(env, s, "resets")
+    env.close()
