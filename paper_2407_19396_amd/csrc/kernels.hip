@@ -160,19 +160,41 @@ __device__ __forceinline__ bool is_ball(const Layout& L, int x, int y) {
   return hit;
 }
 
-// Layout-stream draws taken in order, one Philox block per 4 words.  kCalls:
-// drawn inside a call (see make_layout), whose registers are its own.
-template <bool kCalls>
-struct DrawStream {
+// The layout stream for the two generators whose number of draws varies: a
+// window of kDrawWords words per lane in LDS (word i of lane l at [64 i + l]).
+// Drawn word by word from registers, some lane would need a new Philox block
+// at nearly every draw, and the whole wave would compute it.  Twelve words
+// fit the fused kernel's stage; a larger window would cost it a workgroup per
+// compute unit on the mixed batch (20 steps 184 -> 211 us at 24 words).
+constexpr int kDrawBlocks = 3;
+constexpr int kDrawWords = 4 * kDrawBlocks;
+constexpr int kDrawBytes = kDrawWords * kWave * 4;
+
+struct DrawWindow {
+  uint32_t* words;    // the lane's column
   uint2 seed;
-  uint32_t id, episode, w;
-  uint4 block;
-  __device__ __forceinline__ uint32_t next(uint32_t n) {
-    if ((w & 3u) == 0) block = philox10(make_uint4(id, episode, w >> 2, 0u), kCalls ? seed : opaque(seed));
-    const uint32_t r = bounded(pick4(block, w & 3u), n);
-    ++w;
-    return r;
+  uint32_t id, episode;
+  uint32_t block, w;  // the window's first block; the next word, from there
+
+  __device__ __forceinline__ void fill() {
+    block += w >> 2;
+    w &= 3u;
+    const uint2 key = opaque(seed);
+#pragma unroll
+    for (int b = 0; b < kDrawBlocks; ++b) {
+      const uint4 v = philox10(make_uint4(id, episode, block + (uint32_t)b, 0u), key);
+      uint32_t* p = words + 4 * kWave * b;
+      p[0] = v.x;
+      p[kWave] = v.y;
+      p[2 * kWave] = v.z;
+      p[3 * kWave] = v.w;
+    }
   }
+  // refills every lane's window if some lane's holds fewer than n <= 9 words
+  __device__ __forceinline__ void need(uint32_t n) {
+    if (__ballot(w + n > kDrawWords)) fill();
+  }
+  __device__ __forceinline__ uint32_t next(uint32_t n) { return bounded(words[kWave * w++], n); }
 };
 
 // position of the k-th (0-based) set bit of m
@@ -194,17 +216,18 @@ struct Rivers {
   uint64_t vopen, hopen;
 };
 
-template <bool kCalls>
 __device__ __forceinline__ Rivers crossings_layout(int S, int N, uint2 seed, uint32_t rng_id,
-                                                uint32_t episode) {
-  DrawStream<kCalls> ds{seed, rng_id, episode, 0u, make_uint4(0, 0, 0, 0)};
+                                                   uint32_t episode, uint32_t* words) {
+  static_assert(kMaxRivers <= kDrawWords, "the rivers' draws fit the window");
+  DrawWindow d{words, seed, rng_id, episode, 0u, 0u};
+  d.fill();
   const int M = S - 3, h = M / 2;
   int mkey[kMaxRivers], mval[kMaxRivers];
   Rivers R{0u, 0u, 0ull, 0ull};
 #pragma unroll
   for (int k = 0; k < kMaxRivers; ++k) {
     if (k < N) {
-      const int r = k + (int)ds.next((uint32_t)(M - k));
+      const int r = k + (int)d.next((uint32_t)(M - k));
       int vk = k, vr = r;
 #pragma unroll
       for (int j = 0; j < k; ++j) {
@@ -220,17 +243,18 @@ __device__ __forceinline__ Rivers crossings_layout(int S, int N, uint2 seed, uin
   const int nv = __builtin_popcount(R.vmask), nh = __builtin_popcount(R.hmask);
   int ci = 0, rj = 0;
   for (int q = 0; q < N; ++q) {
+    d.need(2u);
     const int rv = nv - ci, rh = nh - rj;
-    if ((int)ds.next((uint32_t)(rv + rh)) < rv) {
+    if ((int)d.next((uint32_t)(rv + rh)) < rv) {
       const int lo = rj == 0 ? 0 : kth_bit(R.hmask, rj - 1);
       const int hi = rj == nh ? S - 1 : kth_bit(R.hmask, rj);
-      const uint64_t y = (uint64_t)(lo + 1 + (int)ds.next((uint32_t)(hi - lo - 1)));
+      const uint64_t y = (uint64_t)(lo + 1 + (int)d.next((uint32_t)(hi - lo - 1)));
       R.vopen |= y << (5 * ci);
       ++ci;
     } else {
       const int lo = ci == 0 ? 0 : kth_bit(R.vmask, ci - 1);
       const int hi = ci == nv ? S - 1 : kth_bit(R.vmask, ci);
-      const uint64_t x = (uint64_t)(lo + 1 + (int)ds.next((uint32_t)(hi - lo - 1)));
+      const uint64_t x = (uint64_t)(lo + 1 + (int)d.next((uint32_t)(hi - lo - 1)));
       R.hopen |= x << (5 * rj);
       ++rj;
     }
@@ -275,81 +299,88 @@ __device__ __forceinline__ uint32_t kc_byte(const uint32_t (&kd)[3], int e) {
   return e < 8 ? (uint32_t)(lo >> (8 * e)) & 0xFFu : (kd[2] >> (8 * (e - 8))) & 0xFFu;
 }
 
-// rooms reachable from room `from` (bit j * 3 + i) through the open walls:
-// right[r] / down[r] bits say room r connects to r + 1 / r + 3
-__device__ __forceinline__ uint32_t kc_reach(uint32_t from, uint32_t right, uint32_t down) {
-  uint32_t r = from;
-#pragma unroll
-  for (int it = 0; it < 8; ++it)
-    r |= ((r & right) << 1) | ((r >> 1) & right) | ((r & down) << 3) | ((r >> 3) & down);
-  return r;
-}
-
 struct KcLayout {
   int rl, colour, gx, gy, kx, ky, ax, ay, dir;
   uint32_t kd[3];
 };
 
-template <bool kCalls>
 __device__ __forceinline__ KcLayout keycorridor_layout(int S, int R, uint2 seed, uint32_t rng_id,
-                                                    uint32_t episode) {
-  DrawStream<kCalls> ds{seed, rng_id, episode, 0u, make_uint4(0, 0, 0, 0)};
+                                                       uint32_t episode, uint32_t* words) {
+  DrawWindow d{words, seed, rng_id, episode, 0u, 0u};
+  d.fill();   // the walls take at most 12 draws
   const int st = (S - 1) / 3, inner = st - 1;
   // door positions of walls e = 0..9 (the table's numbering), 4 bits each
   uint64_t pos = 0;
   for (int j = 0; j < R; ++j)
     for (int i = 0; i < 3; ++i) {
-      if (i < 2) pos |= (uint64_t)ds.next((uint32_t)inner) << (4 * (2 * j + i));
+      if (i < 2) pos |= (uint64_t)d.next((uint32_t)inner) << (4 * (2 * j + i));
       if (j < R - 1) {
-        const uint64_t p = ds.next((uint32_t)inner);   // the hallway's wall draws one too
+        const uint64_t p = d.next((uint32_t)inner);   // the hallway's wall draws one too
         if (i != 1) pos |= p << (4 * (6 + 2 * j + (i >> 1)));
       }
     }
   KcLayout K;
-  K.rl = (int)ds.next((uint32_t)R);
-  K.colour = (int)ds.next(6u);
-  // the door table: bytes 0-7 in lo, 8-9 in hi
-  uint64_t lo = 0;
-  uint32_t hi = 0;
+  d.need(7u);
+  K.rl = (int)d.next((uint32_t)R);
+  K.colour = (int)d.next(6u);
   const int el = 2 * K.rl + 1;   // < 8
-  lo |= (uint64_t)(0x80u | ((uint32_t)K.colour << 4) | (uint32_t)((pos >> (4 * el)) & 15u)) << (8 * el);
+  const uint32_t locked_door = 0x80u | ((uint32_t)K.colour << 4) | (uint32_t)((pos >> (4 * el)) & 15u);
+  K.kd[0] = el < 4 ? locked_door << (8 * el) : 0u;
+  K.kd[1] = el < 4 ? 0u : locked_door << (8 * (el - 4));
+  K.kd[2] = 0u;
   uint32_t q, r;
-  small_divmod(ds.next((uint32_t)(inner * inner)), (uint32_t)inner, q, r);
+  small_divmod(d.next((uint32_t)(inner * inner)), (uint32_t)inner, q, r);
   K.gx = 2 * st + 1 + (int)r;
   K.gy = K.rl * st + 1 + (int)q;
-  const int rk = (int)ds.next((uint32_t)R);
-  small_divmod(ds.next((uint32_t)(inner * inner)), (uint32_t)inner, q, r);
+  const int rk = (int)d.next((uint32_t)R);
+  small_divmod(d.next((uint32_t)(inner * inner)), (uint32_t)inner, q, r);
   K.kx = 1 + (int)r;
   K.ky = rk * st + 1 + (int)q;
   const int ra = R / 2;
-  small_divmod(ds.next((uint32_t)(inner * inner)), (uint32_t)inner, q, r);
+  small_divmod(d.next((uint32_t)(inner * inner)), (uint32_t)inner, q, r);
   K.ax = st + 1 + (int)r;
   K.ay = ra * st + 1 + (int)q;
-  K.dir = (int)ds.next(4u);
+  K.dir = (int)d.next(4u);
   // connect every room (MiniGrid's connect_all), the locked room excepted
   const uint32_t all = (1u << (3 * R)) - 1u;
   uint32_t right = 1u << (3 * K.rl + 1), down = 0u;   // the locked door
   for (int j = 0; j + 1 < R; ++j) down |= 1u << (3 * j + 1);   // the hallway
+  // An attempt picks a room and a wall of it, three words, and takes a fourth
+  // for the colour if it adds a door.  The wave runs attempts until its last
+  // lane is connected (some 55 of them for 64 layouts of nine rooms), so an
+  // attempt is selects without branches.
+  const uint32_t hallway = 0x92u & all;
   for (int it = 0; it < 1024; ++it) {
-    if (kc_reach(1u << (3 * ra + 1), right, down) == all) break;
-    const int i = (int)ds.next(3u), j = (int)ds.next((uint32_t)R), k = (int)ds.next(4u);
-    const int i2 = i + (k == 0) - (k == 2), j2 = j + (k == 1) - (k == 3);
-    if (i2 < 0 || i2 > 2 || j2 < 0 || j2 >= R) continue;
-    const bool horiz = j2 == j;
-    const int room = horiz ? 3 * j + min(i, i2) : 3 * min(j, j2) + i;
-    if (((horiz ? right : down) >> room) & 1u) continue;
-    if ((i == 2 && j == K.rl) || (i2 == 2 && j2 == K.rl)) continue;
-    const uint32_t c = ds.next(6u);
-    const int e = horiz ? 2 * j + min(i, i2) : 6 + 2 * min(j, j2) + (i >> 1);
-    if (horiz) right |= 1u << room;
-    else down |= 1u << room;
-    const uint32_t v = 0x80u | (c << 4) | (uint32_t)((pos >> (4 * e)) & 15u);
-    if (e < 8) lo |= (uint64_t)v << (8 * e);
-    else hi |= v << (8 * (e - 8));
+    // from the hallway any room is at most one wall across and two along
+    uint32_t reached = hallway;
+#pragma unroll
+    for (int hop = 0; hop < 3; ++hop)
+      reached |= ((reached & right) << 1) | ((reached >> 1) & right) | ((reached & down) << 3) | ((reached >> 3) & down);
+    const bool todo = reached != all;
+    if (!__ballot(todo)) break;
+    d.need(4u);
+    const uint32_t* at = d.words + kWave * d.w;
+    const int i = (int)bounded(at[0], 3u), j = (int)bounded(at[kWave], (uint32_t)R);
+    const uint32_t k = bounded(at[2 * kWave], 4u), c = bounded(at[3 * kWave], 6u);
+    // k: east, south, west, north
+    const int i2 = i + (k == 0u ? 1 : 0) - (k == 2u ? 1 : 0), j2 = j + (k == 1u ? 1 : 0) - (k == 3u ? 1 : 0);
+    const bool horiz = (k & 1u) == 0u;
+    const int il = min(i, i2), jl = min(j, j2);
+    const uint32_t room = (uint32_t)(3 * jl + il) & 31u;
+    const uint32_t known = ((horiz ? right : down) >> room) & 1u;
+    const uint32_t inside = ((unsigned)i2 < 3u ? 1u : 0u) & ((unsigned)j2 < (unsigned)R ? 1u : 0u);
+    // a cell (room) number 3 j + i tells the locked room apart
+    const uint32_t locked = (3 * j + i == 3 * K.rl + 2 ? 1u : 0u) | (3 * j2 + i2 == 3 * K.rl + 2 ? 1u : 0u);
+    const uint32_t add = (todo ? inside : 0u) & ~(known | locked);
+    d.w += todo ? 3u + add : 0u;
+    right |= horiz ? add << room : 0u;
+    down |= horiz ? 0u : add << room;
+    const uint32_t e = (uint32_t)(horiz ? 2 * jl + il : 6 + 2 * jl + (i >> 1)) & 15u;
+    const uint32_t v = add ? (0x80u | (c << 4) | (uint32_t)((pos >> (4u * e)) & 15u)) << (8u * (e & 3u)) : 0u;
+    K.kd[0] |= e < 4u ? v : 0u;
+    K.kd[1] |= (e >> 2) == 1u ? v : 0u;
+    K.kd[2] |= (e >> 2) == 2u ? v : 0u;
   }
-  K.kd[0] = (uint32_t)lo;
-  K.kd[1] = (uint32_t)(lo >> 32);
-  K.kd[2] = hi;
   return K;
 }
 
@@ -383,20 +414,11 @@ __device__ __forceinline__ void fourrooms_cell(int S, int m, int g1, int g2, int
   x += x >= m ? 1 : 0;
 }
 
-__device__ __noinline__ Rivers crossings_call(int S, int N, uint2 seed, uint32_t rng_id, uint32_t episode) {
-  return crossings_layout<true>(S, N, seed, rng_id, episode);
-}
-__device__ __noinline__ KcLayout keycorridor_call(int S, int R, uint2 seed, uint32_t rng_id, uint32_t episode) {
-  return keycorridor_layout<true>(S, R, seed, rng_id, episode);
-}
-
-// kCalls: the two long generators as calls (k_plain, which draws once a launch:
-// 5 % faster over all families than inlined; the step loop the other way).
 // meta = family | side << 8 | parameter << 16 (Crossings: rivers; DistShift:
 // variant; Dynamic-Obstacles: balls; KeyCorridor: rows of rooms).  The lava
 // families and Dynamic-Obstacles start at (1, 1) facing east.
-template <bool kCalls>
-__device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32_t episode) {
+// words: the lane's column of the draw window.
+__device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32_t episode, uint32_t* words) {
   const uint32_t fam = meta & 0xFF;
   const int S = (int)((meta >> 8) & 0xFF), param = (int)((meta >> 16) & 0xFF);
   Layout L;
@@ -412,8 +434,7 @@ __device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32
   L.ob[0] = L.ob[1] = L.ob[2] = L.ob[3] = 0xFFFFFFFFu;
   L.kd[0] = L.kd[1] = L.kd[2] = 0u;
   if (fam == kFamKeyCorridor) {
-    const KcLayout K = kCalls ? keycorridor_call(S, param, seed, rng_id, episode)
-                              : keycorridor_layout<false>(S, param, seed, rng_id, episode);
+    const KcLayout K = keycorridor_layout(S, param, seed, rng_id, episode, words);
     L.a = K.rl;
     L.b = param;   // rows of rooms
     L.colour = K.colour;
@@ -506,8 +527,7 @@ __device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32
       L.a = 2 + (int)bounded(w0.x, (uint32_t)(S - 4));
       L.b = 1 + (int)bounded(w0.y, (uint32_t)(S - 2));
     } else if (fam == kFamCrossings) {
-      const Rivers R = kCalls ? crossings_call(S, param, seed, rng_id, episode)
-                              : crossings_layout<false>(S, param, seed, rng_id, episode);
+      const Rivers R = crossings_layout(S, param, seed, rng_id, episode, words);
       L.vmask = R.vmask;
       L.hmask = R.hmask;
       L.vopen = R.vopen;
@@ -634,6 +654,10 @@ __device__ __forceinline__ uint32_t layout_cell(const Layout& L, int x, int y) {
 }
 
 __device__ __forceinline__ int bcast(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
+
+__device__ __forceinline__ uint64_t bcast64(uint64_t v, int lane) {
+  return (uint64_t)(uint32_t)bcast((int)(uint32_t)v, lane) | ((uint64_t)(uint32_t)bcast((int)(v >> 32), lane) << 32);
+}
 
 __device__ __forceinline__ Layout bcast_layout(const Layout& L, int r) {
   Layout o;
@@ -1277,13 +1301,13 @@ struct PlainArgs {
   EnvTables env;
   StateBufs st;
   const uint8_t* actions;
-  int32_t reset_all;
   TrajBufs out;
   int32_t row;
 };
 
 __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
-  __shared__ __align__(16) uint8_t stage[kStageBytes];
+  __shared__ __align__(16) uint8_t stage[kStageBytes];   // and the draw window, before
+  static_assert(kDrawBytes <= kStageBytes, "the draw window fits the stage");
   const int lane = threadIdx.x;
   const int e0 = blockIdx.x * kWave;
   const int e = e0 + lane;
@@ -1308,26 +1332,24 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
     rid = a.env.rng_id[e];
     goff = a.env.grid_off[e];
     g = a.st.grid + goff;
-    if (!a.reset_all) {
-      x = a.st.x[e];
-      y = a.st.y[e];
-      dir = a.st.dir[e];
-      t = a.st.t[e];
-      carry = (uint32_t)a.st.carry[e];
-      episode = a.st.episode[e];
-      done_prev = a.st.done_prev[e] != 0;
-      calls = a.st.calls[e];
-      if (fam == kFamDynObs || fam == kFamGoToDoor) {   // the balls, or the mission
-        const uint4 o4 = *reinterpret_cast<const uint4*>(a.st.obst + 16 * (size_t)e);
-        ob[0] = o4.x; ob[1] = o4.y; ob[2] = o4.z; ob[3] = o4.w;
-      }
+    x = a.st.x[e];
+    y = a.st.y[e];
+    dir = a.st.dir[e];
+    t = a.st.t[e];
+    carry = (uint32_t)a.st.carry[e];
+    episode = a.st.episode[e];
+    done_prev = a.st.done_prev[e] != 0;
+    calls = a.st.calls[e];
+    if (fam == kFamDynObs || fam == kFamGoToDoor) {   // the balls, or the mission
+      const uint4 o4 = *reinterpret_cast<const uint4*>(a.st.obst + 16 * (size_t)e);
+      ob[0] = o4.x; ob[1] = o4.y; ob[2] = o4.z; ob[3] = o4.w;
     }
   }
-  const bool do_reset = active && (a.reset_all || done_prev);
+  const bool do_reset = active && done_prev;
   Layout L{};
   if (do_reset) {
-    episode = a.reset_all ? 0u : episode + 1u;
-    L = make_layout<true>(meta, seed, rid, episode);
+    episode += 1u;
+    L = make_layout(meta, seed, rid, episode, reinterpret_cast<uint32_t*>(stage) + lane);
     x = L.ax;
     y = L.ay;
     dir = L.dir;
@@ -1451,7 +1473,7 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
       copy_out<kWave, kObsBytes>(stage, a.out.obs + (rowN + (size_t)e0) * kObsBytes, n_here, lane);
     }
   }
-  if (active && a.out.reward) {
+  if (active) {
     a.out.reward[rowN + e] = reward;
     a.out.flags[rowN + e] = (uint8_t)flags;
     a.out.action[rowN + e] = (uint8_t)act_rec;
@@ -1465,7 +1487,7 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
     a.st.carry[e] = (int32_t)carry;
     a.st.episode[e] = episode;
     a.st.done_prev[e] = done_prev ? 1 : 0;
-    a.st.calls[e] = a.reset_all ? 0u : calls + 1u;
+    a.st.calls[e] = calls + 1u;
     if (fam == kFamDynObs || do_reset)
       *reinterpret_cast<uint4*>(a.st.obst + 16 * (size_t)e) = make_uint4(ob[0], ob[1], ob[2], ob[3]);
   }
@@ -2185,36 +2207,37 @@ __device__ __forceinline__ Next pack_layout(const Layout& L) {
 // The layout of (seed, id, episode) of every active lane of family f, which
 // is uniform across the wave.
 template <uint32_t F>
-__device__ __forceinline__ Next draw_family(uint32_t meta, uint2 seed, uint32_t rng_id, uint32_t episode) {
-  return pack_layout(make_layout<false>((meta & ~255u) | F, seed, rng_id, episode));
+__device__ __forceinline__ Next draw_family(uint32_t meta, uint2 seed, uint32_t rng_id, uint32_t episode,
+                                            uint32_t* words) {
+  return pack_layout(make_layout((meta & ~255u) | F, seed, rng_id, episode, words));
 }
 
 __device__ __forceinline__ Next draw_layout(uint32_t f, uint32_t meta, uint2 seed, uint32_t rng_id,
-                                            uint32_t episode) {
+                                            uint32_t episode, uint32_t* words) {
   switch (f) {
-    case kFamEmpty: return draw_family<kFamEmpty>(meta, seed, rng_id, episode);
-    case kFamTwoRoom: return draw_family<kFamTwoRoom>(meta, seed, rng_id, episode);
-    case kFamFourRooms: return draw_family<kFamFourRooms>(meta, seed, rng_id, episode);
-    case kFamLavaGap: return draw_family<kFamLavaGap>(meta, seed, rng_id, episode);
-    case kFamCrossings: return draw_family<kFamCrossings>(meta, seed, rng_id, episode);
-    case kFamDistShift: return draw_family<kFamDistShift>(meta, seed, rng_id, episode);
-    case kFamDynObs: return draw_family<kFamDynObs>(meta, seed, rng_id, episode);
-    case kFamGoToDoor: return draw_family<kFamGoToDoor>(meta, seed, rng_id, episode);
-    default: return draw_family<kFamKeyCorridor>(meta, seed, rng_id, episode);
+    case kFamEmpty: return draw_family<kFamEmpty>(meta, seed, rng_id, episode, words);
+    case kFamTwoRoom: return draw_family<kFamTwoRoom>(meta, seed, rng_id, episode, words);
+    case kFamFourRooms: return draw_family<kFamFourRooms>(meta, seed, rng_id, episode, words);
+    case kFamLavaGap: return draw_family<kFamLavaGap>(meta, seed, rng_id, episode, words);
+    case kFamCrossings: return draw_family<kFamCrossings>(meta, seed, rng_id, episode, words);
+    case kFamDistShift: return draw_family<kFamDistShift>(meta, seed, rng_id, episode, words);
+    case kFamDynObs: return draw_family<kFamDynObs>(meta, seed, rng_id, episode, words);
+    case kFamGoToDoor: return draw_family<kFamGoToDoor>(meta, seed, rng_id, episode, words);
+    default: return draw_family<kFamKeyCorridor>(meta, seed, rng_id, episode, words);
   }
 }
 
 // Gives every lane with `need` set a Next for `episode`, drawing with it
 // those of the lanes of its family that have none (have == false).
 __device__ __forceinline__ void draw_missing(Next& n, bool& have, bool need, bool active, uint32_t meta, uint2 seed,
-                                             uint32_t rng_id, uint32_t episode) {
+                                             uint32_t rng_id, uint32_t episode, uint32_t* words) {
   while (true) {
     const uint64_t missing = __ballot(need && !have);
     if (!missing) return;
     const uint32_t f =
         (uint32_t)bcast((int)meta, __ffsll((unsigned long long)missing) - 1) & 255u;
     if (active && !have && (meta & 255u) == f) {
-      n = draw_layout(f, opaque(meta), opaque(seed), opaque(rng_id), episode);
+      n = draw_layout(f, opaque(meta), opaque(seed), opaque(rng_id), episode, words);
       have = true;
     }
   }
@@ -2352,6 +2375,7 @@ constexpr int kViewStageBytes = kStageMargin + kWave * kCatBytes + 32;
 // words of emit_dirty_grids's bitmap: one bit per 64 cells of at most 64
 // grids of side 32, starting up to 63 cells before the first
 constexpr int kMarkWords = ((kWave * 32 * 32 + 63 + 63) / 64 + 31) / 32;
+static_assert(kDrawBytes <= kViewStageBytes && kMarkWords * 4 <= kViewStageBytes, "the stage holds each of its uses");
 
 struct FusedArgs {
   EnvTables env;
@@ -2373,7 +2397,7 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
     const int n = __shfl_up(incl, o, kWave);
     if (lane >= o) incl += n;
   }
-  total = __shfl(incl, kWave - 1, kWave);
+  total = bcast(incl, kWave - 1);
   return incl - v;
 }
 
@@ -2399,12 +2423,11 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
 // the policy variant has no loads in its step loop at all.
 template <bool kActions, bool kServe, int kObs>
 __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
-  // first-person variants: the byte masks of a row's visibility bits, and the
-  // stage of the wave's views; whole-grid records need only the bitmap of
-  // emit_dirty_grids, which takes the stage's place after the last step
+  // first-person variants: the byte masks of a row's visibility bits.  The
+  // stage holds, one after another, the words of layouts being drawn, the
+  // wave's views, and after the last step the bitmap of emit_dirty_grids.
   __shared__ __align__(16) uint2 masks[kObs == 2 ? 1 : kMaskEntries];
-  __shared__ __align__(16) uint32_t stage_words[kObs == 2 ? kMarkWords : kViewStageBytes / 4];
-  static_assert(kObs == 2 || kMarkWords * 4 <= kViewStageBytes, "the bitmap fits the view stage");
+  __shared__ __align__(16) uint32_t stage_words[kViewStageBytes / 4];
   __shared__ __align__(16) uint32_t kth_cell[kMaskPatterns];
   // per lane: whether a pickup, drop or toggle changed a cell of its grid
   __shared__ uint8_t cell_changed[kWave];
@@ -2515,9 +2538,9 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     uint8_t* my_codes = codes + my_off;
     // the tile's grids are contiguous in HBM: stage them as codes (a fresh
     // tile's are laid out here instead)
-    if (!kServe) g0 = (uint64_t)__shfl((long long)goff, 0, kWave);
+    if (!kServe) g0 = bcast64(goff, 0);
     if (fresh) {
-      draw_missing(next, have_next, active, active, meta, seed, rid, 0u);
+      draw_missing(next, have_next, active, active, meta, seed, rid, 0u, stage_words + lane);
       if (active) start_episode(next, fam, x, y, dir, ob);
       fill_grids(__ballot(active), false, next, meta, codes, my_off, lane);
       have_next = false;
@@ -2551,7 +2574,7 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       const bool do_reset = active && done_prev;
       const uint64_t pending = __ballot(do_reset);
       if (pending) {
-        draw_missing(next, have_next, do_reset, active, meta, seed, rid, episode + 1u);
+        draw_missing(next, have_next, do_reset, active, meta, seed, rid, episode + 1u, stage_words + lane);
         const bool kept = filled && keeps_base(fam);
         if (any_balls && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
           const uint32_t balls = (opaque(meta) >> 16) & 255u;
@@ -2689,6 +2712,91 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
   }
 }
 
+// Every env's episode 0 (env_reset), tile by tile as k_fused runs them: the
+// layouts are drawn a family at a time, the grids laid out in LDS and written
+// as one block, the first timestep's record taken from them.  Bound by the
+// fill, one env of the tile after another, and the draws; the plain kernel,
+// which did this before, wrote the grids cell by cell as three bytes each.
+template <int kObs>
+__global__ __launch_bounds__(kWave) void k_reset(FusedArgs a) {
+  __shared__ __align__(16) uint2 masks[kObs == 2 ? 1 : kMaskEntries];
+  __shared__ __align__(16) uint32_t stage_words[kViewStageBytes / 4];
+  extern __shared__ __align__(16) uint8_t grids[];
+  uint8_t* codes = grids + kMargin;
+  const int lane = threadIdx.x;
+  const int N = a.env.n;
+  const int e0 = (int)blockIdx.x * a.tiles.tile_envs, e = e0 + lane;
+  const int n_here = min(a.tiles.tile_envs, N - e0);
+  const bool active = lane < n_here;
+  if (kObs != 2) build_mask_table(masks, lane);
+
+  uint32_t meta = 0, rid = 0;
+  uint2 seed = make_uint2(0, 0);
+  uint64_t goff = 0;
+  if (active) {
+    meta = a.env.meta[e];
+    seed = a.env.seed[e];
+    rid = a.env.rng_id[e];
+    goff = a.env.grid_off[e];
+  }
+  const uint32_t fam = meta & 0xFF;
+  const int S = (int)((meta >> 8) & 0xFF);
+  int tile_cells;
+  const int my_off = wave_excl_scan(S * S, lane, tile_cells);
+  const uint64_t g0 = bcast64(goff, 0);
+  Next next{};
+  bool have = false;
+  draw_missing(next, have, active, active, meta, seed, rid, 0u, stage_words + lane);
+  int x = 1, y = 1, dir = 0;
+  uint32_t ob[4] = {~0u, ~0u, ~0u, ~0u};
+  if (active) start_episode(next, fam, x, y, dir, ob);
+  fill_grids(__ballot(active), false, next, meta, codes, my_off, lane);
+  wave_sync();
+
+  uint32_t* const stage = stage_words + kStageMargin / 4;
+  if (a.out.obs && kObs == 2) {
+    uint8_t* at = codes + my_off + y * S + x;
+    uint8_t under = 0;
+    if (active) {
+      under = *at;
+      *at = (uint8_t)(kAgent | ((uint32_t)dir << 4));
+    }
+    wave_sync();
+    if (a.env.obs_mode == 3) emit_types(a.out.obs + g0 / 3, codes, tile_cells, lane);
+    else emit_triples<true>(a.out.obs + g0, codes, tile_cells, lane);
+    wave_sync();
+    if (active) *at = under;
+    wave_sync();
+  } else if (a.out.obs && kObs != 2) {
+    uint32_t f[13];
+    view_codes(grids, kMargin + my_off + y * S + x, S, x, y, dir, kCodeEmpty, masks, false, false, f);
+    store_view(stage, f, lane, n_here);
+    wave_sync();
+    const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
+    if (kObs == 1) emit_types(a.out.obs + (size_t)e0 * kCatBytes, cells, n_here * kCatBytes, lane);
+    else emit_triples<false>(a.out.obs + (size_t)e0 * kObsBytes, cells, n_here * kCatBytes, lane);
+    wave_sync();
+  }
+  emit_dirty_grids(a.st.grid + g0, tile_cells, active, my_off, S * S, codes, stage_words, lane);
+  if (active) {
+    if (a.out.reward) {
+      a.out.reward[e] = 0.0f;
+      a.out.flags[e] = (uint8_t)kFlagFirst;
+      a.out.action[e] = (uint8_t)kActionNone;
+      if (a.out.mission) a.out.mission[e] = (uint8_t)mission_of(fam, ob[0]);
+    }
+    a.st.x[e] = x;
+    a.st.y[e] = y;
+    a.st.dir[e] = dir;
+    a.st.t[e] = 0;
+    a.st.carry[e] = (int32_t)kCellEmpty;
+    a.st.episode[e] = 0u;
+    a.st.done_prev[e] = 0;
+    a.st.calls[e] = 0u;
+    *reinterpret_cast<uint4*>(a.st.obst + 16 * (size_t)e) = make_uint4(ob[0], ob[1], ob[2], ob[3]);
+  }
+}
+
 }  // namespace
 
 size_t fused_dynamic_lds_bytes(int32_t max_tile_cells) { return tile_lds_bytes(max_tile_cells); }
@@ -2698,34 +2806,49 @@ size_t fused_lds_bytes(int32_t max_tile_cells) {
 }
 
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
-                        int reset_all, const TrajBufs& out, int32_t row, hipStream_t stream) {
-  PlainArgs a{env, st, actions, reset_all, out, row};
+                        const TrajBufs& out, int32_t row, hipStream_t stream) {
+  PlainArgs a{env, st, actions, out, row};
   const int blocks = (env.n + kWave - 1) / kWave;
   hipLaunchKernelGGL(k_plain, dim3(blocks), dim3(kWave), 0, stream, a);
   return hipGetLastError();
 }
+
+namespace {
+
+using FusedKernel = void (*)(FusedArgs);
+
+hipError_t launch_tiles(FusedKernel fn, const FusedArgs& a, int32_t blocks, hipStream_t stream) {
+  const size_t lds = fused_dynamic_lds_bytes(a.tiles.max_tile_cells);
+  if (lds > 65536) {
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
+                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, stream, a);
+  return hipGetLastError();
+}
+
+}  // namespace
 
 hipError_t launch_fused(const EnvTables& env, const TileTables& tiles, const StateBufs& st,
                         const uint8_t* actions, int32_t k_steps,
                         const TrajBufs& out, int32_t row0, int32_t grid_blocks,
                         hipStream_t stream, ServeTile* serve, const ServeTile* host_tiles,
                         const SlotConfig* host_slots) {
-  FusedArgs a{env, tiles, st, actions, k_steps, out, row0, serve, host_tiles, host_slots};
-  const size_t lds = fused_dynamic_lds_bytes(tiles.max_tile_cells);
+  const FusedArgs a{env, tiles, st, actions, k_steps, out, row0, serve, host_tiles, host_slots};
   // serving requests record symbolic first-person observations
   const int obs = serve ? 0 : (env.obs_mode >= 2 ? 2 : env.obs_mode);
-  using Kernel = void (*)(FusedArgs);
-  static const Kernel kernels[2][3] = {
+  static const FusedKernel kernels[2][3] = {
       {&k_fused<false, false, 0>, &k_fused<false, false, 1>, &k_fused<false, false, 2>},
       {&k_fused<true, false, 0>, &k_fused<true, false, 1>, &k_fused<true, false, 2>}};
-  const Kernel fn = serve ? &k_fused<false, true, 0> : kernels[actions ? 1 : 0][obs];
-  if (lds > 65536) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(fn, dim3(grid_blocks), dim3(kWave), lds, stream, a);
-  return hipGetLastError();
+  return launch_tiles(serve ? &k_fused<false, true, 0> : kernels[actions ? 1 : 0][obs], a, grid_blocks, stream);
+}
+
+hipError_t launch_reset(const EnvTables& env, const TileTables& tiles, const StateBufs& st, const TrajBufs& out,
+                        hipStream_t stream) {
+  const FusedArgs a{env, tiles, st, nullptr, 0, out, 0, nullptr, nullptr, nullptr};
+  static const FusedKernel kernels[3] = {&k_reset<0>, &k_reset<1>, &k_reset<2>};
+  return launch_tiles(kernels[env.obs_mode >= 2 ? 2 : env.obs_mode], a, tiles.n_tiles, stream);
 }
 
 }  // namespace gx

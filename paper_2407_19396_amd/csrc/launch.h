@@ -101,10 +101,16 @@ inline bool family_ok(int family, int side, int param, int max_side) {
   }
 }
 
-// One launch of the plain kernel: one step of every env (or the reset of
-// every env when reset_all != 0).  Writes output row `row`.
+// One launch of the plain kernel: one step of every env.  Writes output row
+// `row`.
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
-                        int reset_all, const TrajBufs& out, int32_t row, hipStream_t stream);
+                        const TrajBufs& out, int32_t row, hipStream_t stream);
+
+// One launch of the reset kernel: the start of episode 0 of every env, its
+// first timestep in row 0 of `out` (obs may be nullptr; reward nullptr: no
+// outputs at all).
+hipError_t launch_reset(const EnvTables& env, const TileTables& tiles, const StateBufs& st, const TrajBufs& out,
+                        hipStream_t stream);
 
 // One launch of the fused kernel: k_steps steps of every env, state staged
 // in LDS for the whole chunk; step s (0-based within the chunk) writes row

@@ -339,7 +339,8 @@ int env_reset(gx_ctx* c, const gx_state* st, const gx_traj* first, void* stream)
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   gx::TrajBufs tb{nullptr, nullptr, nullptr, nullptr, 1};
   if (first) tb = staged(c, first) ? stage_traj(c) : traj_of(c, first);
-  if (gx::launch_plain(tables_of(c), state_of(st), nullptr, 1, tb, 0, s) != hipSuccess)
+  const gx::TileTables tiles{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs};
+  if (gx::launch_reset(tables_of(c), tiles, state_of(st), tb, s) != hipSuccess)
     return GX_EDEVICE;
   if (staged(c, first) && render_rows(c, 1, first, 0, s) != hipSuccess) return GX_EDEVICE;
   c->has_reset = true;
@@ -355,7 +356,7 @@ int env_step(gx_ctx* c, const gx_state* st, const uint8_t* actions, const gx_tra
   if ((rc = device_status()) != GX_OK) return rc;
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool stg = staged(c, out);
-  if (gx::launch_plain(tables_of(c), state_of(st), actions, 0, stg ? stage_traj(c) : traj_of(c, out), 0,
+  if (gx::launch_plain(tables_of(c), state_of(st), actions, stg ? stage_traj(c) : traj_of(c, out), 0,
                        s) != hipSuccess)
     return GX_EDEVICE;
   if (stg && render_rows(c, 1, out, 0, s) != hipSuccess) return GX_EDEVICE;

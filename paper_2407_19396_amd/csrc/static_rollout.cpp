@@ -135,19 +135,19 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
                           cfg->obs_mode};
   const gx::StateBufs sb{st->grid, st->x,       st->y,         st->dir,   st->t,
                          st->carry, st->episode, st->done_prev, st->calls, st->obst};
+  const int32_t n_tiles = (n + kTileEnvs - 1) / kTileEnvs;
+  const gx::TileTables tiles{n_tiles, max_tile_cells, nullptr};
   if (reset) {
     gx::TrajBufs fb{nullptr, nullptr, nullptr, nullptr, 1};
     if (first) fb = gx::TrajBufs{first->obs, first->reward, first->flags, first->action, first->rows, obs_row,
                                  first->mission};
-    if (gx::launch_plain(env, sb, nullptr, 1, fb, 0, s) != hipSuccess) return GX_EDEVICE;
+    if (gx::launch_reset(env, tiles, sb, fb, s) != hipSuccess) return GX_EDEVICE;
   }
   if (n_steps == 0) return GX_OK;
 
   // the launch shape env_create picks: one single-wave workgroup per tile
-  const int32_t n_tiles = (n + kTileEnvs - 1) / kTileEnvs;
   const int32_t blocks = n_tiles;
   const int32_t k = K > 0 ? K : 64;
-  const gx::TileTables tiles{n_tiles, max_tile_cells, nullptr};
   const gx::TrajBufs tb{traj->obs, traj->reward, traj->flags, traj->action, traj->rows, obs_row, traj->mission};
   for (int32_t s0 = 0; s0 < n_steps; s0 += k) {
     const int32_t ks = std::min(k, n_steps - s0);
