@@ -207,7 +207,10 @@ typedef struct {
   uint8_t* mission;  /* may be NULL */
 } gx_traj;
 
-/* Launch and tiling facts of a context (for tools and benchmarks). */
+/* Launch and tiling facts of a context (for tools and benchmarks).  Until
+ * env_set_tiling or env_set_launch choose tiles or workgroups, they are
+ * those of the default tiling of 64; launches of at most 32768 envs then
+ * run in smaller tiles of the library's choice, one workgroup each. */
 typedef struct {
   int32_t n_envs;
   int32_t n_tiles;            /* workgroup tiles of tile_envs envs (fused rollout) */

@@ -2412,8 +2412,8 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
 //
 // kActions: actions come from a.actions; otherwise from the random policy.
 // kServe: tiles belong to requests described by a.serve (serving): each runs
-// min(K, steps it has left) steps from its own counter step0, writes to its
-// own output rows and advances step0.
+// min(K, steps it has left) steps from the count the host lists it with and
+// writes to its own output rows.
 // kObs: the observation records written, 0 symbolic first person, 1
 // categorical first person, 2 whole grid (a.env.obs_mode 2 or 3); each
 // variant carries only its own record code.
@@ -2448,13 +2448,15 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     // serving lists mark a newly admitted tile with the top bit: its
     // descriptor and slot configurations are still in host staging and its
     // envs are reset here (episode 0) before its first step
-    const uint32_t entry = a.tiles.list ? a.tiles.list[it] : (uint32_t)it;
-    const int tile = (int)(entry & 0x7FFFFFFFu);
-    const bool fresh = kServe && (entry >> 31) != 0;
+    const int part = kServe ? it & ((1 << a.tiles.parts_log2) - 1) : 0;
+    const uint2 entry = kServe ? a.tiles.list[it >> a.tiles.parts_log2] : make_uint2((uint32_t)it, 0u);
+    const int tile = (int)(entry.x & 0x7FFFFFFFu);
+    const bool fresh = kServe && (entry.x >> 31) != 0;
     // where this tile's envs live and where their records go: record of
     // step s, lane l is at index rec_base + s * rec_step (+ l) of the outputs
-    const int tile_envs = kServe ? kWave : a.tiles.tile_envs;
-    const int e0 = tile * tile_envs;
+    const int tile_envs = a.tiles.tile_envs;
+    const int first = part * tile_envs;   // of the listed tile's envs
+    const int e0 = kServe ? tile * kWave + first : tile * tile_envs;
     int n_here, steps;
     uint64_t g0 = 0;
     uint8_t *o_obs, *o_flags, *o_action, *o_mission = nullptr;
@@ -2463,21 +2465,21 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     size_t rec_stride;
     if (kServe) {
       const ServeTile d = fresh ? a.host_tiles[tile] : a.serve[tile];
-      if (fresh && lane == 0) a.serve[tile] = d;   // the device copy later launches read
-      if (!d.active || d.step0 >= d.n_steps) continue;
-      n_here = (int)d.n_envs;
-      steps = min(a.k_steps, (int)(d.n_steps - d.step0));
-      step0 = d.step0;
-      g0 = d.grid_base;
+      if (fresh && part == 0 && lane == 0) a.serve[tile] = d;   // the device copy later launches read
+      step0 = entry.y;
+      n_here = min(tile_envs, (int)d.n_envs - first);
+      if (!d.active || step0 >= d.n_steps || n_here <= 0) continue;
+      steps = min(a.k_steps, (int)(d.n_steps - step0));
       o_obs = d.obs;
       o_reward = d.reward;
       o_flags = d.flags;
       o_action = d.action;
       rec_stride = d.stride;
-      o_obs = o_obs ? o_obs + (size_t)d.local0 * kObsBytes : nullptr;
-      o_reward += d.local0;
-      o_flags += d.local0;
-      o_action += d.local0;
+      const size_t local = (size_t)d.local0 + (size_t)first;
+      o_obs = o_obs ? o_obs + local * kObsBytes : nullptr;
+      o_reward += local;
+      o_flags += local;
+      o_action += local;
     } else {
       n_here = min(tile_envs, N - e0);
       steps = a.k_steps;
@@ -2511,6 +2513,7 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       a.env.seed[e] = c.seed;
       a.env.rng_id[e] = c.rng_id;
       a.env.grid_off[e] = c.grid_off;
+      goff = c.grid_off;
       fam = meta & 0xFF;
       S = (int)((meta >> 8) & 0xFF);
     } else if (active) {
@@ -2520,7 +2523,7 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       T = a.env.max_steps[e];
       seed = a.env.seed[e];
       rid = a.env.rng_id[e];
-      if (!kServe) goff = a.env.grid_off[e];
+      goff = a.env.grid_off[e];
       x = a.st.x[e];
       y = a.st.y[e];
       dir = a.st.dir[e];
@@ -2538,7 +2541,7 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     uint8_t* my_codes = codes + my_off;
     // the tile's grids are contiguous in HBM: stage them as codes (a fresh
     // tile's are laid out here instead)
-    if (!kServe) g0 = bcast64(goff, 0);
+    g0 = bcast64(goff, 0);
     if (fresh) {
       draw_missing(next, have_next, active, active, meta, seed, rid, 0u, stage_words + lane);
       if (active) start_episode(next, fam, x, y, dir, ob);
@@ -2707,7 +2710,6 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       a.st.calls[e] = calls + (uint32_t)steps;
       *reinterpret_cast<uint4*>(a.st.obst + 16 * (size_t)e) = make_uint4(ob[0], ob[1], ob[2], ob[3]);
     }
-    if (kServe && lane == 0) a.serve[tile].step0 = step0 + (uint32_t)steps;
     wave_sync();
   }
 }

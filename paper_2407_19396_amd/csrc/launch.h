@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 namespace gx {
 
 // Per-env static tables in device memory (structure of arrays).
@@ -45,25 +47,41 @@ struct TrajBufs {
 struct TileTables {
   int32_t n_tiles;
   int32_t max_tile_cells;     // LDS bytes of the largest tile's code grids (sum of S^2)
-  const uint32_t* list;       // tile ids to run, n_tiles of them (serving), or nullptr: 0..n_tiles-1
+  const uint2* list;          // serving: the tiles to run, else nullptr (tiles 0..n_tiles-1).  x: tile
+                              // id, top bit set when admitted since the last launch; y: the steps its
+                              // request has run
   int32_t tile_envs = 64;     // E, 1..64
+  int32_t parts_log2 = 0;     // serving: a listed tile of 64 slots is run as 64 / E tiles; n_tiles counts
+                              // these
 };
+
+// Envs per tile of a launch whose caller has not chosen (env_set_tiling,
+// env_set_launch): the smallest of 4, 16, 32 that leaves at most one wave per
+// SIMD (1024 of them), else 64.  A wave's step costs the same for one env as
+// for 64 except for its records and its resets, so spare SIMDs are best given
+// fewer envs each; beyond one wave per SIMD the waves share the vector unit.
+// Empty 8x8, us a step: 4096 envs 1.59 / 1.81 / 2.16 / 2.43 in tiles of
+// 4 / 16 / 32 / 64, 16 384 envs 3.97 / 1.88 / 2.31 / 2.45, 30 011 envs
+// 8.3 / 2.70 / 2.51 / 2.89, 65 536 envs 14.8 / 4.65 / 2.91 / 2.65.
+inline int32_t launch_tile_envs(int64_t n_envs) {
+  for (const int32_t e : {4, 16, 32})
+    if ((n_envs + e - 1) / e <= 1024) return e;
+  return 64;
+}
 
 // A tile of 64 slots serving one request (device memory, 64 bytes).  The
 // tile's envs are slots [tile * 64, tile * 64 + n_envs); their grids are
-// contiguous from grid_base.  The record of the request's step r for its
+// contiguous from the first slot's on.  The record of the request's step r for its
 // env l goes to index r * stride + l of its output buffers.
 struct alignas(64) ServeTile {
   uint32_t active;     // 0: the tile is free
   uint32_t n_envs;     // 1..64
-  uint64_t grid_base;  // byte offset of the tile's grids in the grid pool
   uint8_t* obs;        // [n_steps][stride][147] or nullptr
   float* reward;       // [n_steps][stride]
   uint8_t* flags;
   uint8_t* action;
   uint32_t stride;     // envs per output row of the request (multiple of 16)
   uint32_t local0;     // request-local index of the tile's first env
-  uint32_t step0;      // steps the request has run; advanced by the kernel
   uint32_t n_steps;    // steps the request asked for
 };
 

@@ -33,6 +33,10 @@ struct gx_ctx {
   int32_t max_tile_cells = 0;
   int32_t blocks = 0;
   int32_t k_default = 64;
+  // while the caller has chosen neither tiling nor workgroups, launches run
+  // in tiles of their own choice (gx::launch_tile_envs)
+  bool shape_chosen = false;
+  int32_t auto_envs = 64, auto_tiles = 0, auto_cells = 0;
   std::vector<int32_t> cells;          // S^2 per env, for re-tiling
   // rgb modes: the sprite atlas, and the staging ring of symbolic records
   // (obs [stage_rows][sym_row], then reward, flags, action, mission
@@ -81,6 +85,17 @@ void free_tables(gx_ctx* c) {
   c->d_grid_off = nullptr;
 }
 
+// cells of the largest tile of E consecutive envs
+int32_t largest_tile(const gx_ctx* c, int32_t E) {
+  int32_t most = 0;
+  for (int32_t t0 = 0; t0 < c->n; t0 += E) {
+    int32_t cells = 0;
+    for (int32_t i = t0; i < std::min(c->n, t0 + E); ++i) cells += c->cells[i];
+    most = std::max(most, cells);
+  }
+  return most;
+}
+
 // Tiles of E consecutive envs, one single-wave workgroup per tile: the
 // hardware starts a tile's workgroup wherever an earlier one has finished,
 // which balances tiles of uneven work better than persistent workgroups
@@ -88,13 +103,18 @@ void free_tables(gx_ctx* c) {
 void set_tiling(gx_ctx* c, int32_t E) {
   c->tile_envs = E;
   c->n_tiles = (c->n + E - 1) / E;
-  c->max_tile_cells = 0;
-  for (int32_t t = 0; t < c->n_tiles; ++t) {
-    int32_t cells = 0;
-    for (int32_t i = t * E; i < std::min(c->n, (t + 1) * E); ++i) cells += c->cells[i];
-    c->max_tile_cells = std::max(c->max_tile_cells, cells);
-  }
+  c->max_tile_cells = largest_tile(c, E);
   c->blocks = c->n_tiles;
+}
+
+struct LaunchShape {
+  gx::TileTables tiles;
+  int32_t blocks;
+};
+
+LaunchShape launch_shape(const gx_ctx* c) {
+  if (c->shape_chosen) return {{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs}, c->blocks};
+  return {{c->auto_tiles, c->auto_cells, nullptr, c->auto_envs}, c->auto_tiles};
 }
 
 bool state_ok(const gx_state* st) {
@@ -305,6 +325,9 @@ int env_create(const gx_config* cfg, gx_ctx** out) {
     return rc;
   }
   set_tiling(c, kTileEnvs);
+  c->auto_envs = gx::launch_tile_envs(n);
+  c->auto_tiles = (n + c->auto_envs - 1) / c->auto_envs;
+  c->auto_cells = largest_tile(c, c->auto_envs);
   *out = c;
   return GX_OK;
 }
@@ -339,8 +362,7 @@ int env_reset(gx_ctx* c, const gx_state* st, const gx_traj* first, void* stream)
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   gx::TrajBufs tb{nullptr, nullptr, nullptr, nullptr, 1};
   if (first) tb = staged(c, first) ? stage_traj(c) : traj_of(c, first);
-  const gx::TileTables tiles{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs};
-  if (gx::launch_reset(tables_of(c), tiles, state_of(st), tb, s) != hipSuccess)
+  if (gx::launch_reset(tables_of(c), launch_shape(c).tiles, state_of(st), tb, s) != hipSuccess)
     return GX_EDEVICE;
   if (staged(c, first) && render_rows(c, 1, first, 0, s) != hipSuccess) return GX_EDEVICE;
   c->has_reset = true;
@@ -375,12 +397,12 @@ int env_rollout(gx_ctx* c, const gx_state* st, int32_t n_steps, const uint8_t* a
   // rgb: each fused launch fills the staging ring from row 0, then the
   // renderer draws those rows into the caller's ring
   const int32_t k = std::min(K > 0 ? K : c->k_default, stg ? c->stage_rows : INT32_MAX);
-  const gx::TileTables tiles{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs};   // every tile, in order
+  const LaunchShape shape = launch_shape(c);
   for (int32_t s0 = 0; s0 < n_steps; s0 += k) {
     const int32_t ks = std::min(k, n_steps - s0);
     const uint8_t* act = actions ? actions + (size_t)s0 * (size_t)c->n : nullptr;
-    if (gx::launch_fused(tables_of(c), tiles, state_of(st), act, ks, stg ? stage_traj(c) : traj_of(c, traj),
-                         stg ? 0 : s0 % traj->rows, c->blocks, s) != hipSuccess)
+    if (gx::launch_fused(tables_of(c), shape.tiles, state_of(st), act, ks, stg ? stage_traj(c) : traj_of(c, traj),
+                         stg ? 0 : s0 % traj->rows, shape.blocks, s) != hipSuccess)
       return GX_EDEVICE;
     if (stg && render_rows(c, ks, traj, s0 % traj->rows, s) != hipSuccess) return GX_EDEVICE;
   }
@@ -390,13 +412,17 @@ int env_rollout(gx_ctx* c, const gx_state* st, int32_t n_steps, const uint8_t* a
 int env_set_launch(gx_ctx* c, int32_t K, int32_t blocks) {
   if (!c || K < 1 || blocks < 0) return GX_EINVAL;
   c->k_default = K;
-  if (blocks > 0) c->blocks = blocks;
+  if (blocks > 0) {
+    c->blocks = blocks;
+    c->shape_chosen = true;
+  }
   return GX_OK;
 }
 
 int env_set_tiling(gx_ctx* c, int32_t tile_envs) {
   if (!c || tile_envs < 1 || tile_envs > kTileEnvs) return GX_EINVAL;
   set_tiling(c, tile_envs);
+  c->shape_chosen = true;
   return GX_OK;
 }
 

@@ -60,7 +60,7 @@ struct gx_server {
   gx::SlotConfig* h_slots = nullptr;
   // the tile lists of the last kLists launches (read by the fused kernel
   // from coherent pinned memory); a list is reused once its launch is done
-  uint32_t* h_lists = nullptr;
+  uint2* h_lists = nullptr;
   hipEvent_t list_done[kLists] = {};
   int64_t launches = 0;
   // bookkeeping, sized in env_server_create so that admitting, stepping and
@@ -146,7 +146,7 @@ int env_server_create(int32_t max_tiles, int32_t max_side, int32_t reward_mode, 
   ok = ok && hipHostMalloc(reinterpret_cast<void**>(&s->h_slots), sizeof(gx::SlotConfig) * slots,
                            hipHostMallocCoherent) == hipSuccess;
   ok = ok && hipHostMalloc(reinterpret_cast<void**>(&s->h_lists),
-                           sizeof(uint32_t) * (size_t)max_tiles * kLists, hipHostMallocCoherent) == hipSuccess;
+                           sizeof(uint2) * (size_t)max_tiles * kLists, hipHostMallocCoherent) == hipSuccess;
   for (hipEvent_t& e : s->list_done)
     ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
   // every descriptor starts inactive
@@ -233,14 +233,12 @@ int env_server_admit(gx_server* s, const gx_request* r, int32_t* handle) {
     gx::ServeTile& d = s->h_tiles[t];
     d.active = 1;
     d.n_envs = (uint32_t)n;
-    d.grid_base = base;
     d.obs = r->obs;
     d.reward = r->reward;
     d.flags = r->flags;
     d.action = r->action;
     d.stride = (uint32_t)r->stride;
     d.local0 = (uint32_t)l0;
-    d.step0 = 0;
     d.n_steps = (uint32_t)r->n_steps;
     s->tile_cells[t] = cells;
     s->fresh[t] = 1;
@@ -274,20 +272,24 @@ int env_server_step(gx_server* s, int32_t K, void* stream, int32_t* finished, in
     } else if (q != hipSuccess) {
       return GX_EDEVICE;
     }
-    uint32_t* list = s->h_lists + (size_t)slot * s->max_tiles;
+    uint2* list = s->h_lists + (size_t)slot * s->max_tiles;
     int32_t n = 0, max_cells = 0;
     // a tile admitted since the last launch carries the top bit: that launch
     // takes its descriptor and slots from host staging and resets its envs
     for (int32_t h : s->running)
       for (int32_t t = s->reqs[h].first_tile; t >= 0; t = s->tile_next[t]) {
-        list[n++] = (uint32_t)t | (s->fresh[t] ? 0x80000000u : 0u);
+        list[n++] = make_uint2((uint32_t)t | (s->fresh[t] ? 0x80000000u : 0u), (uint32_t)s->reqs[h].done);
         s->fresh[t] = 0;
         max_cells = std::max(max_cells, s->tile_cells[t]);
       }
-    // one workgroup per tile: a later tile starts on whichever workgroup
-    // slot frees first, so the list (longest first) is scheduled greedily
-    const int32_t blocks = n;
-    const gx::TileTables tiles{n, max_cells, list};
+    // one workgroup per tile, or per part of a tile while there are few: a
+    // later one starts on whichever workgroup slot frees first, so the list
+    // (longest first) is scheduled greedily
+    const int32_t tile_envs = gx::launch_tile_envs((int64_t)n * kTileEnvs);
+    int32_t parts_log2 = 0;
+    while (tile_envs << parts_log2 < kTileEnvs) ++parts_log2;
+    const int32_t blocks = n << parts_log2;
+    const gx::TileTables tiles{blocks, max_cells, list, tile_envs, parts_log2};
     const gx::TrajBufs none{nullptr, nullptr, nullptr, nullptr, 1};
     if (gx::launch_fused(tables_of(s), tiles, state_of(s), nullptr, K, none, 0, blocks, st,
                          s->d_tiles, s->h_tiles, s->h_slots) != hipSuccess)

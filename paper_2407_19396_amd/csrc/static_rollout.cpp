@@ -15,7 +15,6 @@
 namespace {
 
 constexpr int32_t kMaxEnvs = GX_STATIC_MAX_ENVS;
-constexpr int32_t kTileEnvs = 64;
 constexpr int kMaxDevices = 64;
 
 // Table sections of the scratch array, each kMaxEnvs entries (every
@@ -86,6 +85,7 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
   uint32_t* rng_id = reinterpret_cast<uint32_t*>(g_host_tables + kRngOff);
   uint64_t* grid_off = reinterpret_cast<uint64_t*>(g_host_tables + kOffOff);
   uint64_t off = 0;
+  const int32_t tile_envs = gx::launch_tile_envs(n);   // the tiles a context's launches run
   int32_t max_tile_cells = 0, tile_cells = 0;
   for (int32_t i = 0; i < n; ++i) {
     const int fam = cfg->family[i], S = cfg->side[i], P = cfg->param ? cfg->param[i] : 0;
@@ -98,7 +98,7 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
     grid_off[i] = off;
     off += 3ull * (uint64_t)S * (uint64_t)S;
     tile_cells += S * S;
-    if ((i + 1) % kTileEnvs == 0 || i + 1 == n) {
+    if ((i + 1) % tile_envs == 0 || i + 1 == n) {
       max_tile_cells = std::max(max_tile_cells, tile_cells);
       tile_cells = 0;
     }
@@ -135,8 +135,8 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
                           cfg->obs_mode};
   const gx::StateBufs sb{st->grid, st->x,       st->y,         st->dir,   st->t,
                          st->carry, st->episode, st->done_prev, st->calls, st->obst};
-  const int32_t n_tiles = (n + kTileEnvs - 1) / kTileEnvs;
-  const gx::TileTables tiles{n_tiles, max_tile_cells, nullptr};
+  const int32_t n_tiles = (n + tile_envs - 1) / tile_envs;
+  const gx::TileTables tiles{n_tiles, max_tile_cells, nullptr, tile_envs};
   if (reset) {
     gx::TrajBufs fb{nullptr, nullptr, nullptr, nullptr, 1};
     if (first) fb = gx::TrajBufs{first->obs, first->reward, first->flags, first->action, first->rows, obs_row,
