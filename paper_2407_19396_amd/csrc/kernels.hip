@@ -34,22 +34,15 @@ namespace {
 constexpr int kWave = 64;
 constexpr int kView = 7;
 constexpr int kObsBytes = kView * kView * 3;        // 147
-constexpr int kStageBytes = kWave * kObsBytes;      // 9408, a multiple of 16
-constexpr int kObsWords = 37;                       // ceil(147 / 4)
 constexpr int kCatBytes = kView * kView;            // categorical record: 49
-constexpr int kCatWords = 13;                       // ceil(49 / 4)
 
 // Cell triples are packed as type | colour << 8 | state << 16 (MiniGrid's
-// object, colour and state indices).  Bit 31 marks a see-through cell.
+// object, colour and state indices).
 constexpr uint32_t kEmpty = 1, kWall = 2, kDoor = 4, kKey = 5, kBall = 6, kBox = 7, kGoal = 8,
                    kLava = 9;
 constexpr uint32_t kGreen = 1, kGrey = 5;
 constexpr uint32_t kOpen = 0, kClosed = 1, kLocked = 2;
-constexpr uint32_t kSeeBit = 1u << 31;
-constexpr uint32_t kSeeBits = 0xFE000000u;   // see flags of view columns 0-6 at bits 31-25
-constexpr uint32_t kCellWall = kWall | (kGrey << 8);
 constexpr uint32_t kCellEmpty = kEmpty;
-constexpr uint32_t kCellGoal = kGoal | (kGreen << 8);
 
 constexpr uint32_t kFlagTerminated = 1, kFlagTruncated = 2, kFlagFirst = 4;
 constexpr uint32_t kActionNone = 0xFF;
@@ -62,17 +55,6 @@ enum : uint32_t {
 };
 constexpr int kMaxObst = 8;
 constexpr uint32_t kBlue = 2;
-constexpr uint32_t kCellBall = kBall | (kBlue << 8);
-
-__device__ __forceinline__ uint32_t see_through(uint32_t tri) {
-  const uint32_t type = tri & 0xFF, state = (tri >> 16) & 0xFF;
-  const bool opaque = type == kWall || (type == kDoor && state != kOpen);
-  return opaque ? 0u : kSeeBit;
-}
-
-// heading d: 0 east (+x), 1 south (+y), 2 west, 3 north
-__device__ __forceinline__ int dir_dx(int d) { return (d & 1) ? 0 : 1 - d; }
-__device__ __forceinline__ int dir_dy(int d) { return (d & 1) ? 2 - d : 0; }
 
 // ---------------------------------------------------------------------------
 // Philox4x32-10 (Salmon et al., SC'11): counter-based, so every draw is a
@@ -150,14 +132,6 @@ __device__ __forceinline__ uint32_t obst_at(const uint32_t (&ob)[4], int b) {
 __device__ __forceinline__ void obst_set(uint32_t (&ob)[4], int b, uint32_t x, uint32_t y) {
   const int sh = 16 * (b & 1);
   ob[b >> 1] = (ob[b >> 1] & ~(0xFFFFu << sh)) | ((x | (y << 8)) << sh);
-}
-
-__device__ __forceinline__ bool is_ball(const Layout& L, int x, int y) {
-  const uint32_t xy = (uint32_t)x | ((uint32_t)y << 8);
-  bool hit = false;
-#pragma unroll
-  for (int b = 0; b < kMaxObst; ++b) hit = hit || obst_at(L.ob, b) == xy;
-  return hit;
 }
 
 // The layout stream for the two generators whose number of draws varies: a
@@ -260,20 +234,6 @@ __device__ __forceinline__ Rivers crossings_layout(int S, int N, uint2 seed, uin
     }
   }
   return R;
-}
-
-// whether interior cell (x, y) of a Crossings layout is lava
-__device__ __forceinline__ bool crossings_lava(const Layout& L, int x, int y) {
-  bool lava = false;
-  if ((L.vmask >> x) & 1u) {
-    const int rank = __builtin_popcount(L.vmask & ((1u << x) - 1u));
-    lava = y != (int)((L.vopen >> (5 * rank)) & 31u);
-  }
-  if ((L.hmask >> y) & 1u) {
-    const int rank = __builtin_popcount(L.hmask & ((1u << y) - 1u));
-    lava = lava || x != (int)((L.hopen >> (5 * rank)) & 31u);
-  }
-  return lava;
 }
 
 // q = k / w, r = k % w for k < 2^16 and 1 <= w <= 32.  The single-precision
@@ -581,201 +541,10 @@ __device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32
   return L;
 }
 
-// content of cell (x, y) of a freshly generated layout (triple, no see bit)
-// GoToDoor door i's colour, or -1 when (x, y) holds no door
-__device__ __forceinline__ int gotodoor_door(const Layout& L, int x, int y) {
-  int i = -1;
-  i = (y == 0 && x == L.a) ? 0 : i;
-  i = (x == L.kx - 1 && y == L.b) ? 1 : i;
-  i = (y == L.ky - 1 && x == L.c) ? 2 : i;
-  i = (x == 0 && y == L.d) ? 3 : i;
-  return i < 0 ? -1 : (int)(((uint32_t)L.colour >> (4 * i)) & 15u);
-}
-
-// content of KeyCorridor cell (x, y): rooms of stride st = (S - 1) / 3 in
-// the top R * st + 1 rows, wall below; doors from the wall table
-__device__ __forceinline__ uint32_t keycorridor_cell(const Layout& L, int x, int y) {
-  const int st = (L.S - 1) / 3, R = L.b;
-  if (y > R * st) return kCellWall;
-  uint32_t qx, mx, qy, my;
-  small_divmod((uint32_t)x, (uint32_t)st, qx, mx);
-  small_divmod((uint32_t)y, (uint32_t)st, qy, my);
-  if (mx != 0 && my != 0) {
-    if (x == L.gx && y == L.gy) return kCellGoal;
-    if (x == L.kx && y == L.ky) return kKey | ((uint32_t)L.colour << 8);
-    return kCellEmpty;
-  }
-  if (mx == 0 && my == 0) return kCellWall;
-  int e;
-  uint32_t p;
-  if (mx == 0) {   // a wall between columns qx - 1 and qx, in row qy
-    if (qx == 0 || qx == 3) return kCellWall;
-    e = 2 * (int)qy + (int)qx - 1;
-    p = my - 1;
-  } else {         // a wall between rows qy - 1 and qy, in column qx
-    if (qy == 0 || (int)qy == R) return kCellWall;
-    if (qx == 1) return kCellEmpty;   // the hallway
-    e = 6 + 2 * ((int)qy - 1) + (int)(qx >> 1);
-    p = mx - 1;
-  }
-  const uint32_t d = kc_byte(L.kd, e);
-  if (!(d & 0x80u) || (d & 15u) != p) return kCellWall;
-  const uint32_t state = e == 2 * L.a + 1 ? kLocked : kClosed;
-  return kDoor | (((d >> 4) & 7u) << 8) | (state << 16);
-}
-
-__device__ __forceinline__ uint32_t layout_cell(const Layout& L, int x, int y) {
-  const int S = L.S;
-  if (L.fam == kFamKeyCorridor) return keycorridor_cell(L, x, y);
-  if (L.fam == kFamGoToDoor) {
-    const int dc = gotodoor_door(L, x, y);
-    if (dc >= 0) return kDoor | ((uint32_t)dc << 8) | (kClosed << 16);
-    return (x == 0 || y == 0 || x >= L.kx - 1 || y >= L.ky - 1) ? kCellWall : kCellEmpty;
-  }
-  if (x == 0 || y == 0 || x == S - 1 || y == S - 1) return kCellWall;
-  if (x == L.gx && y == L.gy) return kCellGoal;
-  if (L.fam == kFamTwoRoom) {
-    if (x == L.a) return y == L.b ? (kDoor | ((uint32_t)L.colour << 8) | (kLocked << 16)) : kCellWall;
-    if (x == L.kx && y == L.ky) return kKey | ((uint32_t)L.colour << 8);
-  } else if (L.fam == kFamFourRooms) {
-    const int m = S / 2;
-    if (x == m) return (y == L.a || y == L.b) ? kCellEmpty : kCellWall;
-    if (y == m) return (x == L.c || x == L.d) ? kCellEmpty : kCellWall;
-  } else if (L.fam == kFamLavaGap) {
-    if (x == L.a && y != L.b) return kLava;
-  } else if (L.fam == kFamCrossings) {
-    if (crossings_lava(L, x, y)) return kLava;
-  } else if (L.fam == kFamDistShift) {
-    if ((y == 1 || y == L.a) && x >= 3 && x <= S - 3) return kLava;
-  } else if (L.fam == kFamDynObs) {
-    if (is_ball(L, x, y)) return kCellBall;
-  }
-  return kCellEmpty;
-}
-
 __device__ __forceinline__ int bcast(int v, int lane) { return __builtin_amdgcn_readlane(v, lane); }
 
 __device__ __forceinline__ uint64_t bcast64(uint64_t v, int lane) {
   return (uint64_t)(uint32_t)bcast((int)(uint32_t)v, lane) | ((uint64_t)(uint32_t)bcast((int)(v >> 32), lane) << 32);
-}
-
-__device__ __forceinline__ Layout bcast_layout(const Layout& L, int r) {
-  Layout o;
-  o.fam = bcast(L.fam, r); o.S = bcast(L.S, r);
-  o.a = bcast(L.a, r); o.b = bcast(L.b, r); o.c = bcast(L.c, r); o.d = bcast(L.d, r);
-  o.colour = bcast(L.colour, r);
-  o.kx = bcast(L.kx, r); o.ky = bcast(L.ky, r);
-  o.gx = bcast(L.gx, r); o.gy = bcast(L.gy, r);
-  o.ax = o.ay = o.dir = 0;
-  o.vmask = (uint32_t)bcast((int)L.vmask, r);
-  o.hmask = (uint32_t)bcast((int)L.hmask, r);
-  o.vopen = (uint64_t)(uint32_t)bcast((int)(uint32_t)L.vopen, r) |
-            ((uint64_t)(uint32_t)bcast((int)(L.vopen >> 32), r) << 32);
-  o.hopen = (uint64_t)(uint32_t)bcast((int)(uint32_t)L.hopen, r) |
-            ((uint64_t)(uint32_t)bcast((int)(L.hopen >> 32), r) << 32);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) o.ob[i] = (uint32_t)bcast((int)L.ob[i], r);
-#pragma unroll
-  for (int i = 0; i < 3; ++i) o.kd[i] = (uint32_t)bcast((int)L.kd[i], r);
-  return o;
-}
-
-// ---------------------------------------------------------------------------
-// Intervention I(s, a) (Table "systems"; App. A): turn, forward with
-// collision, pickup, drop, toggle.  `front` is the triple ahead.
-// ---------------------------------------------------------------------------
-struct ActResult {
-  uint32_t new_front;
-  bool front_changed;
-  bool terminated;
-  bool goal;      // the task achieved: the goal reached, or (GoToDoor) done at the mission's door
-  bool penalty;   // ended with reward -1: walked into lava, or (Dynamic-Obstacles)
-                  // stepped forward at a ball or wall
-};
-
-__device__ __forceinline__ ActResult intervene(uint32_t act, int& x, int& y, int& dir, uint32_t& carry,
-                                               uint32_t front, int fx, int fy) {
-  // every lane of a wave holds its own action, so the rules are evaluated
-  // as selects rather than branches
-  const uint32_t type = front & 0xFF, colour = (front >> 8) & 0xFF, state = (front >> 16) & 0xFF;
-  const uint32_t front24 = front & 0xFFFFFFu;
-  dir = (dir + (act == kLeft ? 3 : (act == kRight ? 1 : 0))) & 3;
-  const bool walk = act == kForward && (type == kEmpty || type == kGoal || type == kLava ||
-                                        (type == kDoor && state == kOpen));
-  x = walk ? fx : x;
-  y = walk ? fy : y;
-  const bool pick = act == kPickup && carry == kCellEmpty && (type == kKey || type == kBall || type == kBox);
-  const bool drop = act == kDrop && carry != kCellEmpty && type == kEmpty;
-  const bool door = act == kToggle && type == kDoor;
-  const bool unlock = door && state == kLocked && (carry & 0xFF) == kKey && ((carry >> 8) & 0xFF) == colour;
-  const bool flip = door && state != kLocked;
-  const uint32_t door_open = kDoor | (colour << 8) | (kOpen << 16);
-  const uint32_t door_flipped = kDoor | (colour << 8) | ((state == kOpen ? kClosed : kOpen) << 16);
-  ActResult r;
-  r.new_front = pick ? kCellEmpty : (drop ? carry : (unlock ? door_open : (flip ? door_flipped : front24)));
-  r.front_changed = pick || drop || unlock || flip;
-  r.penalty = act == kForward && type == kLava;
-  r.goal = act == kForward && type == kGoal;
-  r.terminated = r.goal || r.penalty;
-  carry = pick ? front24 : (drop ? kCellEmpty : carry);
-  return r;
-}
-
-// ---------------------------------------------------------------------------
-// Transition system of Dynamic-Obstacles (Table "systems"; Fig. 1): every
-// ball, in list order, moves to a uniformly drawn empty cell of the 8
-// around it that the agent does not occupy (the k-th in row-major order,
-// k = u(count) of its word), or stays if there is none.  Ball b's word:
-// key = seed, counter (rng_id, call, b / 4, 2), lane b % 4.  Cells: the
-// grid accessor reads "is empty" and writes a ball or an empty cell.  List
-// entries off the interior (only a malformed state has them) do not move.
-// ---------------------------------------------------------------------------
-// position of the k-th (0-based) set bit of an 8-bit m, k < popcount(m):
-// halve the search range three times instead of clearing k bits one by one
-__device__ __forceinline__ uint32_t kth_bit8(uint32_t m, uint32_t k) {
-  uint32_t base = 0, p = (uint32_t)__builtin_popcount(m & 15u);
-  const bool hi4 = k >= p;
-  k -= hi4 ? p : 0u;
-  m = hi4 ? m >> 4 : m;
-  base += hi4 ? 4u : 0u;
-  p = (uint32_t)__builtin_popcount(m & 3u);
-  const bool hi2 = k >= p;
-  k -= hi2 ? p : 0u;
-  m = hi2 ? m >> 2 : m;
-  base += hi2 ? 2u : 0u;
-  return base + ((k >= (m & 1u)) ? 1u : 0u);
-}
-
-template <class Grid>
-__device__ __forceinline__ void move_obstacles(const Grid& g, int n, int ax, int ay, uint32_t (&ob)[4],
-                                               uint2 seed, uint32_t rng_id, uint32_t call) {
-  uint4 blk = make_uint4(0, 0, 0, 0);
-#pragma unroll
-  for (int b = 0; b < kMaxObst; ++b) {
-    if (b < n) {
-      if ((b & 3) == 0) blk = philox10(make_uint4(rng_id, call, (uint32_t)(b >> 2), 2u), seed);
-      const uint32_t word = pick4(blk, (uint32_t)(b & 3));
-      const uint32_t pos = obst_at(ob, b);
-      const int bx = (int)(pos & 0xFF), by = (int)(pos >> 8);
-      // an entry off the interior (a malformed state) is left alone, so no
-      // access ever leaves the env's grid
-      const bool inside = bx >= 1 && by >= 1 && bx <= g.S - 2 && by <= g.S - 2;
-      uint32_t mask = 0;   // bit i: neighbour i (row-major, the ball's own cell skipped) is empty
-      if (inside) mask = g.free8(bx, by);
-      // the agent's cell is never a destination
-      const uint32_t ac = (uint32_t)(3 * (ay - by + 1) + (ax - bx + 1));
-      if ((unsigned)(ax - bx + 1) < 3u && (unsigned)(ay - by + 1) < 3u && ac != 4u)
-        mask &= ~(1u << (ac - (ac > 4u)));
-      if (mask) {
-        const uint32_t i = kth_bit8(mask, bounded(word, (uint32_t)__builtin_popcount(mask)));
-        const uint32_t cell = i + (i >= 4u);   // 0..8 without the centre
-        const int dx = (int)(cell % 3u) - 1, dy = (int)(cell / 3u) - 1;
-        g.put_empty(bx, by);
-        g.put_ball(bx + dx, by + dy);
-        obst_set(ob, b, (uint32_t)(bx + dx), (uint32_t)(by + dy));
-      }
-    }
-  }
 }
 
 // Reward of Eq. (1) in the time-discounted form 1 - 0.9 * (t / T), t after
@@ -787,147 +556,12 @@ __device__ __forceinline__ float goal_reward(int32_t t, int32_t T, int32_t mode)
   return __fsub_rn(1.0f, p);
 }
 
-// Reward of a step: -1 for walking into lava (R2 of Table "envs") or, in
-// Dynamic-Obstacles, for stepping forward at a ball or wall (R3), in both
-// modes; the goal reward on reaching the goal; else 0.
-__device__ __forceinline__ float step_reward(const ActResult& r, int32_t t, int32_t T, int32_t mode) {
-  return r.penalty ? -1.0f : (r.goal ? goal_reward(t, T, mode) : 0.0f);
-}
-
-// GoToDoor's rules on top of the intervention (on_door_done of Tables
-// "rewards" and "terminations"): the done action (any value >= 6) with the
-// mission's door directly ahead achieves the task; toggling ends the
-// episode with reward 0.  mission = the target door's colour.
-__device__ __forceinline__ void gotodoor_rules(ActResult& r, uint32_t act, uint32_t front, uint32_t mission) {
-  const bool done_at = act >= 6u && (front & 0xFF) == kDoor && ((front >> 8) & 0xFF) == mission;
-  r.goal = r.goal || done_at;
-  r.terminated = r.terminated || done_at || act == kToggle;
-}
-
 // the mission reported with every record: GoToDoor's target colour, else 0xFF
 __device__ __forceinline__ uint32_t mission_of(uint32_t fam, uint32_t ob0) {
   return fam == kFamGoToDoor ? (ob0 & 0xFFu) : 0xFFu;
 }
 
-// ---------------------------------------------------------------------------
-// Observation O(s) (Table "observations", symbolic_first_person, R = 7):
-// the 7x7 view ahead of the agent, agent at view column 3 of row 6; walls
-// and non-open doors block sight.  Per view row the visible cells are the
-// seeds plus the see-through runs that touch a see-through seed, widened
-// by one cell on each side; the next row's seeds are the three cells ahead
-// of every visible see-through cell.  This is MiniGrid's two-pass rule in
-// bit-parallel form, the run fills being carry propagations.
-// ---------------------------------------------------------------------------
-// Row masks are kept in a dual form: the 7 column bits in bits 0-6 and the
-// same bits reversed in bits 25-31.  One add then fills runs towards higher
-// columns in the low half and towards lower columns in the high half (the
-// carry out of bit 6 dies in the empty bit 7, that of bit 31 leaves the
-// word), and one bit reversal merges the two directions.
-__device__ __forceinline__ uint32_t visible_row(uint32_t seeds2, uint32_t see, uint32_t& next2) {
-  const uint32_t p2 = see | __builtin_bitreverse32(see);
-  const uint32_t g2 = seeds2 & p2;
-  const uint32_t fill = (((p2 + g2) ^ p2) | g2) & p2;
-  const uint32_t run2 = fill | __builtin_bitreverse32(fill);
-  next2 = (run2 | (run2 << 1) | (run2 >> 1)) & 0xFE00007Fu;
-  return seeds2 | next2;
-}
-
-// Computes the lane's observation obs[j][i][c] (147 bytes) as the 38 words
-// u[0..37] it occupies once placed at byte 147 * slot of a record stage
-// (slot = the lane's position in the staged group; slot 0 starts a group).
-// rows.load_all(c) fills c[j][i] with the triple of view cell (i, j) and, when
-// it is see-through, bit 31 - i set (no other bit of the top byte).  Lanes with valid == false produce zeros (their
-// loader must still be safe to call).
-//
-// Records are realigned to their byte offset with byte permutes.  A word
-// shared by two neighbouring records belongs to the higher one: u[0] of a
-// record starting mid-word already holds the lower record's tail, received
-// by a cross-lane shuffle; store_words writes exactly the words a record
-// owns.
-template <bool kCat, class Rows>
-__device__ __forceinline__ void observe_words(const Rows& rows, uint32_t carry, bool valid, int slot,
-                                              uint32_t (&u)[kObsWords + 1]) {
-  constexpr int kBytes = kCat ? kCatBytes : kObsBytes;
-  constexpr int kWords = kCat ? kCatWords : kObsWords;
-  const uint32_t m = (uint32_t)(kBytes * slot) & 3u;
-  const uint32_t realign = 0x07060504u - m * 0x01010101u;
-
-  // all 49 reads first: they are independent and stay in flight together
-  uint32_t cells[kView][kView];
-  rows.load_all(cells);
-
-  uint32_t seeds = valid ? ((1u << 3) | (1u << 28)) : 0u;   // column 3, dual form
-  // masked first cells of the row processed before (row j + 1); zero past
-  // the record's end
-  uint32_t later[3] = {0u, 0u, 0u};
-  uint32_t w_hi = 0;          // record word d + 1 (zero past the end)
-#pragma unroll
-  for (int j = kView - 1; j >= 0; --j) {
-    uint32_t (&c)[kView] = cells[j];
-    // see-through bits: cell i carries its flag at bit 31 - i, so the row's
-    // flags are one OR away, already in the high half of the dual form
-    const uint32_t see = ((c[0] | c[1] | c[2]) | (c[3] | c[4] | c[5]) | c[6]) & kSeeBits;
-    uint32_t next;
-    const uint32_t vis = visible_row(seeds, see, next);
-    seeds = next;
-#pragma unroll
-    for (int i = 0; i < kView; ++i) c[i] &= (uint32_t)(((int32_t)(vis << (31 - i))) >> 31);
-    if (j == kView - 1) c[3] = valid ? carry : 0u;   // the agent's cell shows what it carries
-#pragma unroll
-    for (int d = kWords - 1; d >= 0; --d) {
-      uint32_t wd;
-      if (kCat) {
-        // word d holds the types of cells 4d .. 4d + 3 (byte b = cell b)
-        const int k = 4 * d;
-        if (k / kView != j) continue;
-        const int i = k - kView * j;
-        const uint32_t c0 = c[i];
-        const uint32_t c1 = i + 1 < kView ? c[i + 1] : later[i + 1 - kView];
-        const uint32_t c2 = i + 2 < kView ? c[i + 2] : later[i + 2 - kView];
-        const uint32_t c3 = i + 3 < kView ? c[i + 3] : later[i + 3 - kView];
-        wd = __builtin_amdgcn_perm(__builtin_amdgcn_perm(c3, c2, 0x0C0C0400u),
-                                   __builtin_amdgcn_perm(c1, c0, 0x0C0C0400u), 0x05040100u);
-      } else {
-        // word d spans cells 4d/3 and 4d/3 + 1 (byte b belongs to cell b / 3)
-        const int k = (4 * d) / 3;
-        if (k / kView != j) continue;
-        const int i = k - kView * j, off = (4 * d) % 3;
-        const uint32_t sel = off == 0 ? 0x04020100u : (off == 1 ? 0x05040201u : 0x06050402u);
-        wd = __builtin_amdgcn_perm(i + 1 < kView ? c[i + 1] : later[0], c[i], sel);
-      }
-      u[d + 1] = __builtin_amdgcn_perm(w_hi, wd, realign);
-      w_hi = wd;
-    }
-    later[0] = c[0];
-    later[1] = c[1];
-    later[2] = c[2];
-  }
-  u[0] = __builtin_amdgcn_perm(w_hi, 0u, realign);
-  // the word a record shares with the next one (the one holding the next
-  // record's first byte): symbolic u[36] when the record starts on a word
-  // boundary, u[37] when it starts two or three bytes in; categorical u[12]
-  const uint32_t tail = kCat ? u[kCatWords - 1] : (m == 0 ? u[kObsWords - 1] : u[kObsWords]);
-  const uint32_t lower_tail = (uint32_t)__shfl_up((int)tail, 1, kWave);
-  if (m != 0) u[0] |= lower_tail;
-}
-
-// Writes the words a record owns (see observe_words) at stage + bytes * slot:
-// all but the word holding the next record's first byte, which that record
-// writes (symbolic: the next record starts inside word 36 unless m == 1 puts
-// it at word 37; categorical: inside word 12 unless m == 3).
-template <bool kCat>
-__device__ __forceinline__ void store_words(uint8_t* stage, int slot, const uint32_t (&u)[kObsWords + 1]) {
-  constexpr int kBytes = kCat ? kCatBytes : kObsBytes;
-  constexpr int kWords = kCat ? kCatWords : kObsWords;
-  const uint32_t s = (uint32_t)(kBytes * slot);
-  const uint32_t m = s & 3u;
-  uint32_t* base = reinterpret_cast<uint32_t*>(stage) + (s >> 2);
-#pragma unroll
-  for (int q = 0; q < kWords - 1; ++q) base[q] = u[q];
-  if (kCat ? m == 3 : m != 0) base[kWords - 1] = u[kWords - 1];
-}
-
-// Both kernels' workgroups are single waves and all the data its lanes
+// Every kernel's workgroups are single waves and all the data its lanes
 // exchange lives in LDS, whose operations a wave performs in issue order: a
 // wavefront-scope fence (no wait instruction) plus a compiler barrier is
 // enough to make one lane's LDS writes visible to the others' later reads.
@@ -939,562 +573,10 @@ __device__ __forceinline__ void wave_sync() {
 
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
-// Copies the first `bytes` (1 <= bytes <= kMaxBytes) staged bytes to dst.
-// To a 16-byte aligned dst the whole 16-byte chunks go as vector stores
-// (all of a lane's LDS reads issued before its stores, so the reads are in
-// flight together) and the last bytes % 16 bytes one by one; otherwise
-// every byte goes alone.
-template <int kMaxBytes>
-__device__ __forceinline__ void copy_piece(const uint8_t* stage, uint8_t* dst, int bytes, int lane) {
-  constexpr int kMaxChunks = (kMaxBytes + 15) / 16;
-  constexpr int kPerLane = (kMaxChunks + kWave - 1) / kWave;
-  if ((reinterpret_cast<uintptr_t>(dst) & 15) == 0) {
-    const u32x4* src = reinterpret_cast<const u32x4*>(stage);
-    u32x4* out = reinterpret_cast<u32x4*>(dst);
-    const int n = bytes >> 4;
-    if (n > 0) {
-      // Reads clamp to the last chunk so they need no branch.
-      u32x4 v[kPerLane];
-#pragma unroll
-      for (int i = 0; i < kPerLane; ++i) v[i] = src[min(lane + i * kWave, n - 1)];
-#pragma unroll
-      for (int i = 0; i < kPerLane; ++i) {
-        const int c = lane + i * kWave;
-        if (c < n) __builtin_nontemporal_store(v[i], out + c);
-      }
-    }
-    if (lane < (bytes & 15)) dst[16 * n + lane] = stage[16 * n + lane];
-  } else {
-    for (int b = lane; b < bytes; b += kWave) dst[b] = stage[b];
-  }
-}
-
-// Copies n_envs staged records of kBytes bytes (1 <= n_envs <= kMaxEnvs) to dst.
-template <int kMaxEnvs, int kBytes>
-__device__ __forceinline__ void copy_out(const uint8_t* stage, uint8_t* dst, int n_envs, int lane) {
-  copy_piece<kMaxEnvs * kBytes>(stage, dst, n_envs * kBytes, lane);
-}
-
-// ---------------------------------------------------------------------------
-// Whole-grid observations (Table "observations": symbolic [S][S][3] and
-// categorical [S][S]), MiniGrid's fully observed encoding: every cell's
-// triple (or type) with the agent drawn over its own cell as (10, red,
-// heading).  A wave's records are contiguous in the output row, exactly like
-// its envs' grids, so the wave writes them as one byte range [0, n): window
-// by window, the lanes fill the LDS stage a word at a time (fill(o) returns
-// output bytes o..o+3; o may fall outside [0, n) at the window edges, where
-// the bytes are never stored), every lane then writes its agent's bytes over
-// its cell, and the window leaves as 16-byte aligned stores; bytes outside
-// [0, n) belong to neighbouring waves' records and are left alone.
-// ---------------------------------------------------------------------------
 constexpr uint32_t kAgent = 10;
 
-template <int kWin, class Fill>
-__device__ __forceinline__ void emit_grids(uint8_t* dst, int64_t n, uint8_t* stage, int lane, bool has_agent,
-                                           int64_t agent_o, uint32_t agent_bytes, int agent_len,
-                                           const Fill& fill) {
-  static_assert(kWin % 16 == 0, "stage windows are whole 16-byte chunks");
-  const uintptr_t d0 = reinterpret_cast<uintptr_t>(dst), d1 = d0 + (uintptr_t)n;
-  uint32_t* words = reinterpret_cast<uint32_t*>(stage);
-  // windows start on 64-byte boundaries of the output (kWin is a multiple
-  // of 64), so every store instruction covers whole 64-byte units of HBM
-  static_assert(kWin % 64 == 0, "windows keep the 64-byte alignment");
-  for (uintptr_t A = d0 & ~(uintptr_t)63; A < d1; A += kWin) {
-    const int win = (int)min((uintptr_t)kWin, (d1 - A + 15) & ~(uintptr_t)15);
-    const int64_t rel = (int64_t)A - (int64_t)d0;   // output byte of stage byte 0, >= -63
-    for (int q = lane; q < (win >> 2); q += kWave) words[q] = fill(rel + 4 * q);
-    wave_sync();
-    if (has_agent) {
-      for (int k = 0; k < agent_len; ++k) {
-        const int64_t p = agent_o + k - rel;
-        if (p >= 0 && p < win) stage[p] = (uint8_t)(agent_bytes >> (8 * k));
-      }
-    }
-    wave_sync();
-    for (int c = lane; c < (win >> 4); c += kWave) {
-      const uintptr_t a = A + 16 * (uintptr_t)c;
-      if (a >= d0 && a + 16 <= d1) {
-        __builtin_nontemporal_store(reinterpret_cast<const u32x4*>(stage)[c], reinterpret_cast<u32x4*>(a));
-      } else {
-        for (int b = 0; b < 16; ++b)
-          if (a + b >= d0 && a + b < d1) reinterpret_cast<uint8_t*>(a)[b] = stage[16 * c + b];
-      }
-    }
-    wave_sync();
-  }
-}
-
-// Fill of symbolic records from the HBM grids (the plain kernel): output
-// byte o is byte o of the wave's grid block of n bytes.
-struct FillHbmSymbolic {
-  const uint8_t* src;
-  int64_t n;
-  __device__ __forceinline__ uint32_t operator()(int64_t o) const {
-    uint32_t w = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (o + k >= 0 && o + k < n) w |= (uint32_t)src[o + k] << (8 * k);
-    return w;
-  }
-};
-
-// Categorical records from the HBM grids: output byte o is the type channel
-// of cell o of the wave's block of n cells.
-struct FillHbmCategorical {
-  const uint8_t* src;
-  int64_t n;
-  __device__ __forceinline__ uint32_t operator()(int64_t o) const {
-    uint32_t w = 0;
-#pragma unroll
-    for (int k = 0; k < 4; ++k)
-      if (o + k >= 0 && o + k < n) w |= (uint32_t)src[3 * (o + k)] << (8 * k);
-    return w;
-  }
-};
-
 // ---------------------------------------------------------------------------
-// Plain kernel
-// ---------------------------------------------------------------------------
-// Cell (x, y) for view column i: the triple, plus bit 31 - i if see-through.
-struct HbmCells {
-  const uint8_t* g;
-  int S;
-  __device__ __forceinline__ uint32_t operator()(int x, int y, int i) const {
-    if ((unsigned)x >= (unsigned)S || (unsigned)y >= (unsigned)S) return kCellWall;
-    const uint8_t* p = g + 3 * (y * S + x);
-    const uint32_t tri = (uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16);
-    return tri | (see_through(tri) >> i);
-  }
-};
-
-// The 7x7 view straight from the HBM grid, cells outside it read as walls.
-// Whatever the heading, the view covers a 7x7 square of the world: 7 grid
-// rows of 7 consecutive cells, i.e. 21 contiguous bytes each.  A row is
-// read as the 24 bytes from its dword-aligned start (one 16-byte and one
-// 8-byte load) instead of 21 byte loads; near the grid's first and last
-// bytes the row falls back to single dwords, each read only if it holds a
-// byte of the env's grid.  The square is then turned to the view's
-// orientation by selects on the heading.
-struct HbmWindow {
-  const uint8_t* g;
-  int S;   // 0: every cell reads as a wall
-  int ax, ay, dir;
-  __device__ __forceinline__ void load_all(uint32_t (&c)[kView][kView]) const {
-    // top-left world cell of the square
-    const int x0 = dir == 0 ? ax : (dir == 2 ? ax - 6 : ax - 3);
-    const int y0 = dir == 3 ? ay - 6 : (dir == 1 ? ay : ay - 3);
-    const uintptr_t gb = reinterpret_cast<uintptr_t>(g);
-    const uintptr_t lo = gb & ~(uintptr_t)3, hi = (gb + 3 * (uintptr_t)(S * S) + 3) & ~(uintptr_t)3;
-    uint32_t w[kView][6];
-#pragma unroll
-    for (int r = 0; r < kView; ++r) {
-      const int yy = y0 + r;
-#pragma unroll
-      for (int d = 0; d < 6; ++d) w[r][d] = 0u;
-      if ((unsigned)yy < (unsigned)S) {
-        const uintptr_t a = (uintptr_t)((intptr_t)gb + 3 * (intptr_t)(yy * S + x0)) & ~(uintptr_t)3;
-        if (a >= lo && a + 24 <= hi) {
-          const uint32_t* q = reinterpret_cast<const uint32_t*>(a);
-          const u32x4 v4 = *reinterpret_cast<const u32x4*>(q);
-          const uint2 v2 = *reinterpret_cast<const uint2*>(q + 4);
-          w[r][0] = v4.x; w[r][1] = v4.y; w[r][2] = v4.z; w[r][3] = v4.w;
-          w[r][4] = v2.x; w[r][5] = v2.y;
-        } else {
-#pragma unroll
-          for (int d = 0; d < 6; ++d)
-            if (a + 4 * d >= lo && a + 4 * d < hi) w[r][d] = reinterpret_cast<const uint32_t*>(a)[d];
-        }
-      }
-    }
-    // world cell (x0 + k, y0 + r), with its see-through flag at bit 31
-    uint32_t W[kView][kView];
-#pragma unroll
-    for (int r = 0; r < kView; ++r) {
-      const int yy = y0 + r;
-      const uint32_t rb = (uint32_t)((uintptr_t)((intptr_t)gb + 3 * (intptr_t)(yy * S + x0)) & 3);
-      uint32_t b[6];
-#pragma unroll
-      for (int d = 0; d < 5; ++d) b[d] = __builtin_amdgcn_alignbyte(w[r][d + 1], w[r][d], rb);
-      b[5] = w[r][5] >> (8 * rb);
-#pragma unroll
-      for (int k = 0; k < kView; ++k) {
-        const int o = 3 * k, d = o >> 2, off = o & 3;
-        const uint32_t tri = (__builtin_amdgcn_alignbyte(b[d + 1], b[d], (uint32_t)off)) & 0xFFFFFFu;
-        const bool in = (unsigned)yy < (unsigned)S && (unsigned)(x0 + k) < (unsigned)S;
-        W[r][k] = in ? tri | see_through(tri) : kCellWall;
-      }
-    }
-    // view cell (i, j) = world a + (i - 3) right + (6 - j) ahead
-#pragma unroll
-    for (int j = 0; j < kView; ++j)
-#pragma unroll
-      for (int i = 0; i < kView; ++i) {
-        uint32_t v = W[j][i];                              // north
-        v = dir == 0 ? W[i][6 - j] : v;                    // east
-        v = dir == 1 ? W[6 - j][6 - i] : v;                // south
-        v = dir == 2 ? W[6 - i][j] : v;                    // west
-        c[j][i] = (v & ~kSeeBit) | ((v & kSeeBit) >> i);
-      }
-  }
-};
-
-// The plain kernel's view, read before the action is applied.  The step can
-// only end in one of two 7x7 squares: a turn ends in the new heading's
-// square; forward ends in the current square or in the one a cell ahead;
-// every other action (and a reset) keeps the current square.  Their union is
-// the final heading's square extended by one cell along that heading, at
-// most 8 grid rows of 8 cells, and it holds the cell ahead as well.  Reading
-// it as soon as the action is known puts the cell ahead and the view in one
-// round trip to HBM instead of two dependent ones.
-//
-// Region cell (k, r) is world cell (X0 + k, Y0 + r).  Heading east the region
-// starts at the agent's column, west 7 cells behind it; south at the agent's
-// row, north 7 rows above it; across the heading it spans the square's 7
-// cells.  The final square starts at offset m along the heading: east and
-// south m = 1 when the agent moved, west and north m = 0 when it moved.
-struct HbmSpan {
-  uint32_t w[8][7];   // row r: the 28 bytes from the dword-aligned start of cell (X0, Y0 + r)
-  uintptr_t gb;
-  int S, X0, Y0, dir;
-
-  // dir: the heading the step ends with; rows outside the grid and the
-  // eighth row of a horizontal heading are not read
-  __device__ __forceinline__ void load(const uint8_t* g, int S_, int ax, int ay, int dir_) {
-    gb = reinterpret_cast<uintptr_t>(g);
-    S = S_;
-    dir = dir_;
-    X0 = dir == 0 ? ax : (dir == 2 ? ax - 7 : ax - 3);
-    Y0 = dir == 1 ? ay : (dir == 3 ? ay - 7 : ay - 3);
-    const bool vert = (dir & 1) != 0;
-    const uintptr_t lo = gb & ~(uintptr_t)3, hi = (gb + 3 * (uintptr_t)(S * S) + 3) & ~(uintptr_t)3;
-#pragma unroll
-    for (int r = 0; r < 8; ++r) {
-      const int yy = Y0 + r;
-#pragma unroll
-      for (int d = 0; d < 7; ++d) w[r][d] = 0u;
-      if ((unsigned)yy < (unsigned)S && (r < 7 || vert)) {
-        const uintptr_t a = (uintptr_t)((intptr_t)gb + 3 * (intptr_t)(yy * S + X0)) & ~(uintptr_t)3;
-        if (a >= lo && a + 28 <= hi) {
-          const u32x4 v4 = *reinterpret_cast<const u32x4*>(a);
-          const uint32_t* q = reinterpret_cast<const uint32_t*>(a + 16);
-          w[r][0] = v4.x; w[r][1] = v4.y; w[r][2] = v4.z; w[r][3] = v4.w;
-          w[r][4] = q[0]; w[r][5] = q[1]; w[r][6] = q[2];
-        } else {
-#pragma unroll
-          for (int d = 0; d < 7; ++d)
-            if (a + 4 * d >= lo && a + 4 * d < hi) w[r][d] = reinterpret_cast<const uint32_t*>(a)[d];
-        }
-      }
-    }
-  }
-
-  // the triple of region cell (k, r); a cell outside the grid reads as
-  // whatever the loaded bytes hold there (bytes of the grid's other rows, up
-  // to 3 bytes of a neighbouring env's grid in the dwords at the grid's two
-  // ends, or zeros for rows that were not read)
-  __device__ __forceinline__ uint32_t cell(int k, int r) const {
-    const int yy = Y0 + r;
-    const uint32_t rb = (uint32_t)((uintptr_t)((intptr_t)gb + 3 * (intptr_t)(yy * S + X0)) & 3);
-    const int o = 3 * k, d = o >> 2, off = o & 3;
-    const uint32_t b0 = __builtin_amdgcn_alignbyte(w[r][d + 1], w[r][d], rb);
-    const uint32_t b1 = d + 2 < 7 ? __builtin_amdgcn_alignbyte(w[r][d + 2], w[r][d + 1], rb) : w[r][d + 1] >> (8 * rb);
-    return __builtin_amdgcn_alignbyte(b1, b0, (uint32_t)off) & 0xFFFFFFu;
-  }
-
-  // the cell ahead of the agent before it moves (heading dir, no turn)
-  __device__ __forceinline__ uint32_t front() const {
-    return dir == 0 ? cell(1, 3) : (dir == 1 ? cell(3, 1) : (dir == 2 ? cell(6, 3) : cell(3, 6)));
-  }
-
-  // c[j][i] as for observe_words, for the square at offset m along the
-  // heading; `patch` replaces the cell ahead of the unmoved agent (a
-  // pickup, drop or toggle, which neither move nor turn it).  Cells outside
-  // the grid are not masked: whenever the grid's outer ring is opaque (walls
-  // and closed or locked doors) sight never crosses it, so none of them is
-  // ever visible.  Only a door on the ring toggled open breaks that, and
-  // such a step reads its view bounds-checked instead.
-  __device__ __forceinline__ void view(bool moved, bool patch, uint32_t new_front,
-                                       uint32_t (&c)[kView][kView]) const {
-    const bool vert = (dir & 1) != 0;
-    const bool m = moved != (dir >= 2);
-    uint32_t R[8][8];
-#pragma unroll
-    for (int r = 0; r < 8; ++r)
-#pragma unroll
-      for (int k = 0; k < 8; ++k) R[r][k] = (r == 7 && k == 7) ? 0u : cell(k, r);
-    const uint32_t nf = new_front;
-    R[3][1] = patch && dir == 0 ? nf : R[3][1];
-    R[1][3] = patch && dir == 1 ? nf : R[1][3];
-    R[3][6] = patch && dir == 2 ? nf : R[3][6];
-    R[6][3] = patch && dir == 3 ? nf : R[6][3];
-    // world cell (X0 + k, Y0 + r) of the final square, offset applied
-    uint32_t W[kView][kView];
-#pragma unroll
-    for (int r = 0; r < kView; ++r)
-#pragma unroll
-      for (int k = 0; k < kView; ++k) W[r][k] = m ? (vert ? R[r + 1][k] : R[r][k + 1]) : R[r][k];
-    // view cell (i, j) = world a + (i - 3) right + (6 - j) ahead
-#pragma unroll
-    for (int j = 0; j < kView; ++j)
-#pragma unroll
-      for (int i = 0; i < kView; ++i) {
-        uint32_t v = W[j][i];                              // north
-        v = dir == 0 ? W[i][6 - j] : v;                    // east
-        v = dir == 1 ? W[6 - j][6 - i] : v;                // south
-        v = dir == 2 ? W[6 - i][j] : v;                    // west
-        c[j][i] = v | (see_through(v) >> i);
-      }
-  }
-};
-
-// A view computed beforehand, handed to observe_words.
-struct ViewCells {
-  const uint32_t (&c)[kView][kView];
-  __device__ __forceinline__ void load_all(uint32_t (&o)[kView][kView]) const {
-#pragma unroll
-    for (int j = 0; j < kView; ++j)
-#pragma unroll
-      for (int i = 0; i < kView; ++i) o[j][i] = c[j][i];
-  }
-};
-
-// View rows straight from the HBM grid, cells outside it read as walls.
-struct HbmRows {
-  HbmCells cells;
-  int ax, ay, fx, fy;
-  __device__ __forceinline__ void load(int j, uint32_t (&c)[kView]) const {
-    const int rx = -fy, ry = fx;
-    const int bx = ax - 3 * rx + (6 - j) * fx, by = ay - 3 * ry + (6 - j) * fy;
-#pragma unroll
-    for (int i = 0; i < kView; ++i) c[i] = cells(bx + i * rx, by + i * ry, i);
-  }
-  __device__ __forceinline__ void load_all(uint32_t (&c)[kView][kView]) const {
-#pragma unroll
-    for (int j = kView - 1; j >= 0; --j) load(j, c[j]);
-  }
-};
-
-__device__ __forceinline__ void store_triple(uint8_t* p, uint32_t tri) {
-  p[0] = (uint8_t)tri;
-  p[1] = (uint8_t)(tri >> 8);
-  p[2] = (uint8_t)(tri >> 16);
-}
-
-// Grid accessors for the obstacle transition: HBM triples, LDS codes.
-struct HbmGrid {
-  uint8_t* g;
-  int S;
-  // the 8 cells around interior cell (x, y), row-major, as bits: set = empty
-  __device__ __forceinline__ uint32_t free8(int x, int y) const {
-    const uint8_t* p = g + 3 * ((y - 1) * S + (x - 1));
-    const uint8_t* q = p + 3 * S;
-    const uint8_t* r = q + 3 * S;
-    return (p[0] == kEmpty ? 1u : 0u) | (p[3] == kEmpty ? 2u : 0u) | (p[6] == kEmpty ? 4u : 0u) |
-           (q[0] == kEmpty ? 8u : 0u) | (q[6] == kEmpty ? 16u : 0u) | (r[0] == kEmpty ? 32u : 0u) |
-           (r[3] == kEmpty ? 64u : 0u) | (r[6] == kEmpty ? 128u : 0u);
-  }
-  __device__ __forceinline__ void put_empty(int x, int y) const { store_triple(g + 3 * (y * S + x), kCellEmpty); }
-  __device__ __forceinline__ void put_ball(int x, int y) const { store_triple(g + 3 * (y * S + x), kCellBall); }
-};
-
-struct PlainArgs {
-  EnvTables env;
-  StateBufs st;
-  const uint8_t* actions;
-  TrajBufs out;
-  int32_t row;
-};
-
-__global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
-  __shared__ __align__(16) uint8_t stage[kStageBytes];   // and the draw window, before
-  static_assert(kDrawBytes <= kStageBytes, "the draw window fits the stage");
-  const int lane = threadIdx.x;
-  const int e0 = blockIdx.x * kWave;
-  const int e = e0 + lane;
-  const int N = a.env.n;
-  const bool active = e < N;
-  const int n_here = min(kWave, N - e0);
-
-  uint32_t fam = 0, meta = 0;
-  int S = 5, T = 1, x = 1, y = 1, dir = 0, t = 0;
-  uint32_t carry = kCellEmpty, episode = 0, rid = 0, calls = 0;
-  bool done_prev = false;
-  uint2 seed = make_uint2(0, 0);
-  uint8_t* g = a.st.grid;
-  uint64_t goff = 0;
-  uint32_t ob[4] = {~0u, ~0u, ~0u, ~0u};
-  if (active) {
-    meta = a.env.meta[e];
-    fam = meta & 0xFF;
-    S = (int)((meta >> 8) & 0xFF);
-    T = a.env.max_steps[e];
-    seed = a.env.seed[e];
-    rid = a.env.rng_id[e];
-    goff = a.env.grid_off[e];
-    g = a.st.grid + goff;
-    x = a.st.x[e];
-    y = a.st.y[e];
-    dir = a.st.dir[e];
-    t = a.st.t[e];
-    carry = (uint32_t)a.st.carry[e];
-    episode = a.st.episode[e];
-    done_prev = a.st.done_prev[e] != 0;
-    calls = a.st.calls[e];
-    if (fam == kFamDynObs || fam == kFamGoToDoor) {   // the balls, or the mission
-      const uint4 o4 = *reinterpret_cast<const uint4*>(a.st.obst + 16 * (size_t)e);
-      ob[0] = o4.x; ob[1] = o4.y; ob[2] = o4.z; ob[3] = o4.w;
-    }
-  }
-  const bool do_reset = active && done_prev;
-  Layout L{};
-  if (do_reset) {
-    episode += 1u;
-    L = make_layout(meta, seed, rid, episode, reinterpret_cast<uint32_t*>(stage) + lane);
-    x = L.ax;
-    y = L.ay;
-    dir = L.dir;
-    t = 0;
-    carry = kCellEmpty;
-#pragma unroll
-    for (int i = 0; i < 4; ++i) ob[i] = L.ob[i];
-  }
-  // the wave writes every resetting env's new grid together, 32 cells a row
-  uint64_t pending = __ballot(do_reset);
-  while (pending) {
-    const int r = __ffsll((unsigned long long)pending) - 1;
-    pending &= pending - 1;
-    const Layout Lr = bcast_layout(L, r);
-    const uint64_t gr = ((uint64_t)(uint32_t)bcast((int)(uint32_t)reinterpret_cast<uint64_t>(g), r)) |
-                        ((uint64_t)(uint32_t)bcast((int)(uint32_t)(reinterpret_cast<uint64_t>(g) >> 32), r) << 32);
-    uint8_t* gp = reinterpret_cast<uint8_t*>(gr);
-    const int xx = lane & 31;
-    for (int yy = lane >> 5; yy < Lr.S; yy += 2)
-      if (xx < Lr.S) store_triple(gp + 3 * (yy * Lr.S + xx), layout_cell(Lr, xx, yy));
-  }
-  __threadfence_block();
-  __syncthreads();
-
-  uint32_t act = 0;
-  if (active && !do_reset) {
-    if (a.actions) {
-      act = a.actions[e];
-    } else {
-      act = bounded(pick4(policy_block(seed, rid, calls), calls & 3u), 7u);
-    }
-  }
-  // The first-person modes read the view as soon as the action is known
-  // (HbmSpan), the cell ahead included.  Dynamic-Obstacles envs, whose
-  // balls move before the action applies, read the cell ahead and the view
-  // from HBM afterwards instead, and so does every env when the records are
-  // whole grids (copied from the grids) or not written at all.
-  const bool span_view = a.out.obs != nullptr && a.env.obs_mode < 2;
-  HbmSpan span;
-  if (span_view) {
-    const int dir_f = do_reset ? dir : (dir + (act == kLeft ? 3 : (act == kRight ? 1 : 0))) & 3;
-    span.load(g, active && fam != kFamDynObs ? S : 0, x, y, dir_f);
-  }
-
-  float reward = 0.0f;
-  uint32_t flags = 0, act_rec = kActionNone;
-  bool moved = false, patch = false, edge_view = false;
-  uint32_t new_front = 0;
-  if (active && !do_reset) {
-    const int fx = x + dir_dx(dir), fy = y + dir_dy(dir);
-    const HbmCells cells{g, S};
-    const bool ahead_in_span = span_view && fam != kFamDynObs;
-    uint32_t front;
-    if (ahead_in_span) front = span.front();
-    else front = cells(fx, fy, 0);
-    bool blocked = false;
-    if (fam == kFamDynObs) {
-      // three actions; the cell ahead is judged before the balls move
-      act = act > kForward ? kLeft : act;
-      blocked = (front & 0xFF) != kEmpty && (front & 0xFF) != kGoal;
-      move_obstacles(HbmGrid{g, S}, (int)((meta >> 16) & 0xFF), x, y, ob, seed, rid, calls);
-      front = cells(fx, fy, 0);
-    }
-    const int x_was = x, y_was = y;
-    ActResult r = intervene(act, x, y, dir, carry, front, fx, fy);
-    moved = x != x_was || y != y_was;
-    r.penalty = r.penalty || (blocked && act == kForward);
-    r.terminated = r.terminated || r.penalty;
-    if (fam == kFamGoToDoor) gotodoor_rules(r, act, front, ob[0] & 0xFFu);
-    if (r.front_changed) store_triple(g + 3 * (fy * S + fx), r.new_front);
-    patch = r.front_changed;
-    new_front = r.new_front;
-    edge_view = fam == kFamGoToDoor && r.front_changed;   // a door toggled, possibly on the outer ring
-    t += 1;
-    const bool trunc = t >= T;
-    reward = step_reward(r, t, T, a.env.reward_mode);
-    flags = (r.terminated ? kFlagTerminated : 0u) | (trunc ? kFlagTruncated : 0u);
-    done_prev = r.terminated || trunc;
-    act_rec = act & 0xFF;
-  } else if (do_reset) {
-    flags = kFlagFirst;
-    done_prev = false;
-  }
-
-  const size_t rowN = (size_t)a.row * (size_t)N;
-  if (a.out.obs && a.env.obs_mode >= 2) {
-    // whole-grid records: the step's grid writes by every lane (resets,
-    // doors, keys, balls) must be visible before the wave copies the grids
-    __threadfence_block();
-    __syncthreads();
-    const uint64_t G0 = (uint64_t)__shfl((long long)goff, 0, kWave);
-    const uint64_t end = active ? goff + 3ull * (uint64_t)(S * S) : 0ull;
-    const int64_t n = (int64_t)((uint64_t)__shfl((long long)end, n_here - 1, kWave) - G0);
-    const int64_t cell = (int64_t)(goff - G0) / 3 + y * S + x;   // the agent's cell in the block
-    const uint8_t* src = a.st.grid + G0;
-    uint8_t* dst = a.out.obs + (size_t)a.row * a.out.obs_row;
-    if (a.env.obs_mode == 3)
-      emit_grids<kStageBytes>(dst + G0 / 3, n / 3, stage, lane, active, cell, kAgent, 1,
-                              FillHbmCategorical{src, n / 3});
-    else
-      emit_grids<kStageBytes>(dst + G0, n, stage, lane, active, 3 * cell, kAgent | ((uint32_t)dir << 16), 3,
-                              FillHbmSymbolic{src, n});
-  } else if (a.out.obs) {
-    // inactive lanes read no cell (S = 0 above): every cell is a wall
-    uint32_t u[kObsWords + 1];
-    uint32_t view[kView][kView];
-    span.view(moved, patch, new_front, view);
-    // balls that moved, or a door on the ring toggled open: read the view
-    // again, bounds-checked, from the grid as the step left it
-    if (fam == kFamDynObs || edge_view) HbmWindow{g, S, x, y, dir}.load_all(view);
-    const ViewCells rows{view};
-    if (a.env.obs_mode == 1) {
-      observe_words<true>(rows, carry, active, lane, u);
-      store_words<true>(stage, lane, u);
-      __syncthreads();
-      copy_out<kWave, kCatBytes>(stage, a.out.obs + (rowN + (size_t)e0) * kCatBytes, n_here, lane);
-    } else {
-      observe_words<false>(rows, carry, active, lane, u);
-      store_words<false>(stage, lane, u);
-      __syncthreads();
-      copy_out<kWave, kObsBytes>(stage, a.out.obs + (rowN + (size_t)e0) * kObsBytes, n_here, lane);
-    }
-  }
-  if (active) {
-    a.out.reward[rowN + e] = reward;
-    a.out.flags[rowN + e] = (uint8_t)flags;
-    a.out.action[rowN + e] = (uint8_t)act_rec;
-    if (a.out.mission) a.out.mission[rowN + e] = (uint8_t)mission_of(fam, ob[0]);
-  }
-  if (active) {
-    a.st.x[e] = x;
-    a.st.y[e] = y;
-    a.st.dir[e] = dir;
-    a.st.t[e] = t;
-    a.st.carry[e] = (int32_t)carry;
-    a.st.episode[e] = episode;
-    a.st.done_prev[e] = done_prev ? 1 : 0;
-    a.st.calls[e] = calls + 1u;
-    if (fam == kFamDynObs || do_reset)
-      *reinterpret_cast<uint4*>(a.st.obst + 16 * (size_t)e) = make_uint4(ob[0], ob[1], ob[2], ob[3]);
-  }
-}
-
-// ---------------------------------------------------------------------------
-// Fused kernel
+// Cells as codes
 // ---------------------------------------------------------------------------
 // One byte per cell in LDS.  Bits 0-3 hold the type, bits 4-6 the colour and
 // bit 7 is set on cells that block sight.  A door's state is in bits 7 and 0:
@@ -1774,16 +856,20 @@ __device__ __forceinline__ void transpose3(uint32_t a, uint32_t b, uint32_t c, u
 // lanes with `edge` set, for the rare step whose view can leave the grid,
 // through a door on the outer ring that the step itself opened (GoToDoor
 // rooms use the grid's border as walls).
+//
+// view_from_rows: the same from the rows' codes, row r's cells 0-3 and 4-6 in
+// lo[r] and hi[r], rows in the order described above, bytes ascending.
+// patch: ~0 where the cell ahead of the agent shows `front` instead.
+__device__ __forceinline__ void view_from_rows(uint32_t (&lo)[7], uint32_t (&hi)[7], int S, int x, int y, int dir,
+                                               uint32_t carry_code, uint32_t patch, uint32_t front,
+                                               const uint2* masks, bool check, bool edge, uint32_t (&f)[13]);
+
 __device__ __forceinline__ void view_codes(const uint8_t* lds, int at, int S, int x, int y, int dir,
                                            uint32_t carry_code, const uint2* masks, bool check, bool edge,
                                            uint32_t (&f)[13]) {
   const bool vert = (dir & 1) != 0;            // south, north
-  const bool back = dir == 1 || dir == 2;      // rows loaded bottom up
-  const bool flip = dir < 2;                   // rows read backwards
-  const int step = back ? -S : S;
+  const int step = (dir == 1 || dir == 2) ? -S : S;   // south, west: rows loaded bottom up
   int idx = at - (vert ? 3 : (dir == 0 ? 0 : 6)) - (vert ? 6 : 3) * step;
-  const uint32_t sel_lo = flip ? 0x03040506u : 0x03020100u;
-  const uint32_t sel_hi = flip ? 0x0C000102u : 0x0C060504u;
   uint32_t lo[kView], hi[kView], raw[kView][3];
   int at_row = idx;
 #pragma unroll
@@ -1797,11 +883,25 @@ __device__ __forceinline__ void view_codes(const uint8_t* lds, int at, int S, in
 #pragma unroll
   for (int r = 0; r < kView; ++r) {
     const uint32_t sh = (uint32_t)idx & 3u;
-    const uint32_t l = __builtin_amdgcn_alignbyte(raw[r][1], raw[r][0], sh);
-    const uint32_t h = __builtin_amdgcn_alignbyte(raw[r][2], raw[r][1], sh);
+    lo[r] = __builtin_amdgcn_alignbyte(raw[r][1], raw[r][0], sh);
+    hi[r] = __builtin_amdgcn_alignbyte(raw[r][2], raw[r][1], sh);
+    idx += step;
+  }
+  view_from_rows(lo, hi, S, x, y, dir, carry_code, 0u, 0u, masks, check, edge, f);
+}
+
+__device__ __forceinline__ void view_from_rows(uint32_t (&lo)[7], uint32_t (&hi)[7], int S, int x, int y, int dir,
+                                               uint32_t carry_code, uint32_t patch, uint32_t front,
+                                               const uint2* masks, bool check, bool edge, uint32_t (&f)[13]) {
+  const bool vert = (dir & 1) != 0;
+  const bool flip = dir < 2;                   // south, east: the view runs backwards along a row
+  const uint32_t sel_lo = flip ? 0x03040506u : 0x03020100u;
+  const uint32_t sel_hi = flip ? 0x0C000102u : 0x0C060504u;
+#pragma unroll
+  for (int r = 0; r < kView; ++r) {
+    const uint32_t l = lo[r], h = hi[r];
     lo[r] = perm(h, l, sel_lo);
     hi[r] = perm(h, l, sel_hi);
-    idx += step;
   }
   {
     uint32_t a[4], b[4], c[4], d[4];
@@ -1815,6 +915,7 @@ __device__ __forceinline__ void view_codes(const uint8_t* lds, int at, int S, in
       hi[r] = vert ? hi[r] : (r < 4 ? c[r & 3] : d[r & 3]);
     }
   }
+  lo[5] = (lo[5] & ~(patch & 0xFF000000u)) | (patch & (front << 24));
   if (check) {
     const int e = S - 1 - x, s = S - 1 - y;   // cells to the east and south
     const int ahead = dir == 0 ? e : (dir == 1 ? s : (dir == 2 ? x : y));
@@ -2377,6 +1478,267 @@ constexpr int kViewStageBytes = kStageMargin + kWave * kCatBytes + 32;
 constexpr int kMarkWords = ((kWave * 32 * 32 + 63 + 63) / 64 + 31) / 32;
 static_assert(kDrawBytes <= kViewStageBytes && kMarkWords * 4 <= kViewStageBytes, "the stage holds each of its uses");
 
+__device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
+  int incl = v;
+#pragma unroll
+  for (int o = 1; o < kWave; o <<= 1) {
+    const int n = __shfl_up(incl, o, kWave);
+    if (lane >= o) incl += n;
+  }
+  total = bcast(incl, kWave - 1);
+  return incl - v;
+}
+
+// ---------------------------------------------------------------------------
+// Plain kernel: one step of every env per launch, state and grids in HBM, the
+// first-person record modes (or none) of families without moving balls; the
+// other steps run k_fused for one step, which stages whole grids.
+//
+// The view is read as soon as the action is known, before it is applied: a
+// step ends in one of at most two 7x7 squares (a turn: the new heading's;
+// forward: the current one or the one a cell ahead; anything else, and a
+// reset: the current one), whose union is the final heading's square extended
+// by one cell along it, 8 grid rows of 8 cells at most, and holds the cell
+// ahead as well.  So the cell ahead and the view come in one round trip to
+// HBM.  A row is 24 bytes at any alignment, converted to eight codes; from
+// there on the step is k_fused's.  Rows outside the grid are read as its first
+// or last row: no cell outside the grid is visible (see kMargin).
+//
+// Bound by HBM: the grids' lines that the views touch (2.9 of 128 bytes each
+// on the mixed batch), the state and the records, 145 MB a launch for 262 144
+// mixed envs; with few envs by its chain of two round trips and one wave's
+// instructions, so small batches run in small tiles (launch_tile_envs).
+// ---------------------------------------------------------------------------
+typedef uint32_t u32x2_any __attribute__((ext_vector_type(2), aligned(1)));
+
+// Codes of eight rows of eight cells: row q starts at cell (x0, y0 + q step),
+// y clamped to the grid.  first / last: the env's grid is the first / last of
+// the buffer, whose bytes beyond are not to be read: such rows are read from
+// the buffer's edge and shifted into place by whole cells.
+__device__ __forceinline__ void load_rows(const uint8_t* g, int S, int x0, int y0, int step, bool first, bool last,
+                                          uint32_t (&lo)[8], uint32_t (&hi)[8]) {
+  const int least = first ? 0 : -21, most = last ? 3 * S * S - 24 : 3 * S * S;
+  x0 = min(max(x0, -7), S - 1);
+  u32x4 w4[8];
+  u32x2_any w2[8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    const int y = min(max(y0 + q * step, 0), S - 1);
+    const uint8_t* p = g + min(max(3 * (y * S + x0), least), most);
+    w4[q] = *reinterpret_cast<const u32x4_any*>(p);
+    w2[q] = *reinterpret_cast<const u32x2_any*>(p + 16);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) {
+    lo[q] = encode_cells(w4[q].x, w4[q].y, w4[q].z);
+    hi[q] = encode_cells(w4[q].w, w2[q].x, w2[q].y);
+  }
+  if (__ballot(first || last)) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int o = 3 * (min(max(y0 + q * step, 0), S - 1) * S + x0);
+      const int cells = (min(max(o, least), most) - o) / 3;   // -8 .. 7
+      const uint64_t v = (uint64_t)lo[q] | ((uint64_t)hi[q] << 32);
+      const uint64_t s = cells >= 0 ? v << (8 * cells) : (cells > -8 ? v >> (-8 * cells) : 0ull);
+      lo[q] = (uint32_t)s;
+      hi[q] = (uint32_t)(s >> 32);
+    }
+  }
+}
+
+__device__ __forceinline__ void store_code(uint8_t* p, uint32_t code) {
+  const Cells4 c = decode_cells<false>(code);
+  p[0] = (uint8_t)c.type;
+  p[1] = (uint8_t)c.colour;
+  p[2] = (uint8_t)c.state;
+}
+
+// Lays out the grids of the lanes in `pending` (a lane's grid at g in HBM) by
+// way of `buf`, as many at a time as it holds.
+constexpr int kNewGridBytes = 4096;   // at least one grid of side 32
+
+__device__ __forceinline__ void write_new_grids(uint64_t pending, const Next& n, uint32_t meta, uint8_t* g,
+                                                uint8_t* buf, int lane) {
+  const int S = (int)((meta >> 8) & 255u), cells = S * S;
+  while (pending) {
+    const bool mine = (pending >> lane) & 1u;
+    int total;
+    const int off = wave_excl_scan(mine ? (cells + 3) & ~3 : 0, lane, total);
+    const uint64_t now = __ballot(mine && off + cells <= kNewGridBytes);
+    fill_grids(now, false, n, meta, buf, off, lane);
+    wave_sync();
+    for (uint64_t todo = now; todo; todo &= todo - 1) {
+      const int r = __ffsll((unsigned long long)todo) - 1;
+      uint8_t* dst = reinterpret_cast<uint8_t*>(bcast64(reinterpret_cast<uint64_t>(g), r));
+      const uint8_t* src = buf + bcast(off, r);
+      const int c = bcast(cells, r);
+      for (int p = 0; p < c; p += 4 * kWave) emit_some<false, false, false>(dst, src, c, p, 0u, lane);
+      if (c & 3) emit_ends<false, false>(dst, src, c, 0, c & 3, lane);
+    }
+    wave_sync();
+    pending &= ~now;
+  }
+}
+
+struct PlainArgs {
+  EnvTables env;
+  StateBufs st;
+  const uint8_t* actions;
+  TrajBufs out;
+  int32_t row;
+  int32_t tile_envs;   // envs per workgroup
+};
+
+// kObs: 0 symbolic, 1 categorical first person, 2 no observations
+template <int kObs>
+__global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
+  __shared__ __align__(16) uint2 masks[kObs == 2 ? 1 : kMaskEntries];
+  __shared__ __align__(16) uint32_t stage_words[kViewStageBytes / 4];   // and the draw window, before
+  __shared__ __align__(16) uint8_t new_grids[kNewGridBytes + 16];
+  const int lane = threadIdx.x;
+  const int N = a.env.n;
+  const int e0 = (int)blockIdx.x * a.tile_envs, e = e0 + lane;
+  const int n_here = min(a.tile_envs, N - e0);
+  const bool active = lane < n_here;
+
+  // a lane without an env reads the first bytes of the buffer (48 at least)
+  uint32_t fam = 0, meta = 0;
+  int S = 4, T = 1, x = 1, y = 1, dir = 0, t = 0;
+  uint32_t carry = kCellEmpty, episode = 0, rid = 0, calls = 0, act = 6u;
+  bool done_prev = false;
+  uint2 seed = make_uint2(0, 0);
+  uint8_t* g = a.st.grid;
+  uint32_t ob[4] = {~0u, ~0u, ~0u, ~0u};
+  if (active) {
+    meta = a.env.meta[e];
+    T = a.env.max_steps[e];
+    seed = a.env.seed[e];
+    rid = a.env.rng_id[e];
+    g = a.st.grid + a.env.grid_off[e];
+    x = a.st.x[e];
+    y = a.st.y[e];
+    dir = a.st.dir[e];
+    t = a.st.t[e];
+    carry = (uint32_t)a.st.carry[e];
+    episode = a.st.episode[e];
+    done_prev = a.st.done_prev[e] != 0;
+    calls = a.st.calls[e];
+    if (a.actions) act = a.actions[e];
+    fam = meta & 0xFF;
+    S = (int)((meta >> 8) & 0xFF);
+    if (fam == kFamGoToDoor) ob[0] = *reinterpret_cast<const uint32_t*>(a.st.obst + 16 * (size_t)e);   // the mission
+  }
+  if (kObs != 2) build_mask_table(masks, lane);
+  const bool do_reset = active && done_prev;
+  const uint64_t pending = __ballot(do_reset);
+  uint32_t carry_code = code_of(carry);
+  bool carry_changed = do_reset;
+  if (pending) {
+    Next next{};
+    bool have = false;
+    draw_missing(next, have, do_reset, do_reset, meta, seed, rid, episode + 1u, stage_words + lane);
+    if (do_reset) {
+      episode += 1u;
+      start_episode(next, fam, x, y, dir, ob);
+      t = 0;
+      carry_code = kCodeEmpty;
+    }
+    write_new_grids(pending, next, meta, g, new_grids, lane);
+    __threadfence_block();
+    __syncthreads();
+  }
+  const bool live = active && !do_reset;
+  if (!a.actions) act = bounded(pick4(policy_block(seed, rid, calls), calls & 3u), 7u);
+  act = live ? act : 6u;
+  const uint32_t a6 = min(act, 6u);
+
+  // the cell ahead, and the rows of the view
+  const int dir_f = (dir + (int)((7u >> (2u * a6)) & 3u)) & 3;   // left 3, right 1
+  const uint32_t dir2 = 2u * (uint32_t)dir;
+  const int dx = (int)((0x46u >> dir2) & 3u) - 1, dy = (int)((0x19u >> dir2) & 3u) - 1;
+  const bool vert = (dir_f & 1) != 0;
+  uint32_t rlo[8], rhi[8], front;
+  if (kObs != 2) {
+    const bool back = dir_f == 1 || dir_f == 2;   // rows bottom up
+    load_rows(g, S, x - (vert ? 3 : (dir_f == 0 ? 0 : 7)), back ? y + (vert ? 7 : 3) : y - (vert ? 7 : 3),
+              back ? -1 : 1, e == 0 || !active, e == N - 1 || !active, rlo, rhi);
+    front = vert ? rlo[6] >> 24 : ((dir_f == 0 ? rlo[3] >> 8 : rhi[3] >> 16) & 255u);
+  } else {
+    const uint8_t* p = g + 3 * (min(max(y + dy, 0), S - 1) * S + min(max(x + dx, 0), S - 1));
+    front = code_of((uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16));
+  }
+
+  const CodeAction r = act_on_code(a6, carry_code, front);
+  dir = dir_f;
+  const uint32_t walked = a6 == kForward ? r.ok : 0u;
+  const int ahead = (y + dy) * S + x + dx;
+  x += (int)(walked & (uint32_t)dx);
+  y += (int)(walked & (uint32_t)dy);
+  uint32_t goal = r.goal, ended = goal | r.lava;
+  const uint32_t patch = a6 > kForward ? r.ok : 0u;   // a pickup, drop or toggle changed the cell ahead
+  bool edge_view = false;
+  if (fam == kFamGoToDoor && live) {
+    // on_door_done of Tables "rewards" and "terminations": the done action
+    // (any value >= 6) with the mission's door directly ahead achieves the
+    // task; toggling ends the episode with reward 0
+    const bool done_at = act >= 6u && is_door_code(front) && ((front >> 4) & 7u) == (ob[0] & 0xFFu);
+    goal |= done_at ? 1u : 0u;
+    ended |= (done_at || act == kToggle) ? 1u : 0u;
+    edge_view = patch != 0u;   // a door toggled, possibly on the outer ring
+  }
+  if (patch) {
+    store_code(g + 3 * ahead, r.new_front);
+    const bool held = a6 != kToggle;
+    carry_code = held ? (a6 == kPickup ? front : kCodeEmpty) : carry_code;
+    carry_changed = carry_changed || held;
+  }
+  t += live ? 1 : 0;
+  const uint32_t trunc = (live && t >= T) ? 1u : 0u;
+  float reward = 0.0f;
+  if (__ballot(ended != 0u)) reward = r.lava ? -1.0f : (goal ? goal_reward(t, T, a.env.reward_mode) : 0.0f);
+  const uint32_t flags = do_reset ? kFlagFirst : ended * kFlagTerminated | trunc * kFlagTruncated;
+  const size_t row0 = (size_t)a.row * (size_t)N + (size_t)e0;
+
+  if (kObs != 2) {
+    // the final square among the rows read: one row or one column of the eight
+    // falls away
+    const bool down = vert && !walked;
+    const uint32_t right = (!vert && (dir == 0) == (walked != 0u)) ? 1u : 0u;
+    uint32_t lo[kView], hi[kView], f[13];
+#pragma unroll
+    for (int q = 0; q < kView; ++q) {
+      const uint32_t l = down ? rlo[q + 1] : rlo[q], h = down ? rhi[q + 1] : rhi[q];
+      lo[q] = __builtin_amdgcn_alignbyte(h, l, right);
+      hi[q] = __builtin_amdgcn_alignbyte(0u, h, right);
+    }
+    view_from_rows(lo, hi, S, x, y, dir, carry_code, patch, r.new_front, masks, __ballot(edge_view) != 0, edge_view,
+                   f);
+    uint32_t* const stage = stage_words + kStageMargin / 4;
+    store_view(stage, f, lane, n_here);
+    wave_sync();
+    const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
+    if (kObs == 1) emit_types(a.out.obs + row0 * kCatBytes, cells, n_here * kCatBytes, lane);
+    else emit_triples<false>(a.out.obs + row0 * kObsBytes, cells, n_here * kCatBytes, lane);
+  }
+  if (active) {
+    a.out.reward[row0 + lane] = reward;
+    a.out.flags[row0 + lane] = (uint8_t)flags;
+    a.out.action[row0 + lane] = (uint8_t)(live ? act : kActionNone);
+    if (a.out.mission) a.out.mission[row0 + lane] = (uint8_t)mission_of(fam, ob[0]);
+    a.st.x[e] = x;
+    a.st.y[e] = y;
+    a.st.dir[e] = dir;
+    a.st.t[e] = t;
+    if (carry_changed) a.st.carry[e] = (int32_t)carry_triple(carry_code);
+    a.st.episode[e] = episode;
+    a.st.done_prev[e] = (ended | trunc) != 0u ? 1 : 0;
+    a.st.calls[e] = calls + 1u;
+    if (do_reset)
+      *reinterpret_cast<uint4*>(a.st.obst + 16 * (size_t)e) = make_uint4(ob[0], ob[1], ob[2], ob[3]);
+  }
+}
+
 struct FusedArgs {
   EnvTables env;
   TileTables tiles;
@@ -2389,17 +1751,6 @@ struct FusedArgs {
   const ServeTile* host_tiles;    // serving: staging of newly admitted tiles (pinned host memory)
   const SlotConfig* host_slots;   // serving: their slot configurations
 };
-
-__device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
-  int incl = v;
-#pragma unroll
-  for (int o = 1; o < kWave; o <<= 1) {
-    const int n = __shfl_up(incl, o, kWave);
-    if (lane >= o) incl += n;
-  }
-  total = bcast(incl, kWave - 1);
-  return incl - v;
-}
 
 // What bounds a step: with few tiles (up to one wave per SIMD, 65 536 envs)
 // one wave's own instruction stream, 5 cycles per independent vector
@@ -2577,7 +1928,10 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       const bool do_reset = active && done_prev;
       const uint64_t pending = __ballot(do_reset);
       if (pending) {
-        draw_missing(next, have_next, do_reset, active, meta, seed, rid, episode + 1u, stage_words + lane);
+        // in the launch's last step only for the lanes that reset: nothing is
+        // kept for the next launch
+        draw_missing(next, have_next, do_reset, s + 1 < steps ? active : do_reset, meta, seed, rid, episode + 1u,
+                     stage_words + lane);
         const bool kept = filled && keeps_base(fam);
         if (any_balls && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
           const uint32_t balls = (opaque(meta) >> 16) & 255u;
@@ -2632,7 +1986,7 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       penalty |= r.lava;
       uint32_t goal = r.goal, ended = goal | penalty;
       if (any_missions && fam == kFamGoToDoor && live) {
-        // (see gotodoor_rules)
+        // as in k_plain
         const bool done_at = act >= 6u && is_door_code(front) && ((front >> 4) & 7u) == (ob[0] & 0xFFu);
         goal |= done_at ? 1u : 0u;
         ended |= (done_at || act == kToggle) ? 1u : 0u;
@@ -2809,9 +2163,12 @@ size_t fused_lds_bytes(int32_t max_tile_cells) {
 
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
                         const TrajBufs& out, int32_t row, hipStream_t stream) {
-  PlainArgs a{env, st, actions, out, row};
-  const int blocks = (env.n + kWave - 1) / kWave;
-  hipLaunchKernelGGL(k_plain, dim3(blocks), dim3(kWave), 0, stream, a);
+  using PlainKernel = void (*)(PlainArgs);
+  static const PlainKernel kernels[3] = {&k_plain<0>, &k_plain<1>, &k_plain<2>};
+  const int32_t tile_envs = launch_tile_envs(env.n);
+  const PlainArgs a{env, st, actions, out, row, tile_envs};
+  const int blocks = (env.n + tile_envs - 1) / tile_envs;
+  hipLaunchKernelGGL(kernels[out.obs ? env.obs_mode : 2], dim3(blocks), dim3(kWave), 0, stream, a);
   return hipGetLastError();
 }
 

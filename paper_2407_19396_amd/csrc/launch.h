@@ -119,8 +119,9 @@ inline bool family_ok(int family, int side, int param, int max_side) {
   }
 }
 
-// One launch of the plain kernel: one step of every env.  Writes output row
-// `row`.
+// One launch of the plain kernel: one step of every env of a batch without
+// Dynamic-Obstacles envs, records first person (obs_mode 0, 1) or none
+// (out.obs nullptr).  Writes output row `row`.
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
                         const TrajBufs& out, int32_t row, hipStream_t stream);
 

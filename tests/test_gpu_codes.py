@@ -70,3 +70,34 @@ def test_resets_all_the_time(case):
     P.assert_rows_equal(traj, ref, what="resets")
     P.assert_state_equal(env, s, "resets")
     env.close()
+
+
+@pytest.mark.parametrize("obs_mode", [0, 1])
+@pytest.mark.parametrize("n,offset", [(1, 0), (2, 3), (3, 16), (5, 33), (17, 2), (66, 1), (300, 48)])
+def test_steps_at_any_alignment(n, offset, obs_mode):
+    """The plain kernel: the first and the last grid of the buffer in every
+    batch, resets on many steps, doors toggled often."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    table = wl.families_table(4 * n + 40, seed=n, mix_seed=3 * n + offset)
+    table = table.subset(np.flatnonzero(table.family != wl.FAMILY_DYNOBS)[:n])
+    table.max_steps[:] = np.random.default_rng(n).integers(2, 30, n)
+    steps = 40
+    acts = np.random.default_rng(n + 1).choice(np.array([0, 1, 2, 2, 2, 3, 4, 5, 5, 6, 200], np.uint8), (steps, n))
+    b, s, _ = P.oracle_reset(table, 0, obs_mode)
+    ref = ox.rollout(b, s, steps, acts)
+    env = ge.GridEnv(table, obs_mode=obs_mode)
+    env.reset()
+    traj = env.traj(steps)
+    raw = torch.full((traj.obs.numel() + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+    at = 64 + offset - raw.data_ptr() % 64
+    shape, size = traj.obs.shape, traj.obs.numel()
+    traj.obs = raw[at:at + size].view(shape)
+    dacts = torch.from_numpy(acts).cuda()
+    for k in range(steps):
+        env.step(traj.row(k), dacts[k])
+    torch.cuda.synchronize()
+    P.assert_rows_equal(traj, ref, what=f"{n} envs at byte {offset}, mode {obs_mode}")
+    P.assert_state_equal(env, s, f"{n} envs at byte {offset}, mode {obs_mode}")
+    assert bool((raw[:at] == 0xA5).all()) and bool((raw[at + size:] == 0xA5).all())
+    env.close()
