@@ -571,6 +571,14 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The barrier of a workgroup of two waves that share LDS only: outstanding
+// loads and stores of device memory are not waited for.
+__device__ __forceinline__ void pair_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr uint32_t kAgent = 10;
@@ -864,9 +872,10 @@ __device__ __forceinline__ void view_from_rows(uint32_t (&lo)[7], uint32_t (&hi)
                                                uint32_t carry_code, uint32_t patch, uint32_t front,
                                                const uint2* masks, bool check, bool edge, uint32_t (&f)[13]);
 
+template <class Loaded>
 __device__ __forceinline__ void view_codes(const uint8_t* lds, int at, int S, int x, int y, int dir,
                                            uint32_t carry_code, const uint2* masks, bool check, bool edge,
-                                           uint32_t (&f)[13]) {
+                                           uint32_t (&f)[13], Loaded loaded) {
   const bool vert = (dir & 1) != 0;            // south, north
   const int step = (dir == 1 || dir == 2) ? -S : S;   // south, west: rows loaded bottom up
   int idx = at - (vert ? 3 : (dir == 0 ? 0 : 6)) - (vert ? 6 : 3) * step;
@@ -880,6 +889,7 @@ __device__ __forceinline__ void view_codes(const uint8_t* lds, int at, int S, in
     at_row += step;
   }
   __builtin_amdgcn_sched_barrier(0);   // all reads in flight before the first is used
+  loaded();
 #pragma unroll
   for (int r = 0; r < kView; ++r) {
     const uint32_t sh = (uint32_t)idx & 3u;
@@ -1768,12 +1778,25 @@ struct FusedArgs {
 // kObs: the observation records written, 0 symbolic first person, 1
 // categorical first person, 2 whole grid (a.env.obs_mode 2 or 3); each
 // variant carries only its own record code.
+// kSplit: a workgroup of two waves.  The second takes the steps (policy,
+// actions, resets, balls, the step's scalars), the first writes the records:
+// it is handed each lane's pose in LDS, reads the views' rows out of the
+// grids, lets the second go on, and computes and stores the records meanwhile.  Two barriers a step, one after the step is taken and one
+// after the rows are read; both waves pass each `steps` times per tile.  Only
+// LDS is shared, so neither wave waits for device memory at them.  Which wave
+// is the longer one changes from step to step: the renderer runs at priority
+// 1, the other at 0, and at 2 while layouts are drawn and filled or balls
+// move.  65 536 TwoRoom 8x8 envs:
+// 2.45 -> 1.92 us a step, 5.3 TB/s of records; 4096 Empty
+// 8x8 1.61 -> 1.16, 30 011 envs of all families 6.4 -> 4.95, 65 536
+// Dynamic-Obstacles envs as type ids 5.7 -> 4.6.  Without the priorities
+// 2.0 / 1.24 / 5.3 / 4.95.
 // On this GPU one counter tracks both outstanding loads and stores, so a
 // load consumed in the same step would also wait for every earlier record
 // store: the action of step s + 1 is therefore fetched during step s, and
 // the policy variant has no loads in its step loop at all.
-template <bool kActions, bool kServe, int kObs>
-__global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
+template <bool kActions, bool kServe, int kObs, bool kSplit>
+__global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs a) {
   // first-person variants: the byte masks of a row's visibility bits.  The
   // stage holds, one after another, the words of layouts being drawn, the
   // wave's views, and after the last step the bitmap of emit_dirty_grids.
@@ -1782,15 +1805,21 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
   __shared__ __align__(16) uint32_t kth_cell[kMaskPatterns];
   // per lane: whether a pickup, drop or toggle changed a cell of its grid
   __shared__ uint8_t cell_changed[kWave];
+  // kSplit: the renderer's own stage, and the poses it is handed (x: the agent's
+  // byte of LDS, heading << 18, toggled << 20; y: x, y, side, carried code)
+  __shared__ __align__(16) uint32_t view_words[kSplit ? kViewStageBytes / 4 : 1];
+  __shared__ uint2 poses[kSplit ? kWave : 1];
   extern __shared__ __align__(16) uint8_t grids[];
   uint8_t* codes = grids + kMargin;
-  const int lane = threadIdx.x;
+  const int lane = kSplit ? threadIdx.x & (kWave - 1) : threadIdx.x;
+  const bool renders = kSplit && __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) == 0;
   const int N = a.env.n;
+  if (renders) __builtin_amdgcn_s_setprio(1);
 
   // a view's first cell lies kStageMargin bytes in (emit_* read a little
   // before and past their cells)
-  uint32_t* const stage = stage_words + kStageMargin / 4;
-  if (kObs != 2) {
+  uint32_t* const stage = (kSplit ? view_words : stage_words) + kStageMargin / 4;
+  if (kObs != 2 && (!kSplit || renders)) {
     build_mask_table(masks, lane);
     wave_sync();
   }
@@ -1816,7 +1845,7 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     size_t rec_stride;
     if (kServe) {
       const ServeTile d = fresh ? a.host_tiles[tile] : a.serve[tile];
-      if (fresh && part == 0 && lane == 0) a.serve[tile] = d;   // the device copy later launches read
+      if (fresh && part == 0 && lane == 0 && !renders) a.serve[tile] = d;   // the device copy later launches read
       step0 = entry.y;
       n_here = min(tile_envs, (int)d.n_envs - first);
       if (!d.active || step0 >= d.n_steps || n_here <= 0) continue;
@@ -1840,6 +1869,36 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       o_action = a.out.action + e0;
       o_mission = a.out.mission ? a.out.mission + e0 : nullptr;
       rec_stride = (size_t)N;
+    }
+    // the lanes' views f as the first-person records from index rec on
+    const auto write_views = [&](const uint32_t (&f)[13], size_t rec) {
+      store_view(stage, f, lane, n_here);
+      wave_sync();
+      const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
+      if (kObs == 1) emit_types(o_obs + rec * kCatBytes, cells, n_here * kCatBytes, lane);
+      else emit_triples<false>(o_obs + rec * kObsBytes, cells, n_here * kCatBytes, lane);
+    };
+    int ring_row = kServe ? 0 : a.row0;   // output row of the next step
+    if (renders) {
+      for (int s = 0; s < steps; ++s) {
+        const size_t row = kServe ? (size_t)(step0 + s) : (size_t)ring_row;
+        if (!kServe) ring_row = ring_row + 1 == a.out.rows ? 0 : ring_row + 1;
+        pair_barrier();   // the step is taken
+        if (o_obs) {
+          const uint2 p = poses[lane];
+          const bool edge_view = ((p.x >> 20) & 1u) != 0u;
+          uint32_t f[13];
+          view_codes(grids, (int)(p.x & 0x3FFFFu), (int)((p.y >> 16) & 255u), (int)(p.y & 255u),
+                     (int)((p.y >> 8) & 255u), (int)((p.x >> 18) & 3u), p.y >> 24, masks, __ballot(edge_view) != 0,
+                     edge_view, f, [] { pair_barrier(); });   // the rows are read: grids may change
+          __builtin_amdgcn_sched_barrier(0);
+          write_views(f, row * rec_stride);
+          wave_sync();
+        } else {
+          pair_barrier();
+        }
+      }
+      continue;
     }
     const int e = e0 + lane;
     const bool active = lane < n_here;
@@ -1912,7 +1971,6 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
     uint4 pol = make_uint4(0, 0, 0, 0);
     uint32_t act_next = 0;
     if (kActions && active) act_next = a.actions[e];
-    int ring_row = kServe ? 0 : a.row0;   // output row of the next step
     for (int s = 0; s < steps; ++s) {
       // the env's call count; envs stepped together share it, so the policy
       // block refresh every 4 calls is uniform across the wave in practice
@@ -1925,8 +1983,10 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
         pol = policy_block(opaque(seed), rid, call);
       }
 
+      if (kSplit && s > 0) pair_barrier();   // the rows of step s - 1 are read
       const bool do_reset = active && done_prev;
       const uint64_t pending = __ballot(do_reset);
+      if (kSplit && (pending || any_balls)) __builtin_amdgcn_s_setprio(2);
       if (pending) {
         // in the launch's last step only for the lanes that reset: nothing is
         // kept for the next launch
@@ -2027,16 +2087,19 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
         if (active) *at = under;
       } else if (kObs != 2 && o_obs) {
         // inactive lanes (S = 0, pose (1, 1)) read inside the guard margin
-        uint32_t f[13];
-        view_codes(grids, kMargin + my_off + pos, S, x, y, dir, carry_code, masks,
-                   __ballot(edge_view) != 0, edge_view, f);
-        __builtin_amdgcn_sched_barrier(0);   // no step of the view is put off into the stores
-        store_view(stage, f, lane, n_here);
-        wave_sync();
-        const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
-        if (kObs == 1) emit_types(o_obs + rec * kCatBytes, cells, n_here * kCatBytes, lane);
-        else emit_triples<false>(o_obs + rec * kObsBytes, cells, n_here * kCatBytes, lane);
+        const int at = kMargin + my_off + pos;
+        if (kSplit) {
+          poses[lane] = make_uint2((uint32_t)at | ((uint32_t)dir << 18) | (edge_view ? 1u << 20 : 0u),
+                                   (uint32_t)x | ((uint32_t)y << 8) | ((uint32_t)S << 16) | (carry_code << 24));
+        } else {
+          uint32_t f[13];
+          view_codes(grids, at, S, x, y, dir, carry_code, masks, __ballot(edge_view) != 0, edge_view, f, [] {});
+          __builtin_amdgcn_sched_barrier(0);   // no step of the view is put off into the stores
+          write_views(f, rec);
+        }
       }
+      if (kSplit) pair_barrier();   // grids and poses are step s's
+      if (kSplit) __builtin_amdgcn_s_setprio(0);
       if (active) {
         o_reward[rec + lane] = reward;
         o_flags[rec + lane] = (uint8_t)flags;
@@ -2045,6 +2108,8 @@ __global__ __launch_bounds__(kWave) void k_fused(FusedArgs a) {
       }
       wave_sync();
     }
+
+    if (kSplit && steps > 0) pair_barrier();   // the rows of the last step are read
 
     // write the chunk's final state back: the grids that changed (laid out
     // afresh, by a reset (the episode counter moved on from the one still
@@ -2125,7 +2190,7 @@ __global__ __launch_bounds__(kWave) void k_reset(FusedArgs a) {
     wave_sync();
   } else if (a.out.obs && kObs != 2) {
     uint32_t f[13];
-    view_codes(grids, kMargin + my_off + y * S + x, S, x, y, dir, kCodeEmpty, masks, false, false, f);
+    view_codes(grids, kMargin + my_off + y * S + x, S, x, y, dir, kCodeEmpty, masks, false, false, f, [] {});
     store_view(stage, f, lane, n_here);
     wave_sync();
     const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
@@ -2176,14 +2241,24 @@ namespace {
 
 using FusedKernel = void (*)(FusedArgs);
 
-hipError_t launch_tiles(FusedKernel fn, const FusedArgs& a, int32_t blocks, hipStream_t stream) {
+// Launches of up to this many workgroups run in pairs of waves (k_fused,
+// kSplit): one pair per SIMD at most.  With more workgroups a SIMD has its two
+// waves without pairs, and a pair's second wave would only take their place:
+// 262 144 mixed envs (4096 workgroups), 20 steps 190 us, in pairs 250; 90 000
+// (1407) 167 against 204; 131 072 TwoRoom 8x8 envs (2048) 275 against 302.
+constexpr int kSplitBlocks = 1024;
+// LDS that the pair needs besides: the renderer's stage and the poses
+constexpr size_t kSplitLds = kViewStageBytes + kWave * sizeof(uint2);
+
+
+hipError_t launch_tiles(FusedKernel fn, const FusedArgs& a, int32_t blocks, int32_t threads, hipStream_t stream) {
   const size_t lds = fused_dynamic_lds_bytes(a.tiles.max_tile_cells);
   if (lds > 65536) {
     const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(fn),
                                              hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(fn, dim3(blocks), dim3(kWave), lds, stream, a);
+  hipLaunchKernelGGL(fn, dim3(blocks), dim3(threads), lds, stream, a);
   return hipGetLastError();
 }
 
@@ -2198,16 +2273,22 @@ hipError_t launch_fused(const EnvTables& env, const TileTables& tiles, const Sta
   // serving requests record symbolic first-person observations
   const int obs = serve ? 0 : (env.obs_mode >= 2 ? 2 : env.obs_mode);
   static const FusedKernel kernels[2][3] = {
-      {&k_fused<false, false, 0>, &k_fused<false, false, 1>, &k_fused<false, false, 2>},
-      {&k_fused<true, false, 0>, &k_fused<true, false, 1>, &k_fused<true, false, 2>}};
-  return launch_tiles(serve ? &k_fused<false, true, 0> : kernels[actions ? 1 : 0][obs], a, grid_blocks, stream);
+      {&k_fused<false, false, 0, false>, &k_fused<false, false, 1, false>, &k_fused<false, false, 2, false>},
+      {&k_fused<true, false, 0, false>, &k_fused<true, false, 1, false>, &k_fused<true, false, 2, false>}};
+  static const FusedKernel split[2][2] = {{&k_fused<false, false, 0, true>, &k_fused<false, false, 1, true>},
+                                          {&k_fused<true, false, 0, true>, &k_fused<true, false, 1, true>}};
+  const int with = actions ? 1 : 0;
+  if (grid_blocks <= kSplitBlocks && obs < 2 && (serve || out.obs) &&
+      fused_lds_bytes(tiles.max_tile_cells) + kSplitLds <= 160 * 1024)
+    return launch_tiles(serve ? &k_fused<false, true, 0, true> : split[with][obs], a, grid_blocks, 2 * kWave, stream);
+  return launch_tiles(serve ? &k_fused<false, true, 0, false> : kernels[with][obs], a, grid_blocks, kWave, stream);
 }
 
 hipError_t launch_reset(const EnvTables& env, const TileTables& tiles, const StateBufs& st, const TrajBufs& out,
                         hipStream_t stream) {
   const FusedArgs a{env, tiles, st, nullptr, 0, out, 0, nullptr, nullptr, nullptr};
   static const FusedKernel kernels[3] = {&k_reset<0>, &k_reset<1>, &k_reset<2>};
-  return launch_tiles(kernels[env.obs_mode >= 2 ? 2 : env.obs_mode], a, tiles.n_tiles, stream);
+  return launch_tiles(kernels[env.obs_mode >= 2 ? 2 : env.obs_mode], a, tiles.n_tiles, kWave, stream);
 }
 
 }  // namespace gx

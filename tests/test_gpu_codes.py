@@ -101,3 +101,30 @@ def test_steps_at_any_alignment(n, offset, obs_mode):
     P.assert_state_equal(env, s, f"{n} envs at byte {offset}, mode {obs_mode}")
     assert bool((raw[:at] == 0xA5).all()) and bool((raw[at + size:] == 0xA5).all())
     env.close()
+
+
+@pytest.mark.parametrize("obs_mode", [0, 1])
+@pytest.mark.parametrize("tile_envs,blocks", [(1, 1025), (1, 1024), (8, 40), (64, 17), (64, 3), (0, 0)])
+def test_waves_alone_and_in_pairs(tile_envs, blocks, obs_mode):
+    """More workgroups than run in pairs of waves, as many, and pairs that
+    take several tiles one after another; resets and toggles on most steps."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    n, steps = 1025, 14
+    table = wl.families_table(n, seed=3, mix_seed=8)
+    table.max_steps[:] = np.random.default_rng(5).integers(1, 12, n)
+    acts = np.random.default_rng(6).choice(np.array([0, 1, 2, 2, 3, 4, 5, 5, 6], np.uint8), (steps, n))
+    for actions in (None, acts):
+        b, s, _ = P.oracle_reset(table, 0, obs_mode)
+        ref = ox.rollout(b, s, steps, actions, nthreads=8)
+        env = ge.GridEnv(table, obs_mode=obs_mode)
+        if tile_envs:
+            env.set_tiling(tile_envs)
+            env.set_launch(6, blocks)
+        env.reset()
+        traj = env.traj(steps)
+        env.rollout(steps, traj, None if actions is None else torch.from_numpy(actions).cuda(), K=6)
+        torch.cuda.synchronize()
+        P.assert_rows_equal(traj, ref, what=f"{blocks} workgroups, mode {obs_mode}")
+        P.assert_state_equal(env, s, f"{blocks} workgroups, mode {obs_mode}")
+        env.close()
