@@ -857,6 +857,36 @@ __device__ __forceinline__ void transpose3(uint32_t a, uint32_t b, uint32_t c, u
   t[3] = perm(c, ab1, 0x0C070302u);
 }
 
+// See-through cells of a row (codes 0-3 and 4-6), dual form.
+__device__ __forceinline__ uint32_t see_through(uint32_t lo, uint32_t hi) {
+  const uint32_t o = __builtin_amdgcn_udot4(lo & 0x80808080u, 0x08040201u,
+                                            __builtin_amdgcn_udot4(hi & 0x80808080u, 0x00402010u, 0u, false), false);
+  return ~(o | __builtin_bitreverse32(o)) & kDual;
+}
+
+// One row of the flood, nearest first: from the row's lit cells on through the
+// see-through ones, then to the cells around them and the next row's.  Bits
+// beside the fields may be set in both results.
+__device__ __forceinline__ uint32_t see_row(uint32_t p, uint32_t& seeds) {
+  const uint32_t g = seeds & p;
+  const uint32_t fill = (((p + g) ^ p) | g) & p;
+  const uint32_t wide = fill | (fill << 1) | (fill >> 1);
+  const uint32_t next = wide | __builtin_bitreverse32(wide);
+  const uint32_t vis = seeds | next;
+  seeds = next;
+  return vis;
+}
+
+// Columns inside the grid, for a view from (x, y), and in `ahead` its rows
+// beyond the agent's.
+__device__ __forceinline__ uint32_t columns_inside(int S, int x, int y, int dir, int& ahead) {
+  const int e = S - 1 - x, s = S - 1 - y;   // cells to the east and south
+  ahead = dir == 0 ? e : (dir == 1 ? s : (dir == 2 ? x : y));
+  const int left = dir == 0 ? y : (dir == 1 ? e : (dir == 2 ? s : x));
+  const int right = dir == 0 ? s : (dir == 1 ? x : (dir == 2 ? y : e));
+  return (0x7Fu << max(3 - left, 0)) & (0x7Fu >> max(3 - right, 0)) & 0x7Fu;
+}
+
 // The lane's view as 13 words of codes f[0..12], cell j * 7 + i (view row j,
 // column i) at byte j * 7 + i, unseen cells and the bytes past the 49th 0.
 // at: the agent's cell's byte offset in `lds` (its grid's rows are S bytes
@@ -927,12 +957,8 @@ __device__ __forceinline__ void view_from_rows(uint32_t (&lo)[7], uint32_t (&hi)
   }
   lo[5] = (lo[5] & ~(patch & 0xFF000000u)) | (patch & (front << 24));
   if (check) {
-    const int e = S - 1 - x, s = S - 1 - y;   // cells to the east and south
-    const int ahead = dir == 0 ? e : (dir == 1 ? s : (dir == 2 ? x : y));
-    const int left = dir == 0 ? y : (dir == 1 ? e : (dir == 2 ? s : x));
-    const int right = dir == 0 ? s : (dir == 1 ? x : (dir == 2 ? y : e));
-    const uint32_t cols = (0x7Fu << max(3 - left, 0)) & (0x7Fu >> max(3 - right, 0)) & 0x7Fu;
-    const uint2 m = masks[cols];
+    int ahead;
+    const uint2 m = masks[columns_inside(S, x, y, dir, ahead)];
 #pragma unroll
     for (int r = 0; r < kView; ++r) {
       const bool in = 6 - r <= ahead;
@@ -944,16 +970,7 @@ __device__ __forceinline__ void view_from_rows(uint32_t (&lo)[7], uint32_t (&hi)
   uint32_t seeds = kDualCentre;
 #pragma unroll
   for (int j = kView - 1; j >= 0; --j) {
-    const uint32_t o = __builtin_amdgcn_udot4(lo[j] & 0x80808080u, 0x08040201u,
-                                              __builtin_amdgcn_udot4(hi[j] & 0x80808080u, 0x00402010u, 0u, false),
-                                              false);
-    const uint32_t p = ~(o | __builtin_bitreverse32(o)) & kDual;   // see-through, dual form
-    const uint32_t g = seeds & p;
-    const uint32_t fill = (((p + g) ^ p) | g) & p;
-    const uint32_t run = fill | __builtin_bitreverse32(fill);
-    const uint32_t next = (run | (run << 1) | (run >> 1)) & kDual;
-    const uint32_t vis = seeds | next;
-    seeds = next;
+    const uint32_t vis = see_row(see_through(lo[j], hi[j]), seeds);
     const uint2 m = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(masks) + ((vis >> 4) & 0x3F8u));
     lo[j] &= m.x;
     hi[j] &= m.y;
@@ -972,6 +989,64 @@ __device__ __forceinline__ void view_from_rows(uint32_t (&lo)[7], uint32_t (&hi)
   f[10] = perm(lo[6], hi[5], 0x05040201u);
   f[11] = perm(hi[6], lo[6], 0x05040302u);
   f[12] = (hi[6] >> 16) & 0xFFu;
+}
+
+// The views of the first n <= 8 lanes' envs, one after another at `stage`: lane
+// 8 i + r computes row r of env i (r = 7: row 6 again, not stored).  A view of
+// its own per lane costs some 250 instructions however few lanes have one;
+// here each handles seven cells, and the flood, which needs the see-through
+// cells of all rows, receives them from the lanes of its group.
+template <class Loaded>
+__device__ __forceinline__ void views_of_few(const uint8_t* lds, uint32_t* stage, uint2 pose, int lane, int n,
+                                             const uint2* masks, bool check, Loaded loaded) {
+  const uint32_t r = min((uint32_t)lane & 7u, 6u);
+  const int S = (int)((pose.y >> 16) & 255u), dir = (int)((pose.x >> 18) & 3u);
+  const bool vert = (dir & 1) != 0;
+  const int fwd = vert ? S : 1, side = vert ? 1 : S;
+  const int ahead_by = dir >= 2 ? -fwd : fwd;                // one cell ahead
+  const int step = dir == 1 || dir == 2 ? -side : side;      // one cell to the right
+  const uint8_t* p = lds + ((int)(pose.x & 0x3FFFFu) + (6 - (int)r) * ahead_by - 3 * step);
+  uint32_t c[kView];
+#pragma unroll
+  for (int k = 0; k < kView; ++k) {
+    c[k] = *p;
+    p += step;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  loaded();
+  uint32_t lo = c[0] | (c[1] << 8) | (c[2] << 16) | (c[3] << 24), hi = c[4] | (c[5] << 8) | (c[6] << 16);
+  if (check) {
+    int ahead;
+    const uint2 m = masks[columns_inside(S, (int)(pose.y & 255u), (int)((pose.y >> 8) & 255u), dir, ahead)];
+    const bool edge = ((pose.x >> 20) & 1u) != 0u, in = 6 - (int)r <= ahead;
+    const uint32_t ml = edge ? (in ? m.x : 0u) : ~0u, mh = edge ? (in ? m.y : 0u) : ~0u;
+    lo = (lo & ml) | (kCodeWall4 & ~ml);
+    hi = (hi & mh) | (kCodeWall4 & ~mh);
+  }
+  const int see = (int)see_through(lo, hi);
+  uint32_t rows[kView];
+  rows[0] = (uint32_t)__builtin_amdgcn_ds_swizzle(see, 0x18 | 0 << 5);
+  rows[1] = (uint32_t)__builtin_amdgcn_ds_swizzle(see, 0x18 | 1 << 5);
+  rows[2] = (uint32_t)__builtin_amdgcn_ds_swizzle(see, 0x18 | 2 << 5);
+  rows[3] = (uint32_t)__builtin_amdgcn_ds_swizzle(see, 0x18 | 3 << 5);
+  rows[4] = (uint32_t)__builtin_amdgcn_ds_swizzle(see, 0x18 | 4 << 5);
+  rows[5] = (uint32_t)__builtin_amdgcn_ds_swizzle(see, 0x18 | 5 << 5);
+  rows[6] = (uint32_t)__builtin_amdgcn_ds_swizzle(see, 0x18 | 6 << 5);
+  uint32_t seeds = kDualCentre, vis = 0;
+#pragma unroll
+  for (int j = kView - 1; j >= 0; --j) {
+    const uint32_t v = see_row(rows[j], seeds);
+    vis = r == (uint32_t)j ? v : vis;
+  }
+  const uint2 m = *reinterpret_cast<const uint2*>(reinterpret_cast<const uint8_t*>(masks) + ((vis >> 4) & 0x3F8u));
+  lo &= m.x;
+  hi &= m.y;
+  lo = r == 6 ? (lo & 0x00FFFFFFu) | (pose.y & 0xFF000000u) : lo;   // the agent's cell shows what it carries
+  if ((lane & 7) < kView && (lane >> 3) < n) {
+    uint8_t* q = reinterpret_cast<uint8_t*>(stage) + kCatBytes * (lane >> 3) + kView * (lane & 7);
+#pragma unroll
+    for (int k = 0; k < kView; ++k) q[k] = (uint8_t)(k < 4 ? lo >> (8 * k) : hi >> (8 * (k - 4)));
+  }
 }
 
 // Writes the first n lanes' views (49 codes each) one after another at
@@ -1482,6 +1557,10 @@ __device__ __forceinline__ void fill_grids(uint64_t pending, bool kept, const Ne
 // the stage of a wave's views: 64 of 49 codes, and what emit_* may read
 // before and past them
 constexpr int kStageMargin = 16;
+// envs of a tile up to which the renderer computes the views together
+// (views_of_few takes 8): Empty 8x8, us a step, 4096 envs in tiles of 4 1.21 ->
+// 0.98, 8192 in tiles of 8 1.40 -> 1.22.
+constexpr int kFewEnvs = 8;
 constexpr int kViewStageBytes = kStageMargin + kWave * kCatBytes + 32;
 // words of emit_dirty_grids's bitmap: one bit per 64 cells of at most 64
 // grids of side 32, starting up to 63 cells before the first
@@ -1788,7 +1867,7 @@ struct FusedArgs {
 // 1, the other at 0, and at 2 while layouts are drawn and filled or balls
 // move.  65 536 TwoRoom 8x8 envs:
 // 2.45 -> 1.92 us a step, 5.3 TB/s of records; 4096 Empty
-// 8x8 1.61 -> 1.16, 30 011 envs of all families 6.4 -> 4.95, 65 536
+// 8x8 1.61 -> 1.16 (0.95 with views_of_few), 30 011 envs of all families 6.4 -> 4.95, 65 536
 // Dynamic-Obstacles envs as type ids 5.7 -> 4.6.  Without the priorities
 // 2.0 / 1.24 / 5.3 / 4.95.
 // On this GPU one counter tracks both outstanding loads and stores, so a
@@ -1870,9 +1949,8 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       o_mission = a.out.mission ? a.out.mission + e0 : nullptr;
       rec_stride = (size_t)N;
     }
-    // the lanes' views f as the first-person records from index rec on
-    const auto write_views = [&](const uint32_t (&f)[13], size_t rec) {
-      store_view(stage, f, lane, n_here);
+    // the staged views as the first-person records from index rec on
+    const auto write_views = [&](size_t rec) {
       wave_sync();
       const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
       if (kObs == 1) emit_types(o_obs + rec * kCatBytes, cells, n_here * kCatBytes, lane);
@@ -1885,14 +1963,22 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
         if (!kServe) ring_row = ring_row + 1 == a.out.rows ? 0 : ring_row + 1;
         pair_barrier();   // the step is taken
         if (o_obs) {
-          const uint2 p = poses[lane];
-          const bool edge_view = ((p.x >> 20) & 1u) != 0u;
-          uint32_t f[13];
-          view_codes(grids, (int)(p.x & 0x3FFFFu), (int)((p.y >> 16) & 255u), (int)(p.y & 255u),
-                     (int)((p.y >> 8) & 255u), (int)((p.x >> 18) & 3u), p.y >> 24, masks, __ballot(edge_view) != 0,
-                     edge_view, f, [] { pair_barrier(); });   // the rows are read: grids may change
-          __builtin_amdgcn_sched_barrier(0);
-          write_views(f, row * rec_stride);
+          // the rows are read: grids may change
+          const auto rows_read = [] { pair_barrier(); };
+          if (tile_envs <= kFewEnvs) {
+            const uint2 p = poses[lane >> 3];
+            views_of_few(grids, stage, p, lane, n_here, masks, __ballot((p.x >> 20) & 1u) != 0, rows_read);
+          } else {
+            const uint2 p = poses[lane];
+            const bool edge_view = ((p.x >> 20) & 1u) != 0u;
+            uint32_t f[13];
+            view_codes(grids, (int)(p.x & 0x3FFFFu), (int)((p.y >> 16) & 255u), (int)(p.y & 255u),
+                       (int)((p.y >> 8) & 255u), (int)((p.x >> 18) & 3u), p.y >> 24, masks, __ballot(edge_view) != 0,
+                       edge_view, f, rows_read);
+            __builtin_amdgcn_sched_barrier(0);
+            store_view(stage, f, lane, n_here);
+          }
+          write_views(row * rec_stride);
           wave_sync();
         } else {
           pair_barrier();
@@ -2095,7 +2181,8 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
           uint32_t f[13];
           view_codes(grids, at, S, x, y, dir, carry_code, masks, __ballot(edge_view) != 0, edge_view, f, [] {});
           __builtin_amdgcn_sched_barrier(0);   // no step of the view is put off into the stores
-          write_views(f, rec);
+          store_view(stage, f, lane, n_here);
+          write_views(rec);
         }
       }
       if (kSplit) pair_barrier();   // grids and poses are step s's

@@ -56,15 +56,16 @@ struct TileTables {
 };
 
 // Envs per tile of a launch whose caller has not chosen (env_set_tiling,
-// env_set_launch): the smallest of 4, 16, 32 that leaves at most one wave per
+// env_set_launch): the smallest of 4, 8, 16, 32 that leaves at most one tile per
 // SIMD (1024 of them), else 64.  A wave's step costs the same for one env as
 // for 64 except for its records and its resets, so spare SIMDs are best given
-// fewer envs each; beyond one wave per SIMD the waves share the vector unit.
-// Empty 8x8, us a step: 4096 envs 1.59 / 1.81 / 2.16 / 2.43 in tiles of
-// 4 / 16 / 32 / 64, 16 384 envs 3.97 / 1.88 / 2.31 / 2.45, 30 011 envs
-// 8.3 / 2.70 / 2.51 / 2.89, 65 536 envs 14.8 / 4.65 / 2.91 / 2.65.
+// fewer envs each; beyond one tile per SIMD the waves share the vector unit.
+// Empty 8x8, us a step in tiles of 4 / 8 / 16 / 32 / 64: 4096 envs 0.98 / 1.19 /
+// 1.34 / 1.64 / 1.84, 8192 envs 2.04 / 1.20 / 1.38 / 1.64 / 1.84, 16 384 envs
+// 3.9 / 2.37 / 1.41 / 1.70 / 1.87, 30 011 envs 7.7 / 4.7 / 2.54 / 1.81 / 2.10,
+// 65 536 envs - / 8.8 / 4.6 / 2.90 / 1.98.
 inline int32_t launch_tile_envs(int64_t n_envs) {
-  for (const int32_t e : {4, 16, 32})
+  for (const int32_t e : {4, 8, 16, 32})
     if ((n_envs + e - 1) / e <= 1024) return e;
   return 64;
 }
