@@ -60,18 +60,38 @@ constexpr uint32_t kBlue = 2;
 // Philox4x32-10 (Salmon et al., SC'11): counter-based, so every draw is a
 // pure function of (key, counter) and needs no stored generator state.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ uint4 philox10(uint4 c, uint2 k) {
+__device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+  return (uint32_t)__builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
+
+__device__ __forceinline__ uint4 philox_round(uint4 c, uint2 k) {
+  const uint32_t lo0 = 0xD2511F53u * c.x, hi0 = __umulhi(0xD2511F53u, c.x);
+  const uint32_t lo1 = 0xCD9E8D57u * c.z, hi1 = __umulhi(0xCD9E8D57u, c.z);
+  return make_uint4(xor3(hi1, c.y, k.x), lo1, xor3(hi0, c.w, k.y), lo0);
+}
+
+// N blocks of one key, round by round beside each other: one alone is a chain
+// of dependent operations (8 cycles each against 5).  With this, one
+// exclusive or of three and the balls' straight line (move_balls): 30 011
+// envs of all families, 64 steps 316 -> 301 us, 65 536 Dynamic-Obstacles 293 ->
+// 275, KeyCorridor 221 -> 213.
+template <int N>
+__device__ __forceinline__ void philox10(uint4 (&c)[N], uint2 k) {
 #pragma unroll
   for (int r = 0; r < 10; ++r) {
     if (r) {
       k.x += 0x9E3779B9u;
       k.y += 0xBB67AE85u;
     }
-    const uint32_t lo0 = 0xD2511F53u * c.x, hi0 = __umulhi(0xD2511F53u, c.x);
-    const uint32_t lo1 = 0xCD9E8D57u * c.z, hi1 = __umulhi(0xCD9E8D57u, c.z);
-    c = make_uint4(hi1 ^ c.y ^ k.x, lo1, hi0 ^ c.w ^ k.y, lo0);
+#pragma unroll
+    for (int i = 0; i < N; ++i) c[i] = philox_round(c[i], k);
   }
-  return c;
+}
+
+__device__ __forceinline__ uint4 philox10(uint4 c, uint2 k) {
+  uint4 one[1] = {c};
+  philox10<1>(one, k);
+  return one[0];
 }
 
 // A value the compiler knows nothing about from here on, so that what is
@@ -153,15 +173,17 @@ struct DrawWindow {
   __device__ __forceinline__ void fill() {
     block += w >> 2;
     w &= 3u;
-    const uint2 key = opaque(seed);
+    uint4 v[kDrawBlocks];
+#pragma unroll
+    for (int b = 0; b < kDrawBlocks; ++b) v[b] = make_uint4(id, episode, block + (uint32_t)b, 0u);
+    philox10<kDrawBlocks>(v, opaque(seed));
 #pragma unroll
     for (int b = 0; b < kDrawBlocks; ++b) {
-      const uint4 v = philox10(make_uint4(id, episode, block + (uint32_t)b, 0u), key);
       uint32_t* p = words + 4 * kWave * b;
-      p[0] = v.x;
-      p[kWave] = v.y;
-      p[2 * kWave] = v.z;
-      p[3 * kWave] = v.w;
+      p[0] = v[b].x;
+      p[kWave] = v[b].y;
+      p[2 * kWave] = v[b].z;
+      p[3 * kWave] = v[b].w;
     }
   }
   // refills every lane's window if some lane's holds fewer than n <= 9 words
@@ -417,9 +439,9 @@ __device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32
     L.ax = L.ay = 1;
     L.dir = 0;
     const uint32_t w = (uint32_t)(S - 2);
-    const uint4 w0 = philox10(make_uint4(rng_id, episode, 0u, 0u), seed);
-    const uint4 w1 = param > 4 ? philox10(make_uint4(rng_id, episode, 1u, 0u), seed)
-                               : make_uint4(0, 0, 0, 0);
+    uint4 blk[2] = {make_uint4(rng_id, episode, 0u, 0u), make_uint4(rng_id, episode, 1u, 0u)};
+    philox10<2>(blk, seed);
+    const uint4 w0 = blk[0], w1 = blk[1];
     uint32_t sorted[kMaxObst];
 #pragma unroll
     for (int b = 0; b < kMaxObst; ++b) {
@@ -448,10 +470,11 @@ __device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32
     // right y, bottom x, left y), four distinct colours by a partial
     // Fisher-Yates shuffle of the six, the mission the colour of door u(4),
     // the agent uniform over the room's interior; 13 words in draw order
-    const uint4 w0 = philox10(make_uint4(rng_id, episode, 0u, 0u), seed);
-    const uint4 w1 = philox10(make_uint4(rng_id, episode, 1u, 0u), seed);
-    const uint4 w2 = philox10(make_uint4(rng_id, episode, 2u, 0u), seed);
-    const uint4 w3 = philox10(make_uint4(rng_id, episode, 3u, 0u), seed);
+    uint4 w[4];
+#pragma unroll
+    for (uint32_t b = 0; b < 4; ++b) w[b] = make_uint4(rng_id, episode, b, 0u);
+    philox10<4>(w, seed);
+    const uint4 w0 = w[0], w1 = w[1], w2 = w[2], w3 = w[3];
     const int rw = 5 + (int)bounded(w0.x, (uint32_t)(S - 4));
     const int rh = 5 + (int)bounded(w0.y, (uint32_t)(S - 4));
     L.kx = rw;
@@ -498,8 +521,9 @@ __device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32
     }
     return L;
   }
-  const uint4 w0 = philox10(make_uint4(rng_id, episode, 0u, 0u), seed);
-  const uint4 w1 = philox10(make_uint4(rng_id, episode, 1u, 0u), seed);
+  uint4 w[2] = {make_uint4(rng_id, episode, 0u, 0u), make_uint4(rng_id, episode, 1u, 0u)};
+  philox10<2>(w, seed);
+  const uint4 w0 = w[0], w1 = w[1];
   if (fam == kFamEmpty) {
     const int w = S - 2;
     const uint32_t k = bounded(w0.x, (uint32_t)(w * w - 1));   // interior minus the last (goal) cell
@@ -732,7 +756,9 @@ __device__ __forceinline__ bool is_door_code(uint32_t code) {
 // Entries off the interior (only a malformed state has them) do not move.
 // One ball is a chain of some 25 dependent operations and two LDS round trips,
 // and a wave runs it for its lane with the most balls: 65 536 envs of the four
-// obstacle tasks 7.4 -> 6.5 us a step against eight byte reads and a search.
+// obstacle tasks 7.4 -> 6.5 us a step against eight byte reads and a search,
+// 4.6 -> 4.3 without a branch for each of a ball's conditions (lanes whose ball
+// is none of theirs look at the interior's first cell and move nothing).
 constexpr int kMaskPatterns = 256;
 
 // entry m: nibble k is the place of the k-th set bit of m among the 8
@@ -753,44 +779,45 @@ __device__ __forceinline__ void build_kth_table(uint32_t* table, int lane) {
   }
 }
 
-// at: byte offset of the env's grid in `lds`, pos: the agent's cell in it
-__device__ __forceinline__ void move_balls(uint8_t* lds, int at, int S, int n, int pos, uint32_t (&ob)[4], uint2 seed,
-                                           uint32_t rng_id, uint32_t call, const uint32_t* kth) {
+// at: byte offset of the env's grid in `lds`, pos: the agent's cell in it,
+// most: the largest n of the wave
+__device__ __forceinline__ void move_balls(uint8_t* lds, int at, int S, int n, int most, int pos, uint32_t (&ob)[4],
+                                           uint2 seed, uint32_t rng_id, uint32_t call, const uint32_t* kth) {
   uint8_t under = lds[at + pos];
   lds[at + pos] = 0;
   const uint32_t inner = (uint32_t)(S - 2);
-  uint4 blk = make_uint4(0, 0, 0, 0);
+  uint4 blk[2] = {make_uint4(rng_id, call, 0u, 2u), make_uint4(rng_id, call, 1u, 2u)};
+  philox10<2>(blk, seed);
 #pragma unroll
   for (int b = 0; b < kMaxObst; ++b) {
-    if (b < n) {
-      if ((b & 3) == 0) blk = philox10(make_uint4(rng_id, call, (uint32_t)(b >> 2), 2u), seed);
-      const uint32_t word = pick4(blk, (uint32_t)(b & 3));
+    if (b < most) {
+      const uint32_t word = pick4(blk[b >> 2], (uint32_t)(b & 3));
       const uint32_t xy = obst_at(ob, b);
       const uint32_t bx = xy & 0xFFu, by = xy >> 8;
-      if (max(bx - 1u, by - 1u) < inner) {
-        const int cell = at + (int)(by * (uint32_t)S + bx);
-        uint32_t mask = 0;
+      const bool ok = b < n && max(bx - 1u, by - 1u) < inner;
+      const int cell = at + (ok ? (int)(by * (uint32_t)S + bx) : S + 1);
+      uint32_t mask = 0;
 #pragma unroll
-        for (int r = 0; r < 3; ++r) {
-          const int o = cell + (r - 1) * S - 1;
-          const uint32_t* p = reinterpret_cast<const uint32_t*>(lds + (o & ~3));
-          // bytes equal to kCodeEmpty: zero after the exclusive or; bit 7 of
-          // each byte of ((v & 0x7F) + 0x7F) | v is clear exactly there
-          const uint32_t v = __builtin_amdgcn_alignbyte(p[1], p[0], (uint32_t)o & 3u) ^ (kCodeEmpty * 0x01010101u);
-          const uint32_t empty = ~(((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v) & 0x80808080u;
-          constexpr uint32_t kPlaces[3] = {0x00040201u, 0x00100008u, 0x00804020u};
-          mask = __builtin_amdgcn_udot4(empty, kPlaces[r], mask, false);
-        }
-        if (mask) {
-          const uint32_t k = bounded(word, (uint32_t)__builtin_popcount(mask));
-          const uint32_t v = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(kth) + (mask >> 5)) >> (4u * k);
-          const int dx = (int)(v & 3u) - 1, dy = (int)((v >> 2) & 3u) - 1;
-          const bool from_agent = cell == at + pos;   // a malformed state's ball under the agent
-          under = from_agent ? (uint8_t)kCodeEmpty : under;
-          lds[cell] = from_agent ? (uint8_t)0 : (uint8_t)kCodeEmpty;
-          lds[cell + dy * S + dx] = (uint8_t)kCodeBall;
-          obst_set(ob, b, bx + (uint32_t)dx, by + (uint32_t)dy);
-        }
+      for (int r = 0; r < 3; ++r) {
+        const int o = cell + (r - 1) * S - 1;
+        const uint32_t* p = reinterpret_cast<const uint32_t*>(lds + (o & ~3));
+        // bytes equal to kCodeEmpty: zero after the exclusive or; bit 7 of
+        // each byte of ((v & 0x7F) + 0x7F) | v is clear exactly there
+        const uint32_t v = __builtin_amdgcn_alignbyte(p[1], p[0], (uint32_t)o & 3u) ^ (kCodeEmpty * 0x01010101u);
+        const uint32_t empty = ~(((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v) & 0x80808080u;
+        constexpr uint32_t kPlaces[3] = {0x00040201u, 0x00100008u, 0x00804020u};
+        mask = __builtin_amdgcn_udot4(empty, kPlaces[r], mask, false);
+      }
+      mask = ok ? mask : 0u;
+      const uint32_t k = bounded(word, (uint32_t)__builtin_popcount(mask));
+      const uint32_t v = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(kth) + (mask >> 5)) >> (4u * k);
+      const uint32_t nx = bx + (v & 3u) - 1u, ny = by + ((v >> 2) & 3u) - 1u;
+      const bool from_agent = cell == at + pos;   // a malformed state's ball under the agent
+      if (mask) {
+        under = from_agent ? (uint8_t)kCodeEmpty : under;
+        lds[cell] = from_agent ? (uint8_t)0 : (uint8_t)kCodeEmpty;
+        lds[at + (int)(ny * (uint32_t)S + nx)] = (uint8_t)kCodeBall;
+        obst_set(ob, b, nx, ny);
       }
     }
   }
@@ -1474,8 +1501,8 @@ __device__ __forceinline__ void fill_cells(const Next& n, uint32_t S, uint32_t p
   if (F == kFamDynObs) {
 #pragma unroll
     for (int i = 0; i < kMaxObst; ++i) {
-      const uint32_t xy = obst_at(n.u, i);
-      if ((uint32_t)i < param) put(xy & 255u, xy >> 8, kCodeBall);
+      const uint32_t xy = (uint32_t)i < param ? obst_at(n.u, i) : obst_at(n.u, 0);
+      put(xy & 255u, xy >> 8, kCodeBall);
     }
   }
   if (F == kFamGoToDoor) {
@@ -2048,10 +2075,13 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
     }
     uint32_t carry_code = code_of(carry);
     bool carry_changed = fresh;   // until then the state's own triple stays
-    const bool any_balls = __ballot(fam == kFamDynObs) != 0, any_missions = __ballot(fam == kFamGoToDoor) != 0;
+    const bool any_missions = __ballot(fam == kFamGoToDoor) != 0;
     int pos = y * S + x;          // the agent's cell in its grid
     bool filled = fresh;          // the grid was laid out in this launch
-    if (any_balls) build_kth_table(kth_cell, lane);
+    int most_balls = 0;           // of an env of this tile
+    while (most_balls < kMaxObst && __ballot(fam == kFamDynObs && ((meta >> 16) & 255u) > (uint32_t)most_balls))
+      ++most_balls;
+    if (most_balls) build_kth_table(kth_cell, lane);
     wave_sync();
 
     uint4 pol = make_uint4(0, 0, 0, 0);
@@ -2072,19 +2102,19 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       if (kSplit && s > 0) pair_barrier();   // the rows of step s - 1 are read
       const bool do_reset = active && done_prev;
       const uint64_t pending = __ballot(do_reset);
-      if (kSplit && (pending || any_balls)) __builtin_amdgcn_s_setprio(2);
+      if (kSplit && (pending || most_balls != 0)) __builtin_amdgcn_s_setprio(2);
       if (pending) {
         // in the launch's last step only for the lanes that reset: nothing is
         // kept for the next launch
         draw_missing(next, have_next, do_reset, s + 1 < steps ? active : do_reset, meta, seed, rid, episode + 1u,
                      stage_words + lane);
         const bool kept = filled && keeps_base(fam);
-        if (any_balls && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
+        if (most_balls != 0 && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
           const uint32_t balls = (opaque(meta) >> 16) & 255u;
 #pragma unroll
           for (int i = 0; i < kMaxObst; ++i) {
-            const uint32_t xy = obst_at(ob, i);
-            if ((uint32_t)i < balls) my_codes[(xy >> 8) * (uint32_t)S + (xy & 255u)] = (uint8_t)kCodeEmpty;
+            const uint32_t xy = (uint32_t)i < balls ? obst_at(ob, i) : obst_at(ob, 0);
+            my_codes[(xy >> 8) * (uint32_t)S + (xy & 255u)] = (uint8_t)kCodeEmpty;
           }
         }
         if (do_reset) {
@@ -2112,12 +2142,12 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       const int ahead = pos + dy * S + dx;
       uint32_t front = my_codes[ahead];
       uint32_t penalty = 0;
-      if (any_balls && fam == kFamDynObs && live) {
+      if (most_balls != 0 && fam == kFamDynObs && live) {
         // three actions; the cell ahead is judged before the balls move
         act = act > kForward ? kLeft : act;
         penalty = (act == kForward && front != kCodeEmpty && (front & 0x8Fu) != kGoal) ? 1u : 0u;
-        move_balls(grids, kMargin + my_off, S, (int)((opaque(meta) >> 16) & 0xFF), pos, ob, opaque(seed), opaque(rid),
-                   call, kth_cell);
+        move_balls(grids, kMargin + my_off, S, (int)((opaque(meta) >> 16) & 0xFF), most_balls, pos, ob,
+                   opaque(seed), opaque(rid), call, kth_cell);
         front = my_codes[ahead];
       }
       const uint32_t a6 = min(act, 6u);
