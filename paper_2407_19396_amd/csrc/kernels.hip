@@ -2253,7 +2253,8 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
 // Every env's episode 0 (env_reset), tile by tile as k_fused runs them: the
 // layouts are drawn a family at a time, the grids laid out in LDS and written
 // as one block, the first timestep's record taken from them.  Bound by the
-// fill, one env of the tile after another, and the draws; the plain kernel,
+// fill, one env of the tile after another (hence its smaller tiles,
+// reset_tile_envs), and the draws; the plain kernel,
 // which did this before, wrote the grids cell by cell as three bytes each.
 template <int kObs>
 __global__ __launch_bounds__(kWave) void k_reset(FusedArgs a) {

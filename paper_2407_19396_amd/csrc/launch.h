@@ -70,6 +70,17 @@ inline int32_t launch_tile_envs(int64_t n_envs) {
   return 64;
 }
 
+// The same for resets (k_reset): at most 32.  An env's grid is laid out by its
+// whole wave, one env after another, and a tile of half the size leaves LDS for
+// twice the waves: 65 536 envs in tiles of 64 / 32 / 16, Empty 8x8 22.9 / 17.2 /
+// 16.2 us, the uneven mix 43 / 31 / 29, FourRooms 19x19 68 / 42 / 47, all
+// families 114 / 108 / 130 (most of it draws of a varying number, where a
+// wave waits for its longest), 262 144 envs of the mix 102 / 89 / 83.
+inline int32_t reset_tile_envs(int64_t n_envs) {
+  const int32_t e = launch_tile_envs(n_envs);
+  return e < 32 ? e : 32;
+}
+
 // A tile of 64 slots serving one request (device memory, 64 bytes).  The
 // tile's envs are slots [tile * 64, tile * 64 + n_envs); their grids are
 // contiguous from the first slot's on.  The record of the request's step r for its

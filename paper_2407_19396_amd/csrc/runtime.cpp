@@ -38,6 +38,7 @@ struct gx_ctx {
   // in tiles of their own choice (gx::launch_tile_envs)
   bool shape_chosen = false;
   int32_t auto_envs = 64, auto_tiles = 0, auto_cells = 0;
+  int32_t reset_envs = 32, reset_tiles = 0, reset_cells = 0;   // env_reset's (gx::reset_tile_envs)
   std::vector<int32_t> cells;          // S^2 per env, for re-tiling
   // rgb modes: the sprite atlas, and the staging ring of symbolic records
   // (obs [stage_rows][sym_row], then reward, flags, action, mission
@@ -330,6 +331,9 @@ int env_create(const gx_config* cfg, gx_ctx** out) {
   c->auto_envs = gx::launch_tile_envs(n);
   c->auto_tiles = (n + c->auto_envs - 1) / c->auto_envs;
   c->auto_cells = largest_tile(c, c->auto_envs);
+  c->reset_envs = gx::reset_tile_envs(n);
+  c->reset_tiles = (n + c->reset_envs - 1) / c->reset_envs;
+  c->reset_cells = largest_tile(c, c->reset_envs);
   *out = c;
   return GX_OK;
 }
@@ -364,7 +368,8 @@ int env_reset(gx_ctx* c, const gx_state* st, const gx_traj* first, void* stream)
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   gx::TrajBufs tb{nullptr, nullptr, nullptr, nullptr, 1};
   if (first) tb = staged(c, first) ? stage_traj(c) : traj_of(c, first);
-  if (gx::launch_reset(tables_of(c), launch_shape(c).tiles, state_of(st), tb, s) != hipSuccess)
+  const gx::TileTables own{c->reset_tiles, c->reset_cells, nullptr, c->reset_envs};
+  if (gx::launch_reset(tables_of(c), c->shape_chosen ? launch_shape(c).tiles : own, state_of(st), tb, s) != hipSuccess)
     return GX_EDEVICE;
   if (staged(c, first) && render_rows(c, 1, first, 0, s) != hipSuccess) return GX_EDEVICE;
   c->has_reset = true;

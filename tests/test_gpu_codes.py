@@ -128,3 +128,24 @@ def test_waves_alone_and_in_pairs(tile_envs, blocks, obs_mode):
         P.assert_rows_equal(traj, ref, what=f"{blocks} workgroups, mode {obs_mode}")
         P.assert_state_equal(env, s, f"{blocks} workgroups, mode {obs_mode}")
         env.close()
+
+
+@pytest.mark.parametrize("n", [32769, 40000])
+def test_reset_in_halves_of_a_launch_tile(n):
+    """From 32 769 envs on resets run tiles of 32 and steps tiles of 64, ragged
+    at both."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    table = wl.families_table(n, seed=4)
+    b, s, first = P.oracle_reset(table, 0, 0)
+    env = ge.GridEnv(table)
+    row = env.traj(1)
+    env.reset(row)
+    P.assert_rows_equal(row, first, what=f"{n} envs, first timestep")
+    ref = ox.rollout(b, s, 3, None, nthreads=8)
+    traj = env.traj(3)
+    env.rollout(3, traj)
+    torch.cuda.synchronize()
+    P.assert_rows_equal(traj, ref, what=f"{n} envs")
+    P.assert_state_equal(env, s, f"{n} envs")
+    env.close()
