@@ -147,8 +147,14 @@ def env_strerror(status: int) -> str:
 
 def _stream_ptr(stream) -> int | None:
     import torch
-    s = stream if stream is not None else torch.cuda.current_stream()
-    return s.cuda_stream or None
+    if stream is not None:
+        return stream.cuda_stream or None
+    if torch.cuda.is_initialized():
+        # the current stream's handle without the Stream object that
+        # current_stream() builds around it: 2.9 -> 0.4 us of every call (a
+        # step of 16 envs 8.0 -> 5.2)
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice()) or None
+    return torch.cuda.current_stream().cuda_stream or None
 
 
 # --------------------------------------------------------------- C names

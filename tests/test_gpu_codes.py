@@ -149,3 +149,15 @@ def test_reset_in_halves_of_a_launch_tile(n):
     P.assert_rows_equal(traj, ref, what=f"{n} envs")
     P.assert_state_equal(env, s, f"{n} envs")
     env.close()
+
+
+def test_current_stream_of_a_call():
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    torch.zeros(1, device="cuda")
+    side = torch.cuda.Stream()
+    assert ge._stream_ptr(None) is None and ge._stream_ptr(side) == side.cuda_stream
+    with torch.cuda.stream(side):
+        assert ge._stream_ptr(None) == side.cuda_stream
+        assert ge._stream_ptr(torch.cuda.default_stream()) is None
+    assert ge._stream_ptr(None) is None
