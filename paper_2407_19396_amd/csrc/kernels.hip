@@ -7,17 +7,18 @@
 // termination systems of Table "systems" and App. A over the entities of
 // Table "entities", for every family of Table "envs".
 //
-// Two kernels share the device functions below:
+// Three kernels share the device functions below:
 //   k_plain  -- one launch per step; one env per lane; state, grid and
-//               outputs in HBM; view cells read straight from the grid.
-//   k_fused  -- persistent; each workgroup takes tiles of 64 envs of any
-//               mix of sizes, stages their grids in LDS as one byte per
-//               cell, runs K steps with the pose in registers, writes one
-//               trajectory record per env-step, then writes the state back.
-//               Its serving variant also admits and resets new requests.
-// Both stage the first-person observations of a wave through LDS so that
-// the wave's records leave as one contiguous block: k_plain as bytes, in
-// 16-byte stores; k_fused as one code per cell, decoded on the way out, in
+//               outputs in HBM; the view's rows read straight from the grid.
+//   k_fused  -- each workgroup takes tiles of up to 64 envs of any mix of
+//               sizes, stages their grids in LDS as one code byte per cell,
+//               runs K steps with the pose in registers, writes one
+//               trajectory record per env-step, then writes the state back;
+//               with few tiles a second wave writes the records.  Its serving
+//               variant also admits and resets new requests.
+//   k_reset  -- episode 0 of every env, laid out in LDS as in k_fused.
+// First-person observations are staged in LDS as one code per cell, so that
+// a wave's records leave as one contiguous block, decoded on the way out, in
 // 12-byte stores.  Whole-grid observations leave the same way, packed like
 // the grids.
 //

@@ -161,3 +161,22 @@ def test_current_stream_of_a_call():
         assert ge._stream_ptr(None) == side.cuda_stream
         assert ge._stream_ptr(torch.cuda.default_stream()) is None
     assert ge._stream_ptr(None) is None
+
+
+@pytest.mark.parametrize("n,steps", [(61440 + 4, 128), (122880, 128), (122816, 128), (131072 + 1, 129)])
+def test_long_rollouts_of_many_tiles(n, steps):
+    """Batches at and beside the tile counts whose long launches take the tiles
+    in turn; the ring keeps the last rows."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    table = wl.mixed_table(n, seed=9)
+    b, s, _ = P.oracle_reset(table, 0, 0)
+    ref = ox.rollout(b, s, steps, None, rows=3, nthreads=8)
+    env = ge.GridEnv(table)
+    env.reset()
+    traj = env.traj(3)
+    env.rollout(steps, traj, K=steps)
+    torch.cuda.synchronize()
+    P.assert_rows_equal(traj, ref, what=f"{n} envs")
+    P.assert_state_equal(env, s, f"{n} envs")
+    env.close()
