@@ -287,8 +287,63 @@ struct KcLayout {
   uint32_t kd[3];
 };
 
+// What connects a layout's rooms so far, for the lanes that keycorridor_layout
+// leaves to connect_few: the doors as bits of the room on their west or north
+// side, the door positions, the next word of the stream, the attempts made.
+struct KcRest {
+  uint32_t todo, right, down;
+  uint64_t pos;
+  uint32_t word, tries;
+};
+constexpr uint32_t kKcTries = 1024;
+constexpr int kKcFew = 8;
+
+// From the hallway any room is at most one wall across and two along.
+__device__ __forceinline__ bool kc_connected(uint32_t R, uint32_t right, uint32_t down) {
+  const uint32_t all = (1u << (3u * R)) - 1u;
+  uint32_t reached = 0x92u & all;
+#pragma unroll
+  for (int hop = 0; hop < 3; ++hop)
+    reached |= ((reached & right) << 1) | ((reached >> 1) & right) | ((reached & down) << 3) | ((reached >> 3) & down);
+  return reached == all;
+}
+
+// An attempt picks a room and a wall of it, three words, and takes a fourth for
+// the colour if it adds a door: 0, or 1 | room << 1 | across << 6 | wall << 7 |
+// the door's table entry << 11.
+__device__ __forceinline__ uint32_t kc_attempt(const uint32_t (&w)[4], uint32_t R, uint32_t rl, uint32_t right,
+                                               uint32_t down, uint64_t pos) {
+  const int i = (int)bounded(w[0], 3u), j = (int)bounded(w[1], R);
+  const uint32_t k = bounded(w[2], 4u), c = bounded(w[3], 6u);
+  // k: east, south, west, north
+  const int i2 = i + (k == 0u ? 1 : 0) - (k == 2u ? 1 : 0), j2 = j + (k == 1u ? 1 : 0) - (k == 3u ? 1 : 0);
+  const uint32_t across = (k & 1u) ^ 1u;
+  const int il = min(i, i2), jl = min(j, j2);
+  const uint32_t room = (uint32_t)(3 * jl + il) & 31u;
+  const uint32_t known = ((across ? right : down) >> room) & 1u;
+  const uint32_t inside = ((unsigned)i2 < 3u ? 1u : 0u) & ((unsigned)j2 < R ? 1u : 0u);
+  // a cell (room) number 3 j + i tells the locked room apart
+  const int lock = (int)(3u * rl + 2u);
+  const uint32_t locked = (3 * j + i == lock ? 1u : 0u) | (3 * j2 + i2 == lock ? 1u : 0u);
+  const uint32_t e = (uint32_t)(across ? 2 * jl + il : 6 + 2 * jl + (i >> 1)) & 15u;
+  const uint32_t entry = 0x80u | (c << 4) | (uint32_t)((pos >> (4u * e)) & 15u);
+  return inside & ~(known | locked) ? 1u | (room << 1) | (across << 6) | (e << 7) | (entry << 11) : 0u;
+}
+
+__device__ __forceinline__ void kc_add(uint32_t door, uint32_t& right, uint32_t& down, uint32_t (&kd)[3]) {
+  const uint32_t bit = (door & 1u) << ((door >> 1) & 31u);
+  const bool across = (door >> 6) & 1u;
+  right |= across ? bit : 0u;
+  down |= across ? 0u : bit;
+  const uint32_t e = (door >> 7) & 15u, v = (door >> 11) << (8u * (e & 3u));
+  kd[0] |= e < 4u ? v : 0u;
+  kd[1] |= (e >> 2) == 1u ? v : 0u;
+  kd[2] |= (e >> 2) == 2u ? v : 0u;
+}
+
+template <bool kTogether>
 __device__ __forceinline__ KcLayout keycorridor_layout(int S, int R, uint2 seed, uint32_t rng_id,
-                                                       uint32_t episode, uint32_t* words) {
+                                                       uint32_t episode, uint32_t* words, KcRest& rest) {
   DrawWindow d{words, seed, rng_id, episode, 0u, 0u};
   d.fill();   // the walls take at most 12 draws
   const int st = (S - 1) / 3, inner = st - 1;
@@ -325,46 +380,78 @@ __device__ __forceinline__ KcLayout keycorridor_layout(int S, int R, uint2 seed,
   K.ay = ra * st + 1 + (int)q;
   K.dir = (int)d.next(4u);
   // connect every room (MiniGrid's connect_all), the locked room excepted
-  const uint32_t all = (1u << (3 * R)) - 1u;
   uint32_t right = 1u << (3 * K.rl + 1), down = 0u;   // the locked door
   for (int j = 0; j + 1 < R; ++j) down |= 1u << (3 * j + 1);   // the hallway
-  // An attempt picks a room and a wall of it, three words, and takes a fourth
-  // for the colour if it adds a door.  The wave runs attempts until its last
-  // lane is connected (some 55 of them for 64 layouts of nine rooms), so an
-  // attempt is selects without branches.
-  const uint32_t hallway = 0x92u & all;
-  for (int it = 0; it < 1024; ++it) {
-    // from the hallway any room is at most one wall across and two along
-    uint32_t reached = hallway;
-#pragma unroll
-    for (int hop = 0; hop < 3; ++hop)
-      reached |= ((reached & right) << 1) | ((reached >> 1) & right) | ((reached & down) << 3) | ((reached >> 3) & down);
-    const bool todo = reached != all;
-    if (!__ballot(todo)) break;
+  // The wave runs attempts until its last lanes are left (55 and more for the
+  // longest of 64 layouts), so an attempt is selects without branches.
+  bool todo = true;
+  uint32_t it = 0;
+  for (; it < kKcTries; ++it) {
+    todo = !kc_connected((uint32_t)R, right, down);
+    if (__popcll(__ballot(todo)) <= (kTogether ? kKcFew : 0)) break;
     d.need(4u);
     const uint32_t* at = d.words + kWave * d.w;
-    const int i = (int)bounded(at[0], 3u), j = (int)bounded(at[kWave], (uint32_t)R);
-    const uint32_t k = bounded(at[2 * kWave], 4u), c = bounded(at[3 * kWave], 6u);
-    // k: east, south, west, north
-    const int i2 = i + (k == 0u ? 1 : 0) - (k == 2u ? 1 : 0), j2 = j + (k == 1u ? 1 : 0) - (k == 3u ? 1 : 0);
-    const bool horiz = (k & 1u) == 0u;
-    const int il = min(i, i2), jl = min(j, j2);
-    const uint32_t room = (uint32_t)(3 * jl + il) & 31u;
-    const uint32_t known = ((horiz ? right : down) >> room) & 1u;
-    const uint32_t inside = ((unsigned)i2 < 3u ? 1u : 0u) & ((unsigned)j2 < (unsigned)R ? 1u : 0u);
-    // a cell (room) number 3 j + i tells the locked room apart
-    const uint32_t locked = (3 * j + i == 3 * K.rl + 2 ? 1u : 0u) | (3 * j2 + i2 == 3 * K.rl + 2 ? 1u : 0u);
-    const uint32_t add = (todo ? inside : 0u) & ~(known | locked);
-    d.w += todo ? 3u + add : 0u;
-    right |= horiz ? add << room : 0u;
-    down |= horiz ? 0u : add << room;
-    const uint32_t e = (uint32_t)(horiz ? 2 * jl + il : 6 + 2 * jl + (i >> 1)) & 15u;
-    const uint32_t v = add ? (0x80u | (c << 4) | (uint32_t)((pos >> (4u * e)) & 15u)) << (8u * (e & 3u)) : 0u;
-    K.kd[0] |= e < 4u ? v : 0u;
-    K.kd[1] |= (e >> 2) == 1u ? v : 0u;
-    K.kd[2] |= (e >> 2) == 2u ? v : 0u;
+    const uint32_t w[4] = {at[0], at[kWave], at[2 * kWave], at[3 * kWave]};
+    const uint32_t door = todo ? kc_attempt(w, (uint32_t)R, (uint32_t)K.rl, right, down, pos) : 0u;
+    d.w += todo ? 3u + (door & 1u) : 0u;
+    kc_add(door, right, down, K.kd);
   }
+  if (kTogether) rest = KcRest{todo && it < kKcTries ? 1u : 0u, right, down, pos, 4u * d.block + d.w, it};
   return K;
+}
+
+// Finishes the at most kKcFew layouts of the wave with rest.todo set, doors
+// into kd: each has a group of 8 lanes, and lane t of a group tries the t-th
+// next attempt.  As long as none adds a door every attempt takes three words, so
+// the first that does is the one a serial run would come to.  All lanes
+// call this.  A layout may take over a hundred attempts one after another, and
+// 65 536 envs always hold such a one: a reset of 65 536 envs of all families 109 ->
+// 55 us, of KeyCorridor alone 111 -> 61.  The steppers do without: the code
+// costs each of their steps 1-3 % (4096 Empty 8x8 240 -> 247 us for 256 steps)
+// and gains 18 % of a KeyCorridor rollout and 7 % of one of all families.
+__device__ __forceinline__ void connect_few(uint32_t (&kd)[3], uint32_t rl, const KcRest& rest, uint32_t meta,
+                                            uint2 seed, uint32_t rng_id, uint32_t episode) {
+  const uint64_t few = __ballot(rest.todo != 0u);
+  if (!few) return;
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+  const int group = lane >> 3;
+  const uint32_t t = (uint32_t)lane & 7u;
+  int owner = 0, groups = 0;
+  for (uint64_t m = few; m; m &= m - 1, ++groups) owner = group == groups ? __ffsll((unsigned long long)m) - 1 : owner;
+  auto of = [&](uint32_t v) { return (uint32_t)__shfl((int)v, owner, kWave); };
+  const uint32_t R = (of(meta) >> 16) & 255u, lock = of(rl), id = of(rng_id), ep = of(episode);
+  const uint2 key = make_uint2(of(seed.x), of(seed.y));
+  const uint64_t pos = (uint64_t)of((uint32_t)rest.pos) | ((uint64_t)of((uint32_t)(rest.pos >> 32)) << 32);
+  uint32_t right = of(rest.right), down = of(rest.down), word = of(rest.word), tries = of(rest.tries);
+  uint32_t doors[3] = {of(kd[0]), of(kd[1]), of(kd[2])};
+  while (true) {
+    const bool todo = group < groups && tries < kKcTries && !kc_connected(R, right, down);
+    if (!__ballot(todo)) break;
+    const uint32_t at = word + 3u * t, sh = at & 3u;
+    uint4 b[2] = {make_uint4(id, ep, at >> 2, 0u), make_uint4(id, ep, (at >> 2) + 1u, 0u)};
+    philox10<2>(b, key);
+    const uint32_t v[7] = {b[0].x, b[0].y, b[0].z, b[0].w, b[1].x, b[1].y, b[1].z};
+    uint32_t w[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const uint32_t lo = (sh & 1u) ? v[q + 1] : v[q], hi = q + 3 < 7 ? ((sh & 1u) ? v[q + 3] : v[q + 2]) : v[q + 2];
+      w[q] = (sh & 2u) ? hi : lo;
+    }
+    const uint32_t door = todo && tries + t < kKcTries ? kc_attempt(w, R, lock, right, down, pos) : 0u;
+    const uint64_t hits = __ballot(door != 0u);
+    const uint32_t mine = (uint32_t)(hits >> (8 * group)) & 255u;
+    const uint32_t first = mine ? (uint32_t)__builtin_ctz(mine) : 0u;
+    const uint32_t added = (uint32_t)__shfl((int)door, 8 * group + (int)first, kWave);
+    kc_add(mine ? added : 0u, right, down, doors);
+    word += mine ? 3u * first + 4u : 24u;
+    tries += mine ? first + 1u : 8u;
+  }
+  const int rank = (int)__popcll(few & ((1ull << lane) - 1ull));
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    const uint32_t v = (uint32_t)__shfl((int)doors[q], (8 * rank) & 63, kWave);
+    kd[q] = rest.todo ? v : kd[q];
+  }
 }
 
 // idx-th free cell, row-major, of a four-room grid of side S = 2m + 1 with
@@ -401,7 +488,9 @@ __device__ __forceinline__ void fourrooms_cell(int S, int m, int g1, int g2, int
 // variant; Dynamic-Obstacles: balls; KeyCorridor: rows of rooms).  The lava
 // families and Dynamic-Obstacles start at (1, 1) facing east.
 // words: the lane's column of the draw window.
-__device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32_t episode, uint32_t* words) {
+template <bool kTogether>
+__device__ __forceinline__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32_t episode, uint32_t* words,
+                              KcRest& rest) {
   const uint32_t fam = meta & 0xFF;
   const int S = (int)((meta >> 8) & 0xFF), param = (int)((meta >> 16) & 0xFF);
   Layout L;
@@ -417,7 +506,7 @@ __device__ Layout make_layout(uint32_t meta, uint2 seed, uint32_t rng_id, uint32
   L.ob[0] = L.ob[1] = L.ob[2] = L.ob[3] = 0xFFFFFFFFu;
   L.kd[0] = L.kd[1] = L.kd[2] = 0u;
   if (fam == kFamKeyCorridor) {
-    const KcLayout K = keycorridor_layout(S, param, seed, rng_id, episode, words);
+    const KcLayout K = keycorridor_layout<kTogether>(S, param, seed, rng_id, episode, words, rest);
     L.a = K.rl;
     L.b = param;   // rows of rooms
     L.colour = K.colour;
@@ -1420,29 +1509,32 @@ __device__ __forceinline__ Next pack_layout(const Layout& L) {
 
 // The layout of (seed, id, episode) of every active lane of family f, which
 // is uniform across the wave.
-template <uint32_t F>
+template <uint32_t F, bool kTogether>
 __device__ __forceinline__ Next draw_family(uint32_t meta, uint2 seed, uint32_t rng_id, uint32_t episode,
-                                            uint32_t* words) {
-  return pack_layout(make_layout((meta & ~255u) | F, seed, rng_id, episode, words));
+                                            uint32_t* words, KcRest& rest) {
+  return pack_layout(make_layout<kTogether>((meta & ~255u) | F, seed, rng_id, episode, words, rest));
 }
 
+template <bool kTogether>
 __device__ __forceinline__ Next draw_layout(uint32_t f, uint32_t meta, uint2 seed, uint32_t rng_id,
-                                            uint32_t episode, uint32_t* words) {
+                                            uint32_t episode, uint32_t* words, KcRest& rest) {
   switch (f) {
-    case kFamEmpty: return draw_family<kFamEmpty>(meta, seed, rng_id, episode, words);
-    case kFamTwoRoom: return draw_family<kFamTwoRoom>(meta, seed, rng_id, episode, words);
-    case kFamFourRooms: return draw_family<kFamFourRooms>(meta, seed, rng_id, episode, words);
-    case kFamLavaGap: return draw_family<kFamLavaGap>(meta, seed, rng_id, episode, words);
-    case kFamCrossings: return draw_family<kFamCrossings>(meta, seed, rng_id, episode, words);
-    case kFamDistShift: return draw_family<kFamDistShift>(meta, seed, rng_id, episode, words);
-    case kFamDynObs: return draw_family<kFamDynObs>(meta, seed, rng_id, episode, words);
-    case kFamGoToDoor: return draw_family<kFamGoToDoor>(meta, seed, rng_id, episode, words);
-    default: return draw_family<kFamKeyCorridor>(meta, seed, rng_id, episode, words);
+    case kFamEmpty: return draw_family<kFamEmpty, kTogether>(meta, seed, rng_id, episode, words, rest);
+    case kFamTwoRoom: return draw_family<kFamTwoRoom, kTogether>(meta, seed, rng_id, episode, words, rest);
+    case kFamFourRooms: return draw_family<kFamFourRooms, kTogether>(meta, seed, rng_id, episode, words, rest);
+    case kFamLavaGap: return draw_family<kFamLavaGap, kTogether>(meta, seed, rng_id, episode, words, rest);
+    case kFamCrossings: return draw_family<kFamCrossings, kTogether>(meta, seed, rng_id, episode, words, rest);
+    case kFamDistShift: return draw_family<kFamDistShift, kTogether>(meta, seed, rng_id, episode, words, rest);
+    case kFamDynObs: return draw_family<kFamDynObs, kTogether>(meta, seed, rng_id, episode, words, rest);
+    case kFamGoToDoor: return draw_family<kFamGoToDoor, kTogether>(meta, seed, rng_id, episode, words, rest);
+    default: return draw_family<kFamKeyCorridor, kTogether>(meta, seed, rng_id, episode, words, rest);
   }
 }
 
 // Gives every lane with `need` set a Next for `episode`, drawing with it
 // those of the lanes of its family that have none (have == false).
+// kTogether: see connect_few.
+template <bool kTogether = false>
 __device__ __forceinline__ void draw_missing(Next& n, bool& have, bool need, bool active, uint32_t meta, uint2 seed,
                                              uint32_t rng_id, uint32_t episode, uint32_t* words) {
   while (true) {
@@ -1450,9 +1542,16 @@ __device__ __forceinline__ void draw_missing(Next& n, bool& have, bool need, boo
     if (!missing) return;
     const uint32_t f =
         (uint32_t)bcast((int)meta, __ffsll((unsigned long long)missing) - 1) & 255u;
+    KcRest rest{};
     if (active && !have && (meta & 255u) == f) {
-      n = draw_layout(f, opaque(meta), opaque(seed), opaque(rng_id), episode, words);
+      n = draw_layout<kTogether>(f, opaque(meta), opaque(seed), opaque(rng_id), episode, words, rest);
       have = true;
+    }
+    if (kTogether && f == kFamKeyCorridor) {
+      uint32_t kd[3] = {n.u[0], n.u[1], n.u[2]};   // (see pack_layout)
+      connect_few(kd, n.u[3], rest, opaque(meta), opaque(seed), opaque(rng_id), episode);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) n.u[q] = rest.todo ? kd[q] : n.u[q];
     }
   }
 }
@@ -2286,7 +2385,7 @@ __global__ __launch_bounds__(kWave) void k_reset(FusedArgs a) {
   const uint64_t g0 = bcast64(goff, 0);
   Next next{};
   bool have = false;
-  draw_missing(next, have, active, active, meta, seed, rid, 0u, stage_words + lane);
+  draw_missing<true>(next, have, active, active, meta, seed, rid, 0u, stage_words + lane);
   int x = 1, y = 1, dir = 0;
   uint32_t ob[4] = {~0u, ~0u, ~0u, ~0u};
   if (active) start_episode(next, fam, x, y, dir, ob);

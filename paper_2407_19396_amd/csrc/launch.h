@@ -74,8 +74,8 @@ inline int32_t launch_tile_envs(int64_t n_envs) {
 // whole wave, one env after another, and a tile of half the size leaves LDS for
 // twice the waves: 65 536 envs in tiles of 64 / 32 / 16, Empty 8x8 22.9 / 17.2 /
 // 16.2 us, the uneven mix 43 / 31 / 29, FourRooms 19x19 68 / 42 / 47, all
-// families 114 / 108 / 130 (most of it draws of a varying number, where a
-// wave waits for its longest), 262 144 envs of the mix 102 / 89 / 83.
+// families 63 / 55 / 62 (most of it draws of a varying number, where a wave
+// waits for its longest), 262 144 envs of the mix 102 / 89 / 83.
 inline int32_t reset_tile_envs(int64_t n_envs) {
   const int32_t e = launch_tile_envs(n_envs);
   return e < 32 ? e : 32;

@@ -180,3 +180,32 @@ def test_long_rollouts_of_many_tiles(n, steps):
     P.assert_rows_equal(traj, ref, what=f"{n} envs")
     P.assert_state_equal(env, s, f"{n} envs")
     env.close()
+
+
+@pytest.mark.parametrize("n,together", [(7, 7), (64, 64), (320, 9), (320, 8), (3000, 40)])
+def test_corridors_connected_by_few_lanes(n, together):
+    """Waves with few, exactly eight, nine and only KeyCorridor envs: layouts
+    whose last doors the wave looks for together."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    rng = np.random.default_rng(n + together)
+    corridor = np.arange(n) % 64 < together
+    side = np.where(corridor, rng.choice([7, 10, 13, 16, 19], n), 5).astype(np.uint8)
+    table = wl.EnvTable(np.where(corridor, wl.FAMILY_KEYCORRIDOR, wl.FAMILY_EMPTY).astype(np.uint8), side,
+                        rng.integers(1, 6, n).astype(np.int32), np.full(n, 77 + n, np.uint64),
+                        np.arange(n, dtype=np.uint32), "corridors",
+                        np.where(corridor, rng.integers(1, 4, n), 0).astype(np.uint8))
+    steps = 30
+    b, s, first = P.oracle_reset(table, 0, 2)
+    env = ge.GridEnv(table, obs_mode=2)
+    env.set_tiling(64)
+    row = env.traj(1)
+    env.reset(row)
+    P.assert_rows_equal(row, first, what="first timestep")
+    ref = ox.rollout(b, s, steps, None, nthreads=8)
+    traj = env.traj(steps)
+    env.rollout(steps, traj, K=13)
+    torch.cuda.synchronize()
+    P.assert_rows_equal(traj, ref, what="corridors")
+    P.assert_state_equal(env, s, "corridors")
+    env.close()
