@@ -406,9 +406,10 @@ __device__ __forceinline__ KcLayout keycorridor_layout(int S, int R, uint2 seed,
 // the first that does is the one a serial run would come to.  All lanes
 // call this.  A layout may take over a hundred attempts one after another, and
 // 65 536 envs always hold such a one: a reset of 65 536 envs of all families 109 ->
-// 55 us, of KeyCorridor alone 111 -> 61.  The steppers do without: the code
-// costs each of their steps 1-3 % (4096 Empty 8x8 240 -> 247 us for 256 steps)
-// and gains 18 % of a KeyCorridor rollout and 7 % of one of all families.
+// 55 us, of KeyCorridor alone 111 -> 61; 64 steps of 30 011 envs of all families
+// 301 -> 281, of 65 536 KeyCorridor envs 213 -> 173.  Step kernels for batches
+// without KeyCorridor leave it out: the code would cost each of their steps
+// 1-3 % (4096 Empty 8x8 240 -> 247 us for 256 steps).
 __device__ __forceinline__ void connect_few(uint32_t (&kd)[3], uint32_t rl, const KcRest& rest, uint32_t meta,
                                             uint2 seed, uint32_t rng_id, uint32_t episode) {
   const uint64_t few = __ballot(rest.todo != 0u);
@@ -2001,7 +2002,7 @@ struct FusedArgs {
 // load consumed in the same step would also wait for every earlier record
 // store: the action of step s + 1 is therefore fetched during step s, and
 // the policy variant has no loads in its step loop at all.
-template <bool kActions, bool kServe, int kObs, bool kSplit>
+template <bool kActions, bool kServe, int kObs, bool kSplit, bool kTogether = false>
 __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs a) {
   // first-person variants: the byte masks of a row's visibility bits.  The
   // stage holds, one after another, the words of layouts being drawn, the
@@ -2166,7 +2167,7 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
     // tile's are laid out here instead)
     g0 = bcast64(goff, 0);
     if (fresh) {
-      draw_missing(next, have_next, active, active, meta, seed, rid, 0u, stage_words + lane);
+      draw_missing<kTogether>(next, have_next, active, active, meta, seed, rid, 0u, stage_words + lane);
       if (active) start_episode(next, fam, x, y, dir, ob);
       fill_grids(__ballot(active), false, next, meta, codes, my_off, lane);
       have_next = false;
@@ -2206,7 +2207,7 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       if (pending) {
         // in the launch's last step only for the lanes that reset: nothing is
         // kept for the next launch
-        draw_missing(next, have_next, do_reset, s + 1 < steps ? active : do_reset, meta, seed, rid, episode + 1u,
+        draw_missing<kTogether>(next, have_next, do_reset, s + 1 < steps ? active : do_reset, meta, seed, rid, episode + 1u,
                      stage_words + lane);
         const bool kept = filled && keeps_base(fam);
         if (most_balls != 0 && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
@@ -2495,11 +2496,19 @@ hipError_t launch_fused(const EnvTables& env, const TileTables& tiles, const Sta
       {&k_fused<true, false, 0, false>, &k_fused<true, false, 1, false>, &k_fused<true, false, 2, false>}};
   static const FusedKernel split[2][2] = {{&k_fused<false, false, 0, true>, &k_fused<false, false, 1, true>},
                                           {&k_fused<true, false, 0, true>, &k_fused<true, false, 1, true>}};
+  // first-person records of batches with KeyCorridor envs: connect_few (see there)
+  static const FusedKernel together[2][2][2] = {
+      {{&k_fused<false, false, 0, false, true>, &k_fused<false, false, 1, false, true>},
+       {&k_fused<true, false, 0, false, true>, &k_fused<true, false, 1, false, true>}},
+      {{&k_fused<false, false, 0, true, true>, &k_fused<false, false, 1, true, true>},
+       {&k_fused<true, false, 0, true, true>, &k_fused<true, false, 1, true, true>}}};
   const int with = actions ? 1 : 0;
-  if (grid_blocks <= kSplitBlocks && obs < 2 && (serve || out.obs) &&
-      fused_lds_bytes(tiles.max_tile_cells) + kSplitLds <= 160 * 1024)
-    return launch_tiles(serve ? &k_fused<false, true, 0, true> : split[with][obs], a, grid_blocks, 2 * kWave, stream);
-  return launch_tiles(serve ? &k_fused<false, true, 0, false> : kernels[with][obs], a, grid_blocks, kWave, stream);
+  const bool pair = grid_blocks <= kSplitBlocks && obs < 2 && (serve || out.obs) &&
+                    fused_lds_bytes(tiles.max_tile_cells) + kSplitLds <= 160 * 1024;
+  FusedKernel fn = pair ? split[with][obs & 1] : kernels[with][obs];
+  if (tiles.corridors && obs < 2) fn = together[pair ? 1 : 0][with][obs & 1];
+  if (serve) fn = pair ? &k_fused<false, true, 0, true> : &k_fused<false, true, 0, false>;
+  return launch_tiles(fn, a, grid_blocks, pair ? 2 * kWave : kWave, stream);
 }
 
 hipError_t launch_reset(const EnvTables& env, const TileTables& tiles, const StateBufs& st, const TrajBufs& out,

@@ -53,6 +53,7 @@ struct TileTables {
   int32_t tile_envs = 64;     // E, 1..64
   int32_t parts_log2 = 0;     // serving: a listed tile of 64 slots is run as 64 / E tiles; n_tiles counts
                               // these
+  bool corridors = false;     // some env is a KeyCorridor
 };
 
 // Envs per tile of a launch whose caller has not chosen (env_set_tiling,

@@ -20,6 +20,7 @@ struct gx_ctx {
   int32_t reward_mode = 0;
   int32_t obs_mode = 0;
   bool balls = false;            // some env's obstacles move
+  bool corridors = false;        // some env is a KeyCorridor
   bool calm = true;              // Empty, DoorKey and FourRooms only: resets are rare
   uint64_t grid_bytes = 0;
   bool has_reset = false;
@@ -116,8 +117,8 @@ struct LaunchShape {
 };
 
 LaunchShape launch_shape(const gx_ctx* c) {
-  if (c->shape_chosen) return {{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs}, c->blocks};
-  return {{c->auto_tiles, c->auto_cells, nullptr, c->auto_envs}, c->auto_tiles};
+  if (c->shape_chosen) return {{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs, 0, c->corridors}, c->blocks};
+  return {{c->auto_tiles, c->auto_cells, nullptr, c->auto_envs, 0, c->corridors}, c->auto_tiles};
 }
 
 // Workgroups of a launch of k steps writing first-person records.  Long launches
@@ -312,6 +313,7 @@ int env_create(const gx_config* cfg, gx_ctx** out) {
   }
   for (int32_t i = 0; i < n; ++i) {
     c->balls = c->balls || cfg->family[i] == GX_FAMILY_DYNOBS;
+    c->corridors = c->corridors || cfg->family[i] == GX_FAMILY_KEYCORRIDOR;
     c->calm = c->calm && cfg->family[i] <= GX_FAMILY_FOURROOMS;
   }
   for (int32_t i = 0; rc == GX_OK && i < n; ++i) c->cells[i] = (int32_t)cfg->side[i] * (int32_t)cfg->side[i];

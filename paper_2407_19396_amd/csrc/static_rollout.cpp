@@ -88,10 +88,12 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
   // the tiles a context's launches and resets run (the latter are the former
   // or halves of them)
   const int32_t tile_envs = gx::launch_tile_envs(n), reset_envs = gx::reset_tile_envs(n);
+  bool corridors = false;
   int32_t max_tile_cells = 0, tile_cells = 0, max_reset_cells = 0, reset_cells = 0;
   for (int32_t i = 0; i < n; ++i) {
     const int fam = cfg->family[i], S = cfg->side[i], P = cfg->param ? cfg->param[i] : 0;
     if (!gx::family_ok(fam, S, P, 32) || cfg->max_steps[i] < 1) return GX_EINVAL;
+    corridors = corridors || fam == GX_FAMILY_KEYCORRIDOR;
     meta[i] = (uint32_t)fam | ((uint32_t)S << 8) | ((uint32_t)P << 16);
     max_steps[i] = cfg->max_steps[i];
     const uint64_t sd = cfg->seed ? cfg->seed[i] : cfg->seed_all;
@@ -143,7 +145,7 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
   const gx::StateBufs sb{st->grid, st->x,       st->y,         st->dir,   st->t,
                          st->carry, st->episode, st->done_prev, st->calls, st->obst};
   const int32_t n_tiles = (n + tile_envs - 1) / tile_envs;
-  const gx::TileTables tiles{n_tiles, max_tile_cells, nullptr, tile_envs};
+  const gx::TileTables tiles{n_tiles, max_tile_cells, nullptr, tile_envs, 0, corridors};
   if (reset) {
     gx::TrajBufs fb{nullptr, nullptr, nullptr, nullptr, 1};
     if (first) fb = gx::TrajBufs{first->obs, first->reward, first->flags, first->action, first->rows, obs_row,

@@ -182,8 +182,9 @@ def test_long_rollouts_of_many_tiles(n, steps):
     env.close()
 
 
+@pytest.mark.parametrize("obs_mode", [0, 1, 2])
 @pytest.mark.parametrize("n,together", [(7, 7), (64, 64), (320, 9), (320, 8), (3000, 40)])
-def test_corridors_connected_by_few_lanes(n, together):
+def test_corridors_connected_by_few_lanes(n, together, obs_mode):
     """Waves with few, exactly eight, nine and only KeyCorridor envs: layouts
     whose last doors the wave looks for together."""
     import torch
@@ -196,8 +197,8 @@ def test_corridors_connected_by_few_lanes(n, together):
                         np.arange(n, dtype=np.uint32), "corridors",
                         np.where(corridor, rng.integers(1, 4, n), 0).astype(np.uint8))
     steps = 30
-    b, s, first = P.oracle_reset(table, 0, 2)
-    env = ge.GridEnv(table, obs_mode=2)
+    b, s, first = P.oracle_reset(table, 0, obs_mode)
+    env = ge.GridEnv(table, obs_mode=obs_mode)
     env.set_tiling(64)
     row = env.traj(1)
     env.reset(row)
