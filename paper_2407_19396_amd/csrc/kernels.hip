@@ -839,7 +839,9 @@ __device__ __forceinline__ bool is_door_code(uint32_t code) {
   return (code & 15u) == kDoor || (code & 0x8Fu) == (0x80u | kKey);
 }
 
-// The transition of move_obstacles on codes, one ball after another.  A
+// The transition system of Dynamic-Obstacles (Table "systems"; Fig. 1) on codes:
+// every ball, in list order, moves to a uniformly drawn empty cell of the 8
+// around it that the agent does not occupy, or stays if there is none.  A
 // ball's 3x3 block is three rows of two aligned words; an exact-match mask of
 // the rows' bytes and three dot products give its 8 neighbours as bits (7-14,
 // row-major, the ball's own cell skipped), and a table (kth_cell, by mask)
@@ -870,6 +872,28 @@ __device__ __forceinline__ void build_kth_table(uint32_t* table, int lane) {
   }
 }
 
+// Bits of a ball's 8 neighbours among the mask of a 3x3 block (7-14), taken a
+// row at a time: row r's three codes are the low bytes of w, empty cells'
+// bits are added to mask.
+template <int r>
+__device__ __forceinline__ uint32_t empty_neighbours(uint32_t w, uint32_t mask) {
+  // bytes equal to kCodeEmpty: zero after the exclusive or; bit 7 of each byte
+  // of ((v & 0x7F) + 0x7F) | v is clear exactly there
+  const uint32_t v = w ^ (kCodeEmpty * 0x01010101u);
+  const uint32_t empty = ~(((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v) & 0x80808080u;
+  constexpr uint32_t kPlaces[3] = {0x00040201u, 0x00100008u, 0x00804020u};
+  return __builtin_amdgcn_udot4(empty, kPlaces[r], mask, false);
+}
+
+// The cell a ball at (bx, by) moves to: the free neighbour that `word` picks.
+__device__ __forceinline__ void ball_target(uint32_t mask, uint32_t word, const uint32_t* kth, uint32_t bx,
+                                            uint32_t by, uint32_t& nx, uint32_t& ny) {
+  const uint32_t k = bounded(word, (uint32_t)__builtin_popcount(mask));
+  const uint32_t v = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(kth) + (mask >> 5)) >> (4u * k);
+  nx = bx + (v & 3u) - 1u;
+  ny = by + ((v >> 2) & 3u) - 1u;
+}
+
 // at: byte offset of the env's grid in `lds`, pos: the agent's cell in it,
 // most: the largest n of the wave
 __device__ __forceinline__ void move_balls(uint8_t* lds, int at, int S, int n, int most, int pos, uint32_t (&ob)[4],
@@ -887,22 +911,17 @@ __device__ __forceinline__ void move_balls(uint8_t* lds, int at, int S, int n, i
       const uint32_t bx = xy & 0xFFu, by = xy >> 8;
       const bool ok = b < n && max(bx - 1u, by - 1u) < inner;
       const int cell = at + (ok ? (int)(by * (uint32_t)S + bx) : S + 1);
-      uint32_t mask = 0;
-#pragma unroll
-      for (int r = 0; r < 3; ++r) {
+      auto row = [&](int r) {
         const int o = cell + (r - 1) * S - 1;
         const uint32_t* p = reinterpret_cast<const uint32_t*>(lds + (o & ~3));
-        // bytes equal to kCodeEmpty: zero after the exclusive or; bit 7 of
-        // each byte of ((v & 0x7F) + 0x7F) | v is clear exactly there
-        const uint32_t v = __builtin_amdgcn_alignbyte(p[1], p[0], (uint32_t)o & 3u) ^ (kCodeEmpty * 0x01010101u);
-        const uint32_t empty = ~(((v & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | v) & 0x80808080u;
-        constexpr uint32_t kPlaces[3] = {0x00040201u, 0x00100008u, 0x00804020u};
-        mask = __builtin_amdgcn_udot4(empty, kPlaces[r], mask, false);
-      }
+        return __builtin_amdgcn_alignbyte(p[1], p[0], (uint32_t)o & 3u);
+      };
+      uint32_t mask = empty_neighbours<0>(row(0), 0u);
+      mask = empty_neighbours<1>(row(1), mask);
+      mask = empty_neighbours<2>(row(2), mask);
       mask = ok ? mask : 0u;
-      const uint32_t k = bounded(word, (uint32_t)__builtin_popcount(mask));
-      const uint32_t v = *reinterpret_cast<const uint32_t*>(reinterpret_cast<const uint8_t*>(kth) + (mask >> 5)) >> (4u * k);
-      const uint32_t nx = bx + (v & 3u) - 1u, ny = by + ((v >> 2) & 3u) - 1u;
+      uint32_t nx, ny;
+      ball_target(mask, word, kth, bx, by, nx, ny);
       const bool from_agent = cell == at + pos;   // a malformed state's ball under the agent
       if (mask) {
         under = from_agent ? (uint8_t)kCodeEmpty : under;
@@ -1708,8 +1727,9 @@ __device__ __forceinline__ int wave_excl_scan(int v, int lane, int& total) {
 
 // ---------------------------------------------------------------------------
 // Plain kernel: one step of every env per launch, state and grids in HBM, the
-// first-person record modes (or none) of families without moving balls; the
-// other steps run k_fused for one step, which stages whole grids.
+// first-person record modes or none.  Whole-grid records, and moving balls
+// where reading every grid costs less than their trips to HBM (step_in_hbm),
+// run k_fused for one step.
 //
 // The view is read as soon as the action is known, before it is applied: a
 // step ends in one of at most two 7x7 squares (a turn: the new heading's;
@@ -1771,6 +1791,49 @@ __device__ __forceinline__ void store_code(uint8_t* p, uint32_t code) {
   p[2] = (uint8_t)c.state;
 }
 
+__device__ __forceinline__ uint32_t load_code(const uint8_t* p) {
+  return code_of((uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16));
+}
+
+// move_balls on a grid in HBM (at g, the agent at (x, y)): bound by latency, one
+// trip per ball for the three rows of nine bytes around it, but no byte of any
+// other env's grid.  One step of Empty 31x31 with 1 % Dynamic-Obstacles, 262 144
+// envs: 44 us, without records 15 (464 and 447 with every grid staged in LDS);
+// 65 536 FourRooms 19x19 with 1 %: 13.6 (27).
+__device__ __forceinline__ void move_balls_hbm(uint8_t* g, int S, int n, int x, int y, uint32_t (&ob)[4], uint2 seed,
+                                               uint32_t rng_id, uint32_t call, const uint32_t* kth) {
+  const uint32_t inner = (uint32_t)(S - 2);
+  uint4 blk[2] = {make_uint4(rng_id, call, 0u, 2u), make_uint4(rng_id, call, 1u, 2u)};
+  philox10<2>(blk, seed);
+#pragma unroll
+  for (int b = 0; b < kMaxObst; ++b) {
+    const uint32_t xy = obst_at(ob, b);
+    const uint32_t bx = xy & 0xFFu, by = xy >> 8;
+    if (b >= n || max(bx - 1u, by - 1u) >= inner) continue;
+    uint8_t* cell = g + 3u * (by * (uint32_t)S + bx);
+    u32x2_any lo[3];
+    uint32_t hi[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const uint8_t* p = cell + 3 * ((r - 1) * S - 1);
+      lo[r] = *reinterpret_cast<const u32x2_any*>(p);
+      hi[r] = p[8];
+    }
+    uint32_t mask = empty_neighbours<0>(encode_cells(lo[0].x, lo[0].y, hi[0]), 0u);
+    mask = empty_neighbours<1>(encode_cells(lo[1].x, lo[1].y, hi[1]), mask);
+    mask = empty_neighbours<2>(encode_cells(lo[2].x, lo[2].y, hi[2]), mask);
+    // the agent's cell, if it is one of the eight, is taken
+    const uint32_t ax = (uint32_t)x - bx + 1u, ay = (uint32_t)y - by + 1u, at = 3u * ay + ax;
+    mask &= max(ax, ay) < 3u && at != 4u ? ~(1u << (7u + at - (at > 4u ? 1u : 0u))) : ~0u;
+    if (!mask) continue;
+    uint32_t nx, ny;
+    ball_target(mask, pick4(blk[b >> 2], (uint32_t)(b & 3)), kth, bx, by, nx, ny);
+    store_code(cell, kCodeEmpty);
+    store_code(g + 3u * (ny * (uint32_t)S + nx), kCodeBall);
+    obst_set(ob, b, nx, ny);
+  }
+}
+
 // Lays out the grids of the lanes in `pending` (a lane's grid at g in HBM) by
 // way of `buf`, as many at a time as it holds.
 constexpr int kNewGridBytes = 4096;   // at least one grid of side 32
@@ -1808,11 +1871,14 @@ struct PlainArgs {
 };
 
 // kObs: 0 symbolic, 1 categorical first person, 2 no observations
-template <int kObs>
+// kBalls: some env is a Dynamic-Obstacles; its balls move in HBM before the
+// view is read
+template <int kObs, bool kBalls>
 __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
   __shared__ __align__(16) uint2 masks[kObs == 2 ? 1 : kMaskEntries];
   __shared__ __align__(16) uint32_t stage_words[kViewStageBytes / 4];   // and the draw window, before
   __shared__ __align__(16) uint8_t new_grids[kNewGridBytes + 16];
+  __shared__ __align__(16) uint32_t kth_cell[kBalls ? kMaskPatterns : 1];
   const int lane = threadIdx.x;
   const int N = a.env.n;
   const int e0 = (int)blockIdx.x * a.tile_envs, e = e0 + lane;
@@ -1845,6 +1911,10 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
     fam = meta & 0xFF;
     S = (int)((meta >> 8) & 0xFF);
     if (fam == kFamGoToDoor) ob[0] = *reinterpret_cast<const uint32_t*>(a.st.obst + 16 * (size_t)e);   // the mission
+    if (kBalls && fam == kFamDynObs) {
+      const uint4 o4 = *reinterpret_cast<const uint4*>(a.st.obst + 16 * (size_t)e);
+      ob[0] = o4.x; ob[1] = o4.y; ob[2] = o4.z; ob[3] = o4.w;
+    }
   }
   if (kObs != 2) build_mask_table(masks, lane);
   const bool do_reset = active && done_prev;
@@ -1868,12 +1938,25 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
   const bool live = active && !do_reset;
   if (!a.actions) act = bounded(pick4(policy_block(seed, rid, calls), calls & 3u), 7u);
   act = live ? act : 6u;
+  const uint32_t dir2 = 2u * (uint32_t)dir;
+  const int dx = (int)((0x46u >> dir2) & 3u) - 1, dy = (int)((0x19u >> dir2) & 3u) - 1;
+  const bool balls = kBalls && fam == kFamDynObs && live;
+  uint32_t penalty = 0;
+  if (kBalls && __ballot(balls)) {
+    build_kth_table(kth_cell, lane);
+    wave_sync();
+    if (balls) {
+      // three actions; the cell ahead is judged before the balls move
+      act = act > kForward ? kLeft : act;
+      const uint32_t before = load_code(g + 3 * (min(max(y + dy, 0), S - 1) * S + min(max(x + dx, 0), S - 1)));
+      penalty = (act == kForward && before != kCodeEmpty && (before & 0x8Fu) != kGoal) ? 1u : 0u;
+      move_balls_hbm(g, S, (int)((meta >> 16) & 255u), x, y, ob, seed, rid, calls, kth_cell);
+    }
+  }
   const uint32_t a6 = min(act, 6u);
 
   // the cell ahead, and the rows of the view
   const int dir_f = (dir + (int)((7u >> (2u * a6)) & 3u)) & 3;   // left 3, right 1
-  const uint32_t dir2 = 2u * (uint32_t)dir;
-  const int dx = (int)((0x46u >> dir2) & 3u) - 1, dy = (int)((0x19u >> dir2) & 3u) - 1;
   const bool vert = (dir_f & 1) != 0;
   uint32_t rlo[8], rhi[8], front;
   if (kObs != 2) {
@@ -1882,8 +1965,7 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
               back ? -1 : 1, e == 0 || !active, e == N - 1 || !active, rlo, rhi);
     front = vert ? rlo[6] >> 24 : ((dir_f == 0 ? rlo[3] >> 8 : rhi[3] >> 16) & 255u);
   } else {
-    const uint8_t* p = g + 3 * (min(max(y + dy, 0), S - 1) * S + min(max(x + dx, 0), S - 1));
-    front = code_of((uint32_t)p[0] | ((uint32_t)p[1] << 8) | ((uint32_t)p[2] << 16));
+    front = load_code(g + 3 * (min(max(y + dy, 0), S - 1) * S + min(max(x + dx, 0), S - 1)));
   }
 
   const CodeAction r = act_on_code(a6, carry_code, front);
@@ -1892,7 +1974,8 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
   const int ahead = (y + dy) * S + x + dx;
   x += (int)(walked & (uint32_t)dx);
   y += (int)(walked & (uint32_t)dy);
-  uint32_t goal = r.goal, ended = goal | r.lava;
+  penalty |= r.lava;
+  uint32_t goal = r.goal, ended = goal | penalty;
   const uint32_t patch = a6 > kForward ? r.ok : 0u;   // a pickup, drop or toggle changed the cell ahead
   bool edge_view = false;
   if (fam == kFamGoToDoor && live) {
@@ -1913,7 +1996,7 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
   t += live ? 1 : 0;
   const uint32_t trunc = (live && t >= T) ? 1u : 0u;
   float reward = 0.0f;
-  if (__ballot(ended != 0u)) reward = r.lava ? -1.0f : (goal ? goal_reward(t, T, a.env.reward_mode) : 0.0f);
+  if (__ballot(ended != 0u)) reward = penalty ? -1.0f : (goal ? goal_reward(t, T, a.env.reward_mode) : 0.0f);
   const uint32_t flags = do_reset ? kFlagFirst : ended * kFlagTerminated | trunc * kFlagTruncated;
   const size_t row0 = (size_t)a.row * (size_t)N + (size_t)e0;
 
@@ -1951,7 +2034,7 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
     a.st.episode[e] = episode;
     a.st.done_prev[e] = (ended | trunc) != 0u ? 1 : 0;
     a.st.calls[e] = calls + 1u;
-    if (do_reset)
+    if (do_reset || balls)
       *reinterpret_cast<uint4*>(a.st.obst + 16 * (size_t)e) = make_uint4(ob[0], ob[1], ob[2], ob[3]);
   }
 }
@@ -2446,13 +2529,14 @@ size_t fused_lds_bytes(int32_t max_tile_cells) {
 }
 
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
-                        const TrajBufs& out, int32_t row, hipStream_t stream) {
+                        const TrajBufs& out, int32_t row, bool balls, hipStream_t stream) {
   using PlainKernel = void (*)(PlainArgs);
-  static const PlainKernel kernels[3] = {&k_plain<0>, &k_plain<1>, &k_plain<2>};
+  static const PlainKernel kernels[2][3] = {{&k_plain<0, false>, &k_plain<1, false>, &k_plain<2, false>},
+                                            {&k_plain<0, true>, &k_plain<1, true>, &k_plain<2, true>}};
   const int32_t tile_envs = launch_tile_envs(env.n);
   const PlainArgs a{env, st, actions, out, row, tile_envs};
   const int blocks = (env.n + tile_envs - 1) / tile_envs;
-  hipLaunchKernelGGL(kernels[out.obs ? env.obs_mode : 2], dim3(blocks), dim3(kWave), 0, stream, a);
+  hipLaunchKernelGGL(kernels[balls ? 1 : 0][out.obs ? env.obs_mode : 2], dim3(blocks), dim3(kWave), 0, stream, a);
   return hipGetLastError();
 }
 

@@ -82,6 +82,21 @@ inline int32_t reset_tile_envs(int64_t n_envs) {
   return e < 32 ? e : 32;
 }
 
+// Whether one step of a batch with Dynamic-Obstacles envs moves its balls in HBM
+// (k_plain) rather than in the LDS of a one-step fused launch, which reads
+// every grid of the batch whole.  A ball in HBM is a trip of its own, about
+// what staging 40 cells costs; a step that writes records gains from LDS up to
+// 4096 cells a tile.  us, fused / plain, 1 % of the envs with 4 balls: side 8,
+// 262 144 envs without records 24.6 / 14.0, with 29.7 / 24.2, 4096 envs 8.1 /
+// 8.7; side 16, 65 536 envs 21.4 / 12.2; side 31, 262 144 envs 472 / 44, 4096
+// envs 11.6 / 9.3.  Every env with 8 balls: side 8, 262 144 envs 45 / 83, side 16
+// 108 / 125, side 24 396 / 232.  All families: 262 144 envs 50 / 38, 4096 envs
+// 11.9 / 12.9, without records 45 / 31 and 11.2 / 10.8.
+inline bool step_in_hbm(int32_t n_envs, int64_t cells, int64_t balls, bool records) {
+  const int64_t tile = launch_tile_envs(n_envs) < n_envs ? launch_tile_envs(n_envs) : n_envs;
+  return tile * (cells - 40 * balls) > (records ? 4096 * (int64_t)n_envs : 0);
+}
+
 // A tile of 64 slots serving one request (device memory, 64 bytes).  The
 // tile's envs are slots [tile * 64, tile * 64 + n_envs); their grids are
 // contiguous from the first slot's on.  The record of the request's step r for its
@@ -132,11 +147,11 @@ inline bool family_ok(int family, int side, int param, int max_side) {
   }
 }
 
-// One launch of the plain kernel: one step of every env of a batch without
-// Dynamic-Obstacles envs, records first person (obs_mode 0, 1) or none
-// (out.obs nullptr).  Writes output row `row`.
+// One launch of the plain kernel: one step of every env, records first person
+// (obs_mode 0, 1) or none (out.obs nullptr).  balls: some env is a
+// Dynamic-Obstacles.  Writes output row `row`.
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
-                        const TrajBufs& out, int32_t row, hipStream_t stream);
+                        const TrajBufs& out, int32_t row, bool balls, hipStream_t stream);
 
 // One launch of the reset kernel: the start of episode 0 of every env, its
 // first timestep in row 0 of `out` (obs may be nullptr; reward nullptr: no

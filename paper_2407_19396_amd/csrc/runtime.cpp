@@ -19,7 +19,8 @@ struct gx_ctx {
   int32_t n = 0;
   int32_t reward_mode = 0;
   int32_t obs_mode = 0;
-  bool balls = false;            // some env's obstacles move
+  int64_t balls = 0;             // moving obstacles of all envs
+  int64_t n_cells = 0;           // cells of all envs
   bool corridors = false;        // some env is a KeyCorridor
   bool calm = true;              // Empty, DoorKey and FourRooms only: resets are rare
   uint64_t grid_bytes = 0;
@@ -312,7 +313,8 @@ int env_create(const gx_config* cfg, gx_ctx** out) {
     rc = GX_ENOMEM;
   }
   for (int32_t i = 0; i < n; ++i) {
-    c->balls = c->balls || cfg->family[i] == GX_FAMILY_DYNOBS;
+    c->balls += cfg->family[i] == GX_FAMILY_DYNOBS ? cfg->param[i] : 0;
+    c->n_cells += (int64_t)cfg->side[i] * cfg->side[i];
     c->corridors = c->corridors || cfg->family[i] == GX_FAMILY_KEYCORRIDOR;
     c->calm = c->calm && cfg->family[i] <= GX_FAMILY_FOURROOMS;
   }
@@ -408,14 +410,15 @@ int env_step(gx_ctx* c, const gx_state* st, const uint8_t* actions, const gx_tra
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   const bool stg = staged(c, out);
   const gx::TrajBufs tb = stg ? stage_traj(c) : traj_of(c, out);
-  // whole-grid records and moving balls want the grid in LDS: one step of the
-  // fused kernel (65 536 envs: whole grids of the mixed batch 87 -> 21 us a
-  // step, their types 37 -> 20, Dynamic-Obstacles 40 -> 24)
+  // whole-grid records want the grid in LDS: one step of the fused kernel
+  // (65 536 envs: whole grids of the mixed batch 87 -> 21 us a step, their
+  // types 37 -> 20), and so may moving balls (gx::step_in_hbm)
   const LaunchShape shape = launch_shape(c);
-  const bool fused = c->balls || (tb.obs && step_obs_mode(c) >= 2);
+  const bool fused = (tb.obs && step_obs_mode(c) >= 2) ||
+                     (c->balls && !gx::step_in_hbm(c->n, c->n_cells, c->balls, tb.obs != nullptr));
   const hipError_t err =
       fused ? gx::launch_fused(tables_of(c), shape.tiles, state_of(st), actions, 1, tb, 0, shape.blocks, s)
-            : gx::launch_plain(tables_of(c), state_of(st), actions, tb, 0, s);
+            : gx::launch_plain(tables_of(c), state_of(st), actions, tb, 0, c->balls != 0, s);
   if (err != hipSuccess) return GX_EDEVICE;
   if (stg && render_rows(c, 1, out, 0, s) != hipSuccess) return GX_EDEVICE;
   return GX_OK;

@@ -1,0 +1,110 @@
+"""Which kernel, tiles and workgroups a call launches: the host runtime built
+with recording stubs in place of HIP and the kernels (launch_recorder.cpp), so
+that rules on batch size, grid sides and families are checked without a GPU."""
+import ctypes
+import os
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_2407_19396_amd import gridenv as ge
+from paper_2407_19396_amd import workloads as wl
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+CSRC = os.path.join(os.path.dirname(HERE), "paper_2407_19396_amd", "csrc")
+KINDS = ("plain", "fused", "reset")
+
+
+class Launch(ctypes.Structure):
+    _fields_ = [(f, ctypes.c_int32) for f in ("kind", "tile_envs", "n_tiles", "blocks", "max_cells", "steps",
+                                              "balls", "corridors")]
+
+
+@pytest.fixture(scope="module")
+def lib(tmp_path_factory):
+    out = str(tmp_path_factory.mktemp("routes") / "recorder.so")
+    src = [os.path.join(HERE, "launch_recorder.cpp")] + [os.path.join(CSRC, f) for f in (
+        "runtime.cpp", "server.cpp", "static_rollout.cpp")]
+    subprocess.run(["g++", "-std=c++17", "-O1", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__",
+                    "-D__align__(n)=__attribute__((aligned(n)))", "-DHIP_SYMBOL(x)=x", "-I/opt/rocm/include",
+                    "-I", CSRC, *src, "-o", out], check=True)
+    return ctypes.CDLL(out)
+
+
+class Batch:
+    """A context of the recorded runtime; its calls return what they launched."""
+
+    def __init__(self, lib, table, obs_mode=0):
+        self.lib, self.n = lib, table.n
+        self.keep = [np.ascontiguousarray(a) for a in (table.family, table.side, table.param, table.max_steps)]
+        fam, side, par, ms = (a.ctypes.data for a in self.keep)
+        self.cfg = ge.GxConfig(table.n, 0, obs_mode, fam, side, par, ms, None, 0, None, None)
+        self.ctx = ctypes.c_void_p()
+        assert lib.env_create(ctypes.byref(self.cfg), ctypes.byref(self.ctx)) == ge.GX_OK
+        self.st = ge.GxState(*([16] * len(ge.STATE_FIELDS)))
+        self.reset()
+
+    def _took(self, rc):
+        assert rc == ge.GX_OK
+        buf = (Launch * 64)()
+        n = self.lib.rec_take(buf, 64)
+        return [{f: getattr(buf[i], f) for f, _ in Launch._fields_} | {"kind": KINDS[buf[i].kind]} for i in range(n)]
+
+    def _out(self, obs, rows=1):
+        return ctypes.byref(ge.GxTraj(16 if obs else None, 16, 16, 16, rows, None))
+
+    def reset(self):
+        return self._took(self.lib.env_reset(self.ctx, ctypes.byref(self.st), None, None))
+
+    def step(self, obs=True):
+        return self._took(self.lib.env_step(self.ctx, ctypes.byref(self.st), None, self._out(obs), None))
+
+    def rollout(self, steps, K=0, obs=True):
+        return self._took(self.lib.env_rollout(self.ctx, ctypes.byref(self.st), steps, None, self._out(obs, steps),
+                                               K, None))
+
+    def set_tiling(self, tile_envs):
+        assert self.lib.env_set_tiling(self.ctx, tile_envs) == ge.GX_OK
+
+    def set_launch(self, K, blocks=0):
+        assert self.lib.env_set_launch(self.ctx, K, blocks) == ge.GX_OK
+
+    def info(self):
+        i = ge.GxInfo()
+        assert self.lib.env_info(self.ctx, ctypes.byref(i)) == ge.GX_OK
+        return i
+
+    def close(self):
+        assert self.lib.env_destroy(self.ctx) == ge.GX_OK
+
+
+def some_balls(n, side, every, balls):
+    t = wl.uniform_table(n, wl.FAMILY_EMPTY, side)
+    t.family[::every] = wl.FAMILY_DYNOBS
+    t.param[::every] = balls
+    return t
+
+
+@pytest.mark.parametrize("n,side,every,balls,obs,kind", [
+    (262144, 31, 101, 4, True, "plain"), (262144, 16, 101, 4, True, "plain"), (65536, 19, 101, 4, True, "plain"),
+    (262144, 8, 101, 4, False, "plain"), (4096, 31, 101, 4, False, "plain"), (16, 8, 101, 4, False, "plain"),
+    (262144, 24, 1, 8, True, "plain"), (262144, 8, 1, 8, True, "fused"), (65536, 8, 1, 4, True, "fused"),
+    (4096, 16, 101, 4, True, "fused"), (16, 8, 1, 2, True, "fused"), (262144, 8, 1, 8, False, "fused")])
+def test_steps_with_moving_balls(lib, n, side, every, balls, obs, kind):
+    """A few moving balls must not make a step read every grid of the batch."""
+    b = Batch(lib, some_balls(n, side, every, balls))
+    (step,) = b.step(obs)
+    assert step["kind"] == kind and step["steps"] == 1
+    assert kind == "fused" or step["balls"] == 1
+    b.close()
+
+
+@pytest.mark.parametrize("obs_mode", [0, 1, 2, 3])
+def test_steps_without_balls(lib, obs_mode):
+    b = Batch(lib, wl.mixed_table(5000), obs_mode)
+    (step,) = b.step()
+    assert step["kind"] == ("plain" if obs_mode < 2 else "fused") and step["balls"] == 0
+    (step,) = b.step(obs=False)
+    assert step["kind"] == "plain"
+    b.close()
