@@ -266,14 +266,14 @@ int env_step(gx_ctx* ctx, const gx_state* st, const uint8_t* actions, const gx_t
 int env_rollout(gx_ctx* ctx, const gx_state* st, int32_t n_steps, const uint8_t* actions,
                 const gx_traj* traj, int32_t K, void* stream);
 
-/* Set the fused kernel's launch shape: steps per launch (K >= 1) and
+/* Set the rollouts' launch shape: steps per launch (K >= 1) and
  * workgroups (blocks >= 1; 0 keeps the current value).  Fewer workgroups
  * than tiles are persistent: workgroup b takes tiles b, b + blocks, ...
  * The default is one workgroup per tile. */
 int env_set_launch(gx_ctx* ctx, int32_t K, int32_t blocks);
 
-/* Set the fused kernel's tiling: tiles of tile_envs (1..64, default 64)
- * consecutive envs, one env per lane on a wave's first tile_envs lanes, the
+/* Set the rollouts' tiling (steps and resets keep the library's own): tiles
+ * of tile_envs (1..64, default 64) consecutive envs, one env per lane on a wave's first tile_envs lanes, the
  * tile's grids in the workgroup's LDS.  Fewer envs per tile leave lanes
  * idle but need less LDS per workgroup, so more workgroups fit a compute
  * unit: the trade for large grids (Sec. 4.2 scales the batch; this picks

@@ -117,9 +117,17 @@ struct LaunchShape {
   int32_t blocks;
 };
 
-LaunchShape launch_shape(const gx_ctx* c) {
-  if (c->shape_chosen) return {{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs, 0, c->corridors}, c->blocks};
+// One-step launches always run in the library's own tiles: what a caller
+// chooses (env_set_tiling, env_set_launch) is the rollouts' shape, and 16
+// workgroups that suit a long rollout would take 912 us for one step of 65 536
+// Dynamic-Obstacles envs, 23 in the library's.
+LaunchShape step_shape(const gx_ctx* c) {
   return {{c->auto_tiles, c->auto_cells, nullptr, c->auto_envs, 0, c->corridors}, c->auto_tiles};
+}
+
+LaunchShape rollout_shape(const gx_ctx* c) {
+  if (!c->shape_chosen) return step_shape(c);
+  return {{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs, 0, c->corridors}, c->blocks};
 }
 
 // Workgroups of a launch of k steps writing first-person records.  Long launches
@@ -393,8 +401,7 @@ int env_reset(gx_ctx* c, const gx_state* st, const gx_traj* first, void* stream)
   gx::TrajBufs tb{nullptr, nullptr, nullptr, nullptr, 1};
   if (first) tb = staged(c, first) ? stage_traj(c) : traj_of(c, first);
   const gx::TileTables own{c->reset_tiles, c->reset_cells, nullptr, c->reset_envs};
-  if (gx::launch_reset(tables_of(c), c->shape_chosen ? launch_shape(c).tiles : own, state_of(st), tb, s) != hipSuccess)
-    return GX_EDEVICE;
+  if (gx::launch_reset(tables_of(c), own, state_of(st), tb, s) != hipSuccess) return GX_EDEVICE;
   if (staged(c, first) && render_rows(c, 1, first, 0, s) != hipSuccess) return GX_EDEVICE;
   c->has_reset = true;
   return GX_OK;
@@ -413,7 +420,7 @@ int env_step(gx_ctx* c, const gx_state* st, const uint8_t* actions, const gx_tra
   // whole-grid records want the grid in LDS: one step of the fused kernel
   // (65 536 envs: whole grids of the mixed batch 87 -> 21 us a step, their
   // types 37 -> 20), and so may moving balls (gx::step_in_hbm)
-  const LaunchShape shape = launch_shape(c);
+  const LaunchShape shape = step_shape(c);
   const bool fused = (tb.obs && step_obs_mode(c) >= 2) ||
                      (c->balls && !gx::step_in_hbm(c->n, c->n_cells, c->balls, tb.obs != nullptr));
   const hipError_t err =
@@ -436,7 +443,7 @@ int env_rollout(gx_ctx* c, const gx_state* st, int32_t n_steps, const uint8_t* a
   // rgb: each fused launch fills the staging ring from row 0, then the
   // renderer draws those rows into the caller's ring
   const int32_t k = std::min(K > 0 ? K : c->k_default, stg ? c->stage_rows : INT32_MAX);
-  const LaunchShape shape = launch_shape(c);
+  const LaunchShape shape = rollout_shape(c);
   const bool first_person = traj->obs && step_obs_mode(c) == 0;
   for (int32_t s0 = 0; s0 < n_steps; s0 += k) {
     const int32_t ks = std::min(k, n_steps - s0);

@@ -108,3 +108,24 @@ def test_steps_without_balls(lib, obs_mode):
     (step,) = b.step(obs=False)
     assert step["kind"] == "plain"
     b.close()
+
+
+@pytest.mark.parametrize("obs_mode", [0, 2])
+@pytest.mark.parametrize("tile_envs,launch", [(0, (64, 16)), (1, None), (64, None), (16, (128, 4096))])
+def test_chosen_shapes_are_the_rollouts_alone(lib, tile_envs, launch, obs_mode):
+    """Tiles and workgroups chosen for rollouts change neither steps nor resets."""
+    b = Batch(lib, wl.uniform_table(65536, wl.FAMILY_DYNOBS, 8, param=4), obs_mode)
+    step, reset, rollout = b.step(), b.reset(), b.rollout(4)
+    assert step[0]["kind"] == "fused"
+    if tile_envs:
+        b.set_tiling(tile_envs)
+    if launch:
+        b.set_launch(*launch)
+    assert b.step() == step and b.reset() == reset
+    (chosen,) = b.rollout(4)
+    if tile_envs not in (0, 64):
+        assert chosen["tile_envs"] == tile_envs
+    if launch:
+        assert chosen["blocks"] == launch[1]
+    assert rollout[0]["blocks"] == 1024
+    b.close()
