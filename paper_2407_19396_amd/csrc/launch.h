@@ -82,6 +82,36 @@ inline int32_t reset_tile_envs(int64_t n_envs) {
   return e < 32 ? e : 32;
 }
 
+// Cells of the largest tile of a batch, for each number of envs a tile can be
+// given by the rules above; envs are added in order.
+struct TileCells {
+  static constexpr int32_t kSizes[5] = {4, 8, 16, 32, 64};
+  int32_t sum[5] = {}, most[5] = {};
+  void add(int64_t env, int32_t cells) {
+    for (int i = 0; i < 5; ++i) {
+      sum[i] = env % kSizes[i] ? sum[i] + cells : cells;
+      most[i] = sum[i] > most[i] ? sum[i] : most[i];
+    }
+  }
+  int32_t of(int32_t envs) const {
+    for (int i = 0; i < 5; ++i)
+      if (kSizes[i] == envs) return most[i];
+    return 0;
+  }
+};
+
+// Envs per tile of a launch that reads or lays out every grid once (a reset, one
+// step of the fused kernel): e, or less while a tile holds more than 16 384
+// cells, whose LDS leaves a compute unit only a few single-wave workgroups.  us in
+// tiles of 64 / 32 / 16 / 8, 262 144 envs: resets of Empty 31x31 1159 / 644 / 372
+// / 291, 24x24 532 / 259 / 192 / 161, 16x16 148 / 100 / 84 / 100; one step with
+// grids as types, 31x31 441 / 278 / 207 / 236, 24x24 208 / 140 / 131 / 154, 19x19
+// 107 / 85 / 94 / 131, 16x16 55 / 51 / 61 / 88.
+inline int32_t one_pass_tile_envs(int32_t e, const TileCells& cells) {
+  while (e > TileCells::kSizes[0] && cells.of(e) > 16384) e /= 2;
+  return e;
+}
+
 // Whether one step of a batch with Dynamic-Obstacles envs moves its balls in HBM
 // (k_plain) rather than in the LDS of a one-step fused launch, which reads
 // every grid of the batch whole.  A ball in HBM is a trip of its own, about

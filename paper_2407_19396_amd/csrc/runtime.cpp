@@ -40,8 +40,9 @@ struct gx_ctx {
   // while the caller has chosen neither tiling nor workgroups, launches run
   // in tiles of their own choice (gx::launch_tile_envs)
   bool shape_chosen = false;
-  int32_t auto_envs = 64, auto_tiles = 0, auto_cells = 0;
-  int32_t reset_envs = 32, reset_tiles = 0, reset_cells = 0;   // env_reset's (gx::reset_tile_envs)
+  gx::TileTables auto_tiles{};    // rollouts'
+  gx::TileTables step_tiles{};    // env_step's when it runs the fused kernel
+  gx::TileTables reset_tiles{};   // env_reset's
   std::vector<int32_t> cells;          // S^2 per env, for re-tiling
   // rgb modes: the sprite atlas, and the staging ring of symbolic records
   // (obs [stage_rows][sym_row], then reward, flags, action, mission
@@ -121,12 +122,10 @@ struct LaunchShape {
 // chooses (env_set_tiling, env_set_launch) is the rollouts' shape, and 16
 // workgroups that suit a long rollout would take 912 us for one step of 65 536
 // Dynamic-Obstacles envs, 23 in the library's.
-LaunchShape step_shape(const gx_ctx* c) {
-  return {{c->auto_tiles, c->auto_cells, nullptr, c->auto_envs, 0, c->corridors}, c->auto_tiles};
-}
+LaunchShape step_shape(const gx_ctx* c) { return {c->step_tiles, c->step_tiles.n_tiles}; }
 
 LaunchShape rollout_shape(const gx_ctx* c) {
-  if (!c->shape_chosen) return step_shape(c);
+  if (!c->shape_chosen) return {c->auto_tiles, c->auto_tiles.n_tiles};
   return {{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs, 0, c->corridors}, c->blocks};
 }
 
@@ -360,12 +359,14 @@ int env_create(const gx_config* cfg, gx_ctx** out) {
     return rc;
   }
   set_tiling(c, kTileEnvs);
-  c->auto_envs = gx::launch_tile_envs(n);
-  c->auto_tiles = (n + c->auto_envs - 1) / c->auto_envs;
-  c->auto_cells = largest_tile(c, c->auto_envs);
-  c->reset_envs = gx::reset_tile_envs(n);
-  c->reset_tiles = (n + c->reset_envs - 1) / c->reset_envs;
-  c->reset_cells = largest_tile(c, c->reset_envs);
+  gx::TileCells cells;
+  for (int32_t i = 0; i < n; ++i) cells.add(i, c->cells[i]);
+  const auto tiles_of = [&](int32_t E) {
+    return gx::TileTables{(n + E - 1) / E, cells.of(E), nullptr, E, 0, c->corridors};
+  };
+  c->auto_tiles = tiles_of(gx::launch_tile_envs(n));
+  c->step_tiles = tiles_of(gx::one_pass_tile_envs(gx::launch_tile_envs(n), cells));
+  c->reset_tiles = tiles_of(gx::one_pass_tile_envs(gx::reset_tile_envs(n), cells));
   *out = c;
   return GX_OK;
 }
@@ -400,8 +401,7 @@ int env_reset(gx_ctx* c, const gx_state* st, const gx_traj* first, void* stream)
   const hipStream_t s = reinterpret_cast<hipStream_t>(stream);
   gx::TrajBufs tb{nullptr, nullptr, nullptr, nullptr, 1};
   if (first) tb = staged(c, first) ? stage_traj(c) : traj_of(c, first);
-  const gx::TileTables own{c->reset_tiles, c->reset_cells, nullptr, c->reset_envs};
-  if (gx::launch_reset(tables_of(c), own, state_of(st), tb, s) != hipSuccess) return GX_EDEVICE;
+  if (gx::launch_reset(tables_of(c), c->reset_tiles, state_of(st), tb, s) != hipSuccess) return GX_EDEVICE;
   if (staged(c, first) && render_rows(c, 1, first, 0, s) != hipSuccess) return GX_EDEVICE;
   c->has_reset = true;
   return GX_OK;

@@ -85,11 +85,8 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
   uint32_t* rng_id = reinterpret_cast<uint32_t*>(g_host_tables + kRngOff);
   uint64_t* grid_off = reinterpret_cast<uint64_t*>(g_host_tables + kOffOff);
   uint64_t off = 0;
-  // the tiles a context's launches and resets run (the latter are the former
-  // or halves of them)
-  const int32_t tile_envs = gx::launch_tile_envs(n), reset_envs = gx::reset_tile_envs(n);
   bool corridors = false;
-  int32_t max_tile_cells = 0, tile_cells = 0, max_reset_cells = 0, reset_cells = 0;
+  gx::TileCells cells;
   for (int32_t i = 0; i < n; ++i) {
     const int fam = cfg->family[i], S = cfg->side[i], P = cfg->param ? cfg->param[i] : 0;
     if (!gx::family_ok(fam, S, P, 32) || cfg->max_steps[i] < 1) return GX_EINVAL;
@@ -101,16 +98,7 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
     rng_id[i] = cfg->rng_id ? cfg->rng_id[i] : (uint32_t)i;
     grid_off[i] = off;
     off += 3ull * (uint64_t)S * (uint64_t)S;
-    tile_cells += S * S;
-    reset_cells += S * S;
-    if ((i + 1) % reset_envs == 0 || i + 1 == n) {
-      max_reset_cells = std::max(max_reset_cells, reset_cells);
-      reset_cells = 0;
-    }
-    if ((i + 1) % tile_envs == 0 || i + 1 == n) {
-      max_tile_cells = std::max(max_tile_cells, tile_cells);
-      tile_cells = 0;
-    }
+    cells.add(i, S * S);
   }
 
   int device = -1;
@@ -144,13 +132,17 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
                           cfg->obs_mode};
   const gx::StateBufs sb{st->grid, st->x,       st->y,         st->dir,   st->t,
                          st->carry, st->episode, st->done_prev, st->calls, st->obst};
+  // the tiles of a context's rollouts and resets
+  const int32_t tile_envs = gx::launch_tile_envs(n);
+  const int32_t reset_envs = gx::one_pass_tile_envs(gx::reset_tile_envs(n), cells);
   const int32_t n_tiles = (n + tile_envs - 1) / tile_envs;
-  const gx::TileTables tiles{n_tiles, max_tile_cells, nullptr, tile_envs, 0, corridors};
+  const gx::TileTables tiles{n_tiles, cells.of(tile_envs), nullptr, tile_envs, 0, corridors};
   if (reset) {
     gx::TrajBufs fb{nullptr, nullptr, nullptr, nullptr, 1};
     if (first) fb = gx::TrajBufs{first->obs, first->reward, first->flags, first->action, first->rows, obs_row,
                                  first->mission};
-    const gx::TileTables reset_tiles{(n + reset_envs - 1) / reset_envs, max_reset_cells, nullptr, reset_envs};
+    const gx::TileTables reset_tiles{(n + reset_envs - 1) / reset_envs, cells.of(reset_envs), nullptr, reset_envs,
+                                     0, corridors};
     if (gx::launch_reset(env, reset_tiles, sb, fb, s) != hipSuccess) return GX_EDEVICE;
   }
   if (n_steps == 0) return GX_OK;

@@ -129,3 +129,31 @@ def test_chosen_shapes_are_the_rollouts_alone(lib, tile_envs, launch, obs_mode):
         assert chosen["blocks"] == launch[1]
     assert rollout[0]["blocks"] == 1024
     b.close()
+
+
+@pytest.mark.parametrize("n", [262144, 40000, 9000, 100])
+@pytest.mark.parametrize("side", [4, 8, 16, 17, 24, 31, 32])
+def test_one_pass_launches_of_large_grids(lib, n, side):
+    """A reset or a whole-grid step reads or writes each grid once: its tiles
+    hold at most 16 384 cells, and are not cut without need."""
+    table = wl.uniform_table(n, wl.FAMILY_EMPTY, side)
+    b = Batch(lib, table, 2)
+    (step,), (reset,), (rollout,) = b.step(), b.reset(), b.rollout(2)
+    assert reset["tile_envs"] <= 32
+    for launch, most in ((step, 64), (reset, 32), (rollout, 64)):
+        E = launch["tile_envs"]
+        assert launch["n_tiles"] == launch["blocks"] == -(-n // E)
+        assert launch["max_cells"] == min(E, n) * side * side
+        if launch is not rollout:
+            assert launch["max_cells"] <= 16384
+            assert E == min(rollout["tile_envs"], most) or 2 * E * side * side > 16384
+    b.close()
+
+
+def test_static_rollout_runs_a_contexts_launches(lib):
+    table = wl.uniform_table(70000, wl.FAMILY_TWOROOM, 31)
+    b = Batch(lib, table)
+    tr, n = b._out(True, 200), table.n
+    rc = lib.env_rollout_static(ctypes.byref(b.cfg), ctypes.byref(b.st), 1, tr, 100, None, tr, 0, None)
+    assert b._took(rc) == b.reset() + b.rollout(100)
+    b.close()
