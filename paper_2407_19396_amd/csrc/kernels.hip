@@ -1551,19 +1551,33 @@ __device__ __forceinline__ Next draw_layout(uint32_t f, uint32_t meta, uint2 see
   }
 }
 
-// Gives every lane with `need` set a Next for `episode`, drawing with it
-// those of the lanes of its family that have none (have == false).
-// kTogether: see connect_few.
-template <bool kTogether = false>
+// Steps a launch must have left for KeyCorridor layouts to be drawn ahead, for
+// all of a wave's lanes instead of those that reset.  A KeyCorridor resets
+// every few hundred steps and its draws vary, so that a wave waits for the
+// longest of up to 64: drawn ahead they pay from 16 steps on.  us, ahead from 2 / 8
+// / 16 / 32 steps, KeyCorridor: 65 536 envs, 2 steps 43.7 / 22.9 / 19.6 / 21.7, 8
+// steps 61.8 / 58.7 / 42.8 / 42.5, 64 steps 174 / 173 / 172 / 173 (never: 202);
+// 262 144 envs, 2 steps 70 / 49 / 47 / 48.  The other families draw ahead from two
+// steps on (Crossings, 65 536 envs, 8 steps 40.6 / 45.4 / 50.5 / 51.0; GoToDoor 41.5
+// / 43.5 / 44.7 / 44.7), and kernels for batches without KeyCorridor leave the
+// rule out: in their step loops it costs 1-4 %.
+constexpr int kCorridorsAhead = 16;
+
+// Gives every lane with `need` set a Next for `episode`, drawing with it those
+// of the `active` lanes of its family that have none (have == false).
+// kTogether: see connect_few.  kAhead: KeyCorridors only if `left`, the launch's
+// steps from this one on, are enough.
+template <bool kTogether = false, bool kAhead = false>
 __device__ __forceinline__ void draw_missing(Next& n, bool& have, bool need, bool active, uint32_t meta, uint2 seed,
-                                             uint32_t rng_id, uint32_t episode, uint32_t* words) {
+                                             uint32_t rng_id, uint32_t episode, uint32_t* words, int left = 0) {
   while (true) {
     const uint64_t missing = __ballot(need && !have);
     if (!missing) return;
     const uint32_t f =
         (uint32_t)bcast((int)meta, __ffsll((unsigned long long)missing) - 1) & 255u;
+    const bool draws = kAhead && f == kFamKeyCorridor && left < kCorridorsAhead ? need : active;
     KcRest rest{};
-    if (active && !have && (meta & 255u) == f) {
+    if (draws && !have && (meta & 255u) == f) {
       n = draw_layout<kTogether>(f, opaque(meta), opaque(seed), opaque(rng_id), episode, words, rest);
       have = true;
     }
@@ -2290,8 +2304,8 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       if (pending) {
         // in the launch's last step only for the lanes that reset: nothing is
         // kept for the next launch
-        draw_missing<kTogether>(next, have_next, do_reset, s + 1 < steps ? active : do_reset, meta, seed, rid, episode + 1u,
-                     stage_words + lane);
+        draw_missing<kTogether, kTogether || kServe>(next, have_next, do_reset, s + 1 < steps ? active : do_reset, meta,
+                                                     seed, rid, episode + 1u, stage_words + lane, steps - s);
         const bool kept = filled && keeps_base(fam);
         if (most_balls != 0 && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
           const uint32_t balls = (opaque(meta) >> 16) & 255u;
@@ -2580,17 +2594,18 @@ hipError_t launch_fused(const EnvTables& env, const TileTables& tiles, const Sta
       {&k_fused<true, false, 0, false>, &k_fused<true, false, 1, false>, &k_fused<true, false, 2, false>}};
   static const FusedKernel split[2][2] = {{&k_fused<false, false, 0, true>, &k_fused<false, false, 1, true>},
                                           {&k_fused<true, false, 0, true>, &k_fused<true, false, 1, true>}};
-  // first-person records of batches with KeyCorridor envs: connect_few (see there)
-  static const FusedKernel together[2][2][2] = {
-      {{&k_fused<false, false, 0, false, true>, &k_fused<false, false, 1, false, true>},
-       {&k_fused<true, false, 0, false, true>, &k_fused<true, false, 1, false, true>}},
-      {{&k_fused<false, false, 0, true, true>, &k_fused<false, false, 1, true, true>},
-       {&k_fused<true, false, 0, true, true>, &k_fused<true, false, 1, true, true>}}};
+  // batches with KeyCorridor envs: connect_few (see there)
+  static const FusedKernel together[2][3] = {{&k_fused<false, false, 0, false, true>, &k_fused<false, false, 1, false, true>,
+                                              &k_fused<false, false, 2, false, true>},
+                                             {&k_fused<true, false, 0, false, true>, &k_fused<true, false, 1, false, true>,
+                                              &k_fused<true, false, 2, false, true>}};
+  static const FusedKernel split_together[2][2] = {{&k_fused<false, false, 0, true, true>, &k_fused<false, false, 1, true, true>},
+                                                   {&k_fused<true, false, 0, true, true>, &k_fused<true, false, 1, true, true>}};
   const int with = actions ? 1 : 0;
   const bool pair = grid_blocks <= kSplitBlocks && obs < 2 && (serve || out.obs) &&
                     fused_lds_bytes(tiles.max_tile_cells) + kSplitLds <= 160 * 1024;
   FusedKernel fn = pair ? split[with][obs & 1] : kernels[with][obs];
-  if (tiles.corridors && obs < 2) fn = together[pair ? 1 : 0][with][obs & 1];
+  if (tiles.corridors) fn = pair ? split_together[with][obs & 1] : together[with][obs];
   if (serve) fn = pair ? &k_fused<false, true, 0, true> : &k_fused<false, true, 0, false>;
   return launch_tiles(fn, a, grid_blocks, pair ? 2 * kWave : kWave, stream);
 }
