@@ -89,7 +89,7 @@ struct TileCells {
   int32_t sum[5] = {}, most[5] = {};
   void add(int64_t env, int32_t cells) {
     for (int i = 0; i < 5; ++i) {
-      sum[i] = env % kSizes[i] ? sum[i] + cells : cells;
+      sum[i] = env & (kSizes[i] - 1) ? sum[i] + cells : cells;
       most[i] = sum[i] > most[i] ? sum[i] : most[i];
     }
   }

@@ -40,3 +40,52 @@ def test_corridors_drawn_ahead_or_not(K, obs_mode):
     table.family[other], table.side[other], table.param[other] = wl.FAMILY_CROSSINGS, 9, 2
     table.max_steps[:] = rng.integers(1, 25, n)
     check_rollout(table, 40, K, obs_mode, what=f"corridors, K = {K}, mode {obs_mode}")
+
+
+def busy_table(n, corridors, seed):
+    """Every family at small sides (KeyCorridor or not), episodes of 1 to 11
+    steps: layouts drawn and filled, balls moved and doors toggled on most steps."""
+    table = wl.families_table(2 * n, seed=seed, mix_seed=seed + 1)
+    table = table.subset(np.flatnonzero((table.family == wl.FAMILY_KEYCORRIDOR) <= corridors)[:n])
+    table.rng_id[:] = np.arange(n)
+    table.max_steps[:] = np.random.default_rng(seed).integers(1, 12, n)
+    return table
+
+
+@pytest.mark.parametrize("obs_mode", [0, 1])
+@pytest.mark.parametrize("n,corridors,with_actions", [(65600, False, False), (65600, True, False),
+                                                      (65600, False, True), (65600, True, True),
+                                                      (65601, False, False), (65599, True, True)])
+def test_full_tiles_of_single_waves(n, corridors, with_actions, obs_mode):
+    """More than 1024 tiles of 64 envs: one wave takes the steps and writes the
+    records, its stage holding layout words, views and the write-back's bitmap
+    in turn; rows on 64-byte boundaries (65 600 envs) and off them."""
+    table = busy_table(n, corridors, seed=n + corridors)
+    steps = 17
+    acts = None
+    if with_actions:
+        acts = np.random.default_rng(n).choice(np.array([0, 1, 2, 2, 2, 3, 4, 5, 5, 6, 99], np.uint8), (steps, n))
+    check_rollout(table, steps, 9, obs_mode, actions=acts, what=f"{n} envs, mode {obs_mode}")
+
+
+@pytest.mark.parametrize("offset", [0, 16, 64, 128, 147])
+def test_single_waves_at_any_alignment(offset):
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    n, steps = 65600, 5
+    table = wl.mixed_table(n, seed=offset)
+    b, s, _ = P.oracle_reset(table)
+    ref = ox.rollout(b, s, steps, None, nthreads=8)
+    env = ge.GridEnv(table)
+    env.reset()
+    traj = env.traj(steps)
+    shape, size = traj.obs.shape, traj.obs.numel()
+    raw = torch.full((size + 1024,), 0xA5, dtype=torch.uint8, device="cuda")
+    at = 256 + offset - raw.data_ptr() % 128
+    traj.obs = raw[at:at + size].view(shape)
+    env.rollout(steps, traj)
+    torch.cuda.synchronize()
+    P.assert_rows_equal(traj, ref, what=f"records at byte {offset}")
+    P.assert_state_equal(env, s, f"records at byte {offset}")
+    assert bool((raw[:at] == 0xA5).all()) and bool((raw[at + size:] == 0xA5).all())
+    env.close()
