@@ -1584,19 +1584,17 @@ constexpr int kCorridorsAhead = 16;
 
 // Gives every lane with `need` set a Next for `episode`, drawing with it those
 // of the `active` lanes of its family that have none (have == false).
-// kTogether: see connect_few.  kAhead: KeyCorridors only if `left`, the launch's
-// steps from this one on, are enough.
-template <bool kTogether = false, bool kAhead = false>
+// kTogether: see connect_few.
+template <bool kTogether = false>
 __device__ __forceinline__ void draw_missing(Next& n, bool& have, bool need, bool active, uint32_t meta, uint2 seed,
-                                             uint32_t rng_id, uint32_t episode, uint32_t* words, int left = 0) {
+                                             uint32_t rng_id, uint32_t episode, uint32_t* words) {
   while (true) {
     const uint64_t missing = __ballot(need && !have);
     if (!missing) return;
     const uint32_t f =
         (uint32_t)bcast((int)meta, __ffsll((unsigned long long)missing) - 1) & 255u;
-    const bool draws = kAhead && f == kFamKeyCorridor && left < kCorridorsAhead ? need : active;
     KcRest rest{};
-    if (draws && !have && (meta & 255u) == f) {
+    if (active && !have && (meta & 255u) == f) {
       n = draw_layout<kTogether>(f, opaque(meta), opaque(seed), opaque(rng_id), episode, words, rest);
       have = true;
     }
@@ -2072,6 +2070,52 @@ __global__ __launch_bounds__(kWave) void k_plain(PlainArgs a) {
   }
 }
 
+// Which wave of a workgroup of two is the renderer (kSplit).  A SIMD with a
+// renderer and a stepper keeps pace; one with two renderers does not, and the
+// whole launch waits for it.  Which SIMDs a workgroup's waves land on depends on
+// where the kernel before left off: by the wave's number alone every SIMD has one
+// of each after a launch of the same shape, but after a kernel of larger
+// workgroups a tenth of the compute units has two renderers on two SIMDs and two
+// steppers on the others.  So where pairs take many tiles in turn (kLong), the
+// workgroups of a compute unit count their renderers by SIMD, in a byte each, and
+// a workgroup takes the SIMD with fewer: 262 144 Empty 8x8, 1024 steps after a
+// fill of 256 MB 9.39 -> 7.28 ms (single waves 8.14), 128 steps 1.19 -> 0.97, as
+// without the fill.  The claim takes some two microseconds a launch.  The counts
+// steer speed alone and are back to what they were when a launch ends.
+__device__ uint32_t renderers_on[16 * 256];   // by XCC and compute unit
+
+// what a workgroup has counted, kept in LDS: a wave may end on another compute
+// unit than it began on (it is saved and restored when processes take turns)
+struct Claim {
+  uint32_t shifts[2];   // the waves' SIMDs as shifts of the count
+  uint32_t unit, second;
+};
+
+// 0 or 1: the wave of the workgroup that is to render, from now on counted
+__device__ __forceinline__ int claim_renderer(Claim& c, int wave, int lane) {
+  constexpr int kHwId = 4 | (15 << 11), kXccId = 20 | (3 << 11);   // s_getreg operands: bits 0-15, 0-3
+  const uint32_t hw = (uint32_t)__builtin_amdgcn_s_getreg(kHwId), xcc = (uint32_t)__builtin_amdgcn_s_getreg(kXccId);
+  if (lane == 0) c.shifts[wave] = 8u * ((hw >> 4) & 3u);
+  pair_barrier();
+  if (wave == 0 && lane == 0) {
+    const uint32_t s0 = c.shifts[0], s1 = c.shifts[1];
+    c.unit = ((xcc & 15u) << 8) | ((hw >> 8) & 255u);
+    uint32_t* const count = renderers_on + c.unit;
+    uint32_t seen = __hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), second;
+    do {   // fails only when another workgroup's claim or end came between
+      second = ((seen >> s1) & 255u) < ((seen >> s0) & 255u) ? 1u : 0u;
+    } while (!__hip_atomic_compare_exchange_strong(count, &seen, seen + (1u << (second ? s1 : s0)), __ATOMIC_RELAXED,
+                                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    c.second = second;
+  }
+  pair_barrier();
+  return __builtin_amdgcn_readfirstlane((int)c.second);
+}
+
+__device__ __forceinline__ void give_back(const Claim& c) {
+  __hip_atomic_fetch_sub(renderers_on + c.unit, 1u << c.shifts[c.second], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 struct FusedArgs {
   EnvTables env;
   TileTables tiles;
@@ -2101,6 +2145,8 @@ struct FusedArgs {
 // kObs: the observation records written, 0 symbolic first person, 1
 // categorical first person, 2 whole grid (a.env.obs_mode 2 or 3); each
 // variant carries only its own record code.
+// kLong: launches of several steps that keep one of two more rules, see
+// claim_renderer (kSplit) and emit_64_views.
 // kSplit: a workgroup of two waves.  The second takes the steps (policy,
 // actions, resets, balls, the step's scalars), the first writes the records:
 // it is handed each lane's pose in LDS, reads the views' rows out of the
@@ -2118,7 +2164,7 @@ struct FusedArgs {
 // load consumed in the same step would also wait for every earlier record
 // store: the action of step s + 1 is therefore fetched during step s, and
 // the policy variant has no loads in its step loop at all.
-template <bool kActions, bool kServe, int kObs, bool kSplit, bool kTogether = false>
+template <bool kActions, bool kServe, int kObs, bool kSplit, bool kTogether = false, bool kLong = false>
 __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs a) {
   // first-person variants: the byte masks of a row's visibility bits.  The
   // stage holds, one after another, the words of layouts being drawn, the
@@ -2135,7 +2181,12 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
   extern __shared__ __align__(16) uint8_t grids[];
   uint8_t* codes = grids + kMargin;
   const int lane = kSplit ? threadIdx.x & (kWave - 1) : threadIdx.x;
-  const bool renders = kSplit && __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) == 0;
+  bool renders = false;
+  __shared__ Claim claim;
+  if (kSplit) {
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    renders = wave == (kLong ? claim_renderer(claim, wave, lane) : 0);
+  }
   const int N = a.env.n;
   if (renders) __builtin_amdgcn_s_setprio(1);
 
@@ -2193,15 +2244,12 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       o_mission = a.out.mission ? a.out.mission + e0 : nullptr;
       rec_stride = (size_t)N;
     }
-    // whether every row's records start on a 64-byte boundary (emit_64_views)
-    constexpr bool kAligned = kObs == 0 && !kSplit && !kActions && !kServe;
-    const bool on_lines = kAligned && n_here == kWave && (N & 63) == 0 && (reinterpret_cast<uintptr_t>(o_obs) & 63u) == 0;
     // the staged views as the first-person records from index rec on
     const auto write_views = [&](size_t rec) {
       wave_sync();
       const uint8_t* cells = reinterpret_cast<const uint8_t*>(stage);
       if (kObs == 1) emit_types(o_obs + rec * kCatBytes, cells, n_here * kCatBytes, lane);
-      else if (kAligned && on_lines) emit_64_views(o_obs + rec * kObsBytes, cells, lane);
+      else if (kLong && !kSplit) emit_64_views(o_obs + rec * kObsBytes, cells, lane);
       else emit_triples<false>(o_obs + rec * kObsBytes, cells, n_here * kCatBytes, lane);
     };
     int ring_row = kServe ? 0 : a.row0;   // output row of the next step
@@ -2326,9 +2374,10 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       if (kSplit && (pending || most_balls != 0)) __builtin_amdgcn_s_setprio(2);
       if (pending) {
         // in the launch's last step only for the lanes that reset: nothing is
-        // kept for the next launch
-        draw_missing<kTogether, kTogether || kServe>(next, have_next, do_reset, s + 1 < steps ? active : do_reset, meta,
-                                                     seed, rid, episode + 1u, stage_words + lane, steps - s);
+        // kept for the next launch (and see kCorridorsAhead)
+        const int ahead = (kTogether || kServe) && fam == kFamKeyCorridor ? kCorridorsAhead : 2;
+        draw_missing<kTogether>(next, have_next, do_reset, steps - s >= ahead ? active : do_reset, meta, seed, rid,
+                                episode + 1u, stage_words + lane);
         const bool kept = filled && keeps_base(fam);
         if (most_balls != 0 && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
           const uint32_t balls = (opaque(meta) >> 16) & 255u;
@@ -2469,6 +2518,7 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
     }
     wave_sync();
   }
+  if (kSplit && kLong && renders && lane == 0) give_back(claim);
 }
 
 // Every env's episode 0 (env_reset), tile by tile as k_fused runs them: the
@@ -2629,6 +2679,15 @@ hipError_t launch_fused(const EnvTables& env, const TileTables& tiles, const Sta
                     fused_lds_bytes(tiles.max_tile_cells) + kSplitLds <= 160 * 1024;
   FusedKernel fn = pair ? split[with][obs & 1] : kernels[with][obs];
   if (tiles.corridors) fn = pair ? split_together[with][obs & 1] : together[with][obs];
+  if (!actions && !serve && obs == 0) {
+    // pairs that take many tiles in turn: renderers counted by SIMD (claim_renderer)
+    if (pair && !tiles.corridors && k_steps >= 128 && tiles.n_tiles > grid_blocks)
+      fn = &k_fused<false, false, 0, true, false, true>;
+    // single waves, every row of every tile 64 records from a 64-byte boundary on (emit_64_views)
+    if (!pair && out.obs && k_steps > 1 && tiles.tile_envs == kWave && env.n % kWave == 0 &&
+        (reinterpret_cast<uintptr_t>(out.obs) & 63u) == 0)
+      fn = tiles.corridors ? &k_fused<false, false, 0, false, true, true> : &k_fused<false, false, 0, false, false, true>;
+  }
   if (serve) fn = pair ? &k_fused<false, true, 0, true> : &k_fused<false, true, 0, false>;
   return launch_tiles(fn, a, grid_blocks, pair ? 2 * kWave : kWave, stream);
 }

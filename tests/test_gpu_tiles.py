@@ -89,3 +89,49 @@ def test_single_waves_at_any_alignment(offset):
     P.assert_state_equal(env, s, f"records at byte {offset}")
     assert bool((raw[:at] == 0xA5).all()) and bool((raw[at + size:] == 0xA5).all())
     env.close()
+
+
+@pytest.mark.parametrize("n,steps", [(61440 + 64, 200), (122880, 1030), (122880 - 64, 130)])
+def test_default_calls_of_long_rollouts(n, steps):
+    """No K and no shape: one launch of up to 1024 steps, tiles in turn, and what
+    is left in another; through both entry points."""
+    import torch
+    import test_zz_no_alloc as static
+    table = wl.mixed_table(n, seed=6)
+    env, bufs = static.run_pair(table, steps, 3, 0)
+    b, s, _ = P.oracle_reset(table)
+    ref = ox.rollout(b, s, steps, None, rows=3, nthreads=8)
+    P.assert_rows_equal(bufs.traj, ref, what=f"{n} envs")
+    P.assert_state_equal(env, s, f"{n} envs")
+    env.close()
+    torch.cuda.empty_cache()
+
+
+def test_long_rollouts_beside_other_kernels():
+    """Pairs that take tiles in turn count their renderers per SIMD: two such
+    launches on two streams at once, with other kernels before and between."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    n, steps = 122880, 128
+    other = torch.zeros(1 << 26, dtype=torch.uint8, device="cuda")
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    runs = []
+    for k, stream in enumerate(streams):
+        table = wl.mixed_table(n, seed=20 + k)
+        env = ge.GridEnv(table)
+        env.reset()
+        runs.append((table, env, env.traj(3), stream))
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for _, env, traj, stream in runs:
+            with torch.cuda.stream(stream):
+                other.add_(1)
+                env.rollout(steps, traj, K=steps)
+    torch.cuda.synchronize()
+    for table, env, traj, _ in runs:
+        b, s, _ = P.oracle_reset(table)
+        for _ in range(3):
+            ref = ox.rollout(b, s, steps, None, rows=3, nthreads=8)
+        P.assert_rows_equal(traj, ref, what="beside other kernels")
+        P.assert_state_equal(env, s, "beside other kernels")
+        env.close()
