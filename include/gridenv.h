@@ -217,7 +217,7 @@ typedef struct {
   int32_t max_tile_cells;     /* largest tile's cells, one LDS byte each */
   int32_t lds_bytes;          /* LDS per workgroup of the fused kernel */
   int32_t blocks;             /* workgroups of the fused kernel (each takes tiles blocks apart) */
-  int32_t k_default;          /* steps fused per launch when K = 0 */
+  int32_t k_default;          /* steps fused per launch when K = 0 (more where env_rollout says so) */
   uint64_t grid_bytes;
   uint64_t obs_row_bytes;     /* bytes of one row of observation outputs */
   int32_t tile_envs;          /* envs per fused tile (one per lane of a wave's first lanes) */
@@ -261,7 +261,9 @@ int env_step(gx_ctx* ctx, const gx_state* st, const uint8_t* actions, const gx_t
  * registers for K steps (the jitted scan of App. B).  Step s of the call
  * writes output row s % traj->rows; the results equal n_steps env_step
  * calls bit for bit.  actions: device bytes [n_steps][n_envs] or NULL for
- * the random policy.  K = 0 picks the context's default.  No allocation
+ * the random policy.  K = 0 leaves it to the context: env_set_launch's value,
+ * else 64, or up to 1024 for long rollouts of large batches whose tiles the
+ * library has its workgroups take in turn (see env_set_launch).  No allocation
  * and no synchronisation: the call can be captured in a HIP graph. */
 int env_rollout(gx_ctx* ctx, const gx_state* st, int32_t n_steps, const uint8_t* actions,
                 const gx_traj* traj, int32_t K, void* stream);
@@ -269,7 +271,10 @@ int env_rollout(gx_ctx* ctx, const gx_state* st, int32_t n_steps, const uint8_t*
 /* Set the rollouts' launch shape: steps per launch (K >= 1) and
  * workgroups (blocks >= 1; 0 keeps the current value).  Fewer workgroups
  * than tiles are persistent: workgroup b takes tiles b, b + blocks, ...
- * The default is one workgroup per tile. */
+ * The default is one workgroup per tile, and 1024 that take the tiles in turn
+ * in launches of 128 steps and more under the random policy, writing symbolic
+ * first-person records of more than 65 536 envs of Empty, DoorKey and FourRooms
+ * in tiles of 64. */
 int env_set_launch(gx_ctx* ctx, int32_t K, int32_t blocks);
 
 /* Set the rollouts' tiling (steps and resets keep the library's own): tiles
@@ -277,8 +282,8 @@ int env_set_launch(gx_ctx* ctx, int32_t K, int32_t blocks);
  * tile's grids in the workgroup's LDS.  Fewer envs per tile leave lanes
  * idle but need less LDS per workgroup, so more workgroups fit a compute
  * unit: the trade for large grids (Sec. 4.2 scales the batch; this picks
- * how a batch maps onto waves).  Resets the workgroup count to one per
- * tile.  Multiples of 16 keep the observation records' stores 16-byte
+ * how a batch maps onto waves).  Resets the workgroup count to the
+ * default.  Multiples of 16 keep the observation records' stores 16-byte
  * aligned; other values fall back to byte stores.  Results do not depend
  * on the tiling. */
 int env_set_tiling(gx_ctx* ctx, int32_t tile_envs);
@@ -419,7 +424,7 @@ int env_serve_run(gx_server* srv, const gx_serve_item* items, int32_t n_items,
  * the per-env tables (28 bytes per env) live in a fixed array of the
  * library's device code, GX_STATIC_MAX_ENVS envs' worth (7 MiB), which
  * each device the library runs on holds until the process ends.  Launch
- * shape: env_create's workgroup count; K = 0 means 64 steps per launch.
+ * shape: that of a context whose caller has chosen nothing, K = 0 included.
  * Observation modes 0..3 only (EINVAL for the rgb modes, whose staging ring
  * would not be modest); GX_ESIZE when cfg->n_envs > GX_STATIC_MAX_ENVS.
  * With reset == 0 the state must come from an earlier reset of the same

@@ -112,6 +112,34 @@ inline int32_t one_pass_tile_envs(int32_t e, const TileCells& cells) {
   return e;
 }
 
+// Workgroups of a launch of k steps under the random policy, writing symbolic
+// first-person records of a batch of Empty, DoorKey and FourRooms, whose caller
+// has chosen none.  Long
+// launches of many tiles drift apart and are bound by their record stores, which
+// 1024 workgroups of two waves that take the tiles in turn write in better step.
+// That holds from 128 steps on, where the turns come out even and where resets
+// are rare; steps that lay out grids or move balls want the more tiles in
+// flight.  ms, one workgroup per tile / 1024 in turn: 262 144 mixed envs, 128 steps
+// 1.08 / 1.05, 256 steps 2.19 / 2.03, 1024 steps 8.30 / 7.47 (64 steps 0.52 /
+// 0.56); Empty 8x8, 256 steps 2.13 / 1.94; 131 072 mixed, 128 steps 0.55 / 0.51;
+// 90 000 mixed (1407 tiles), 256 steps 0.85 / 0.99; GoToDoor 2.85 / 3.38, lava
+// 2.19 / 2.34, all families 3.52 / 4.50; mixed under given actions, whose loads
+// wait for the wave's stores, 2.11 / 2.73.
+inline int32_t rollout_blocks(const TileTables& tiles, int32_t k) {
+  if (tiles.tile_envs != 64 || k < 128 || tiles.n_tiles <= 1024) return tiles.n_tiles;
+  const int32_t turns = (tiles.n_tiles + 1023) / 1024;
+  return tiles.n_tiles >= turns * 960 ? 1024 : tiles.n_tiles;
+}
+
+// Steps per launch of a rollout of n_steps of such a batch, when the caller leaves
+// them to the library: 64, or up to 1024 where rollout_blocks has the tiles taken
+// in turn.  256 steps in launches of 64 / in one, ms: 262 144 mixed envs 2.21 / 2.03,
+// Empty 8x8 2.15 / 1.94.
+inline int32_t rollout_steps(const TileTables& tiles, int32_t n_steps) {
+  const int32_t k = n_steps < 1024 ? n_steps : 1024;
+  return rollout_blocks(tiles, k) < tiles.n_tiles ? k : 64;
+}
+
 // Whether one step of a batch with Dynamic-Obstacles envs moves its balls in HBM
 // (k_plain) rather than in the LDS of a one-step fused launch, which reads
 // every grid of the batch whole.  A ball in HBM is a trip of its own, about

@@ -38,8 +38,9 @@ struct gx_ctx {
   int32_t blocks = 0;
   int32_t k_default = 64;
   // while the caller has chosen neither tiling nor workgroups, launches run
-  // in tiles of their own choice (gx::launch_tile_envs)
-  bool shape_chosen = false;
+  // in tiles of their own choice (gx::launch_tile_envs); while it has not chosen
+  // workgroups or steps, long rollouts choose those (gx::rollout_blocks, _steps)
+  bool shape_chosen = false, blocks_chosen = false, k_chosen = false;
   gx::TileTables auto_tiles{};    // rollouts'
   gx::TileTables step_tiles{};    // env_step's when it runs the fused kernel
   gx::TileTables reset_tiles{};   // env_reset's
@@ -127,22 +128,6 @@ LaunchShape step_shape(const gx_ctx* c) { return {c->step_tiles, c->step_tiles.n
 LaunchShape rollout_shape(const gx_ctx* c) {
   if (!c->shape_chosen) return {c->auto_tiles, c->auto_tiles.n_tiles};
   return {{c->n_tiles, c->max_tile_cells, nullptr, c->tile_envs, 0, c->corridors}, c->blocks};
-}
-
-// Workgroups of a launch of k steps writing first-person records.  Long launches
-// of many tiles drift apart and are bound by their record stores, which 1024
-// workgroups of two waves that take the tiles in turn write in better step.
-// That holds from 128 steps on, where the turns come out even and where
-// resets are rare; steps that lay out grids or move balls want the more
-// tiles in flight.  ms, one workgroup per tile / 1024 in turn: 262 144 mixed
-// envs, 256 steps 2.28 / 2.11, 1024 steps 8.52 / 8.03 (64 steps 0.52 / 0.56);
-// TwoRoom 8x8, 128 steps 1.07 / 0.97; 131 072 mixed, 128 steps 0.57 / 0.53;
-// 90 000 mixed (1407 tiles), 256 steps 0.86 / 1.01; GoToDoor 2.99 / 3.42, lava
-// 2.26 / 2.42, all families 3.70 / 4.50.
-int32_t rollout_blocks(const gx_ctx* c, const LaunchShape& shape, int32_t k, bool first_person) {
-  if (c->shape_chosen || !c->calm || !first_person || k < 128 || shape.tiles.n_tiles <= 1024) return shape.blocks;
-  const int32_t turns = (shape.tiles.n_tiles + 1023) / 1024;
-  return shape.tiles.n_tiles >= turns * 960 ? 1024 : shape.blocks;
 }
 
 bool state_ok(const gx_state* st) {
@@ -442,14 +427,16 @@ int env_rollout(gx_ctx* c, const gx_state* st, int32_t n_steps, const uint8_t* a
   const bool stg = staged(c, traj);
   // rgb: each fused launch fills the staging ring from row 0, then the
   // renderer draws those rows into the caller's ring
-  const int32_t k = std::min(K > 0 ? K : c->k_default, stg ? c->stage_rows : INT32_MAX);
   const LaunchShape shape = rollout_shape(c);
-  const bool first_person = traj->obs && step_obs_mode(c) == 0;
+  const bool turns = !c->blocks_chosen && c->calm && !actions && traj->obs && c->obs_mode == 0;
+  const int32_t own_k = turns && !c->k_chosen ? gx::rollout_steps(shape.tiles, n_steps) : c->k_default;
+  const int32_t k = std::min(K > 0 ? K : own_k, stg ? c->stage_rows : INT32_MAX);
   for (int32_t s0 = 0; s0 < n_steps; s0 += k) {
     const int32_t ks = std::min(k, n_steps - s0);
     const uint8_t* act = actions ? actions + (size_t)s0 * (size_t)c->n : nullptr;
     if (gx::launch_fused(tables_of(c), shape.tiles, state_of(st), act, ks, stg ? stage_traj(c) : traj_of(c, traj),
-                         stg ? 0 : s0 % traj->rows, rollout_blocks(c, shape, ks, first_person), s) != hipSuccess)
+                         stg ? 0 : s0 % traj->rows, turns ? gx::rollout_blocks(shape.tiles, ks) : shape.blocks,
+                         s) != hipSuccess)
       return GX_EDEVICE;
     if (stg && render_rows(c, ks, traj, s0 % traj->rows, s) != hipSuccess) return GX_EDEVICE;
   }
@@ -459,9 +446,10 @@ int env_rollout(gx_ctx* c, const gx_state* st, int32_t n_steps, const uint8_t* a
 int env_set_launch(gx_ctx* c, int32_t K, int32_t blocks) {
   if (!c || K < 1 || blocks < 0) return GX_EINVAL;
   c->k_default = K;
+  c->k_chosen = true;
   if (blocks > 0) {
     c->blocks = blocks;
-    c->shape_chosen = true;
+    c->shape_chosen = c->blocks_chosen = true;
   }
   return GX_OK;
 }
@@ -470,6 +458,7 @@ int env_set_tiling(gx_ctx* c, int32_t tile_envs) {
   if (!c || tile_envs < 1 || tile_envs > kTileEnvs) return GX_EINVAL;
   set_tiling(c, tile_envs);
   c->shape_chosen = true;
+  c->blocks_chosen = false;
   return GX_OK;
 }
 

@@ -85,12 +85,13 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
   uint32_t* rng_id = reinterpret_cast<uint32_t*>(g_host_tables + kRngOff);
   uint64_t* grid_off = reinterpret_cast<uint64_t*>(g_host_tables + kOffOff);
   uint64_t off = 0;
-  bool corridors = false;
+  bool corridors = false, calm = true;
   gx::TileCells cells;
   for (int32_t i = 0; i < n; ++i) {
     const int fam = cfg->family[i], S = cfg->side[i], P = cfg->param ? cfg->param[i] : 0;
     if (!gx::family_ok(fam, S, P, 32) || cfg->max_steps[i] < 1) return GX_EINVAL;
     corridors = corridors || fam == GX_FAMILY_KEYCORRIDOR;
+    calm = calm && fam <= GX_FAMILY_FOURROOMS;
     meta[i] = (uint32_t)fam | ((uint32_t)S << 8) | ((uint32_t)P << 16);
     max_steps[i] = cfg->max_steps[i];
     const uint64_t sd = cfg->seed ? cfg->seed[i] : cfg->seed_all;
@@ -147,14 +148,15 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
   }
   if (n_steps == 0) return GX_OK;
 
-  // the launch shape env_create picks: one single-wave workgroup per tile
-  const int32_t blocks = n_tiles;
-  const int32_t k = K > 0 ? K : 64;
+  // the launches of a context whose caller has chosen nothing
+  const bool turns = calm && !actions && traj->obs && cfg->obs_mode == 0;
+  const int32_t k = K > 0 ? K : turns ? gx::rollout_steps(tiles, n_steps) : 64;
   const gx::TrajBufs tb{traj->obs, traj->reward, traj->flags, traj->action, traj->rows, obs_row, traj->mission};
   for (int32_t s0 = 0; s0 < n_steps; s0 += k) {
     const int32_t ks = std::min(k, n_steps - s0);
     const uint8_t* act = actions ? actions + (size_t)s0 * (size_t)n : nullptr;
-    if (gx::launch_fused(env, tiles, sb, act, ks, tb, s0 % traj->rows, blocks, s) != hipSuccess)
+    if (gx::launch_fused(env, tiles, sb, act, ks, tb, s0 % traj->rows, turns ? gx::rollout_blocks(tiles, ks) : n_tiles,
+                         s) != hipSuccess)
       return GX_EDEVICE;
   }
   return GX_OK;

@@ -60,9 +60,9 @@ class Batch:
     def step(self, obs=True):
         return self._took(self.lib.env_step(self.ctx, ctypes.byref(self.st), None, self._out(obs), None))
 
-    def rollout(self, steps, K=0, obs=True):
-        return self._took(self.lib.env_rollout(self.ctx, ctypes.byref(self.st), steps, None, self._out(obs, steps),
-                                               K, None))
+    def rollout(self, steps, K=0, obs=True, actions=None):
+        return self._took(self.lib.env_rollout(self.ctx, ctypes.byref(self.st), steps, actions,
+                                               self._out(obs, steps), K, None))
 
     def set_tiling(self, tile_envs):
         assert self.lib.env_set_tiling(self.ctx, tile_envs) == ge.GX_OK
@@ -156,4 +156,52 @@ def test_static_rollout_runs_a_contexts_launches(lib):
     tr, n = b._out(True, 200), table.n
     rc = lib.env_rollout_static(ctypes.byref(b.cfg), ctypes.byref(b.st), 1, tr, 100, None, tr, 0, None)
     assert b._took(rc) == b.reset() + b.rollout(100)
+    b.close()
+
+
+def steps_and_blocks(launches):
+    return [(r["steps"], r["blocks"]) for r in launches]
+
+
+def test_long_rollouts_take_tiles_in_turn(lib):
+    """Unless the caller has chosen otherwise, whatever way it leaves the choice
+    to the library: no K, tiles of 64 set, or a K of its own."""
+    b = Batch(lib, wl.mixed_table(262144))
+    assert steps_and_blocks(b.rollout(256)) == [(256, 1024)]
+    assert steps_and_blocks(b.rollout(2100)) == [(1024, 1024), (1024, 1024), (52, 4096)]
+    assert steps_and_blocks(b.rollout(127)) == [(64, 4096), (63, 4096)]
+    assert steps_and_blocks(b.rollout(256, K=128)) == [(128, 1024)] * 2
+    assert steps_and_blocks(b.rollout(256, obs=False)) == [(64, 4096)] * 4
+    assert steps_and_blocks(b.rollout(256, actions=16)) == [(64, 4096)] * 4
+    assert steps_and_blocks(b.rollout(256, K=256, actions=16)) == [(256, 4096)]
+    b.set_tiling(64)
+    assert steps_and_blocks(b.rollout(256)) == [(256, 1024)]
+    b.set_launch(64)
+    assert steps_and_blocks(b.rollout(256)) == [(64, 4096)] * 4
+    assert steps_and_blocks(b.rollout(256, K=200)) == [(200, 1024), (56, 4096)]
+    b.set_launch(256, 4096)
+    assert steps_and_blocks(b.rollout(256)) == [(256, 4096)]
+    b.set_tiling(32)
+    assert steps_and_blocks(b.rollout(256)) == [(256, 8192)]
+    b.close()
+
+
+@pytest.mark.parametrize("table,obs_mode", [(wl.mixed_table(90000), 0), (wl.mixed_table(65536), 0),
+                                            (wl.lava_table(262144), 0), (wl.mixed_table(262144), 1)],
+                         ids=["uneven turns", "one tile per SIMD", "frequent resets", "type ids"])
+def test_other_rollouts_run_64_steps_a_launch(lib, table, obs_mode):
+    b = Batch(lib, table, obs_mode)
+    assert steps_and_blocks(b.rollout(256)) == [(64, -(-table.n // 64))] * 4
+    b.close()
+
+
+@pytest.mark.parametrize("table", [wl.mixed_table(122880), wl.mixed_table(90000), wl.lava_table(122880),
+                                   wl.uniform_table(100, wl.FAMILY_KEYCORRIDOR, 7, param=1)],
+                         ids=["in turn", "uneven turns", "lava", "corridors"])
+@pytest.mark.parametrize("steps,K,actions", [(300, 0, None), (300, 200, None), (40, 0, None), (300, 0, 16)])
+def test_static_rollout_follows_the_context(lib, table, steps, K, actions):
+    b = Batch(lib, table)
+    tr = b._out(True, steps)
+    rc = lib.env_rollout_static(ctypes.byref(b.cfg), ctypes.byref(b.st), 1, tr, steps, actions, tr, K, None)
+    assert b._took(rc) == b.reset() + b.rollout(steps, K, actions=actions)
     b.close()
