@@ -207,15 +207,17 @@ typedef struct {
   uint8_t* mission;  /* may be NULL */
 } gx_traj;
 
-/* Launch and tiling facts of a context (for tools and benchmarks).  Until
- * env_set_tiling or env_set_launch choose tiles or workgroups, they are
- * those of the default tiling of 64; launches of at most 32768 envs then
- * run in smaller tiles of the library's choice, one workgroup each. */
+/* Tiling and workgroups of a context's rollouts (for tools and benchmarks).
+ * Until env_set_tiling or env_set_launch choose them, they are those of the
+ * default tiling of 64, while launches of at most 32768 envs run in smaller
+ * tiles of the library's choice, one workgroup each, and long rollouts as
+ * env_set_launch says.  Steps and resets always run in tiles of the library's
+ * choice. */
 typedef struct {
   int32_t n_envs;
   int32_t n_tiles;            /* workgroup tiles of tile_envs envs (fused rollout) */
   int32_t max_tile_cells;     /* largest tile's cells, one LDS byte each */
-  int32_t lds_bytes;          /* LDS per workgroup of the fused kernel */
+  int32_t lds_bytes;          /* LDS per workgroup of the fused kernel in this shape */
   int32_t blocks;             /* workgroups of the fused kernel (each takes tiles blocks apart) */
   int32_t k_default;          /* steps fused per launch when K = 0 (more where env_rollout says so) */
   uint64_t grid_bytes;

@@ -2611,8 +2611,14 @@ __global__ __launch_bounds__(kWave) void k_reset(FusedArgs a) {
 
 size_t fused_dynamic_lds_bytes(int32_t max_tile_cells) { return tile_lds_bytes(max_tile_cells); }
 
-size_t fused_lds_bytes(int32_t max_tile_cells) {
-  return kMaskEntries * sizeof(uint2) + kViewStageBytes + kMaskPatterns * sizeof(uint32_t) + kWave + fused_dynamic_lds_bytes(max_tile_cells);
+// LDS that a pair of waves needs besides: the renderer's stage and the poses
+constexpr size_t kSplitLds = kViewStageBytes + kWave * sizeof(uint2);
+constexpr size_t kFixedLds = kMaskEntries * sizeof(uint2) + kViewStageBytes + kMaskPatterns * sizeof(uint32_t) + kWave;
+static_assert(kFixedLds + kSplitLds + sizeof(Claim) + 2 * kMargin + kWave * 32 * 32 <= 160 * 1024,
+              "the largest tile fits the LDS of a compute unit");
+
+size_t fused_lds_bytes(int32_t max_tile_cells, bool pairs) {
+  return kFixedLds + (pairs ? kSplitLds : 0) + fused_dynamic_lds_bytes(max_tile_cells);
 }
 
 hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t* actions,
@@ -2630,16 +2636,6 @@ hipError_t launch_plain(const EnvTables& env, const StateBufs& st, const uint8_t
 namespace {
 
 using FusedKernel = void (*)(FusedArgs);
-
-// Launches of up to this many workgroups run in pairs of waves (k_fused,
-// kSplit): one pair per SIMD at most.  With more workgroups a SIMD has its two
-// waves without pairs, and a pair's second wave would only take their place:
-// 262 144 mixed envs (4096 workgroups), 20 steps 190 us, in pairs 250; 90 000
-// (1407) 167 against 204; 131 072 TwoRoom 8x8 envs (2048) 275 against 302.
-constexpr int kSplitBlocks = 1024;
-// LDS that the pair needs besides: the renderer's stage and the poses
-constexpr size_t kSplitLds = kViewStageBytes + kWave * sizeof(uint2);
-
 
 hipError_t launch_tiles(FusedKernel fn, const FusedArgs& a, int32_t blocks, int32_t threads, hipStream_t stream) {
   const size_t lds = fused_dynamic_lds_bytes(a.tiles.max_tile_cells);
@@ -2675,8 +2671,7 @@ hipError_t launch_fused(const EnvTables& env, const TileTables& tiles, const Sta
   static const FusedKernel split_together[2][2] = {{&k_fused<false, false, 0, true, true>, &k_fused<false, false, 1, true, true>},
                                                    {&k_fused<true, false, 0, true, true>, &k_fused<true, false, 1, true, true>}};
   const int with = actions ? 1 : 0;
-  const bool pair = grid_blocks <= kSplitBlocks && obs < 2 && (serve || out.obs) &&
-                    fused_lds_bytes(tiles.max_tile_cells) + kSplitLds <= 160 * 1024;
+  const bool pair = in_pairs(grid_blocks, obs) && (serve || out.obs);
   FusedKernel fn = pair ? split[with][obs & 1] : kernels[with][obs];
   if (tiles.corridors) fn = pair ? split_together[with][obs & 1] : together[with][obs];
   if (!actions && !serve && obs == 0) {

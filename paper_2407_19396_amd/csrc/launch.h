@@ -112,6 +112,14 @@ inline int32_t one_pass_tile_envs(int32_t e, const TileCells& cells) {
   return e;
 }
 
+// Whether a launch of the fused kernel that writes records runs in pairs of waves
+// (k_fused, kSplit): first-person records (obs_mode 0, 1) in up to 1024
+// workgroups, one pair per SIMD at most.  With more workgroups a SIMD has its two
+// waves without pairs, and a pair's second wave would only take their place:
+// 262 144 mixed envs (4096 workgroups), 20 steps 190 us, in pairs 250; 90 000
+// (1407) 167 against 204; 131 072 TwoRoom 8x8 envs (2048) 275 against 302.
+inline bool in_pairs(int32_t blocks, int32_t obs_mode) { return blocks <= 1024 && obs_mode < 2; }
+
 // Workgroups of a launch of k steps under the random policy, writing symbolic
 // first-person records of a batch of Empty, DoorKey and FourRooms, whose caller
 // has chosen none.  Long
@@ -229,7 +237,7 @@ hipError_t launch_fused(const EnvTables& env, const TileTables& tiles, const Sta
                         const ServeTile* host_tiles = nullptr, const SlotConfig* host_slots = nullptr);
 
 // LDS bytes one workgroup of the fused kernel needs for a tile size (static
-// table and record stage plus the dynamic tile grids).
-size_t fused_lds_bytes(int32_t max_tile_cells);
+// tables and record stages plus the dynamic tile grids), in pairs of waves or not.
+size_t fused_lds_bytes(int32_t max_tile_cells, bool pairs);
 
 }  // namespace gx

@@ -369,7 +369,7 @@ int env_info(const gx_ctx* c, gx_info* info) {
   info->n_tiles = c->n_tiles;
   info->tile_envs = c->tile_envs;
   info->max_tile_cells = c->max_tile_cells;
-  info->lds_bytes = (int32_t)gx::fused_lds_bytes(c->max_tile_cells);
+  info->lds_bytes = (int32_t)gx::fused_lds_bytes(c->max_tile_cells, gx::in_pairs(c->blocks, step_obs_mode(c)));
   info->blocks = c->blocks;
   info->k_default = c->k_default;
   info->grid_bytes = c->grid_bytes;

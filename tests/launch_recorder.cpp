@@ -99,7 +99,7 @@ hipError_t launch_fused(const EnvTables&, const TileTables& t, const StateBufs&,
 }
 
 size_t fused_dynamic_lds_bytes(int32_t cells) { return (size_t)cells + 384; }
-size_t fused_lds_bytes(int32_t cells) { return (size_t)cells; }
+size_t fused_lds_bytes(int32_t cells, bool pairs) { return (size_t)cells + (pairs ? 1 : 0); }
 
 hipError_t launch_render(const RenderSrc&, int32_t, int32_t, bool, const uint2*, uint32_t, const uint8_t*,
                          const RenderDst&, int32_t, hipStream_t) {

@@ -205,3 +205,20 @@ def test_static_rollout_follows_the_context(lib, table, steps, K, actions):
     rc = lib.env_rollout_static(ctypes.byref(b.cfg), ctypes.byref(b.st), 1, tr, steps, actions, tr, K, None)
     assert b._took(rc) == b.reset() + b.rollout(steps, K, actions=actions)
     b.close()
+
+
+@pytest.mark.parametrize("obs_mode", [0, 1, 2])
+def test_lds_bytes_of_pairs(lib, obs_mode):
+    """The reported LDS of a workgroup holds the second wave's share wherever the
+    reported shape runs in pairs (the recorder's stub: one byte more)."""
+    b = Batch(lib, wl.uniform_table(70000, wl.FAMILY_EMPTY, 8), obs_mode)
+    cells = 64 * 64
+    assert b.info().lds_bytes == cells                 # 1094 workgroups
+    b.set_launch(128, 1024)
+    assert b.info().lds_bytes == cells + (obs_mode < 2)
+    b.set_tiling(32)
+    assert b.info().lds_bytes == cells // 2
+    b.close()
+    b = Batch(lib, wl.uniform_table(65536, wl.FAMILY_EMPTY, 8), obs_mode)
+    assert b.info().lds_bytes == cells + (obs_mode < 2)
+    b.close()
