@@ -2375,9 +2375,10 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
       if (pending) {
         // in the launch's last step only for the lanes that reset: nothing is
         // kept for the next launch (and see kCorridorsAhead)
-        const int ahead = (kTogether || kServe) && fam == kFamKeyCorridor ? kCorridorsAhead : 2;
-        draw_missing<kTogether>(next, have_next, do_reset, steps - s >= ahead ? active : do_reset, meta, seed, rid,
-                                episode + 1u, stage_words + lane);
+        bool ahead = s + 1 < steps;
+        if (kTogether || kServe) ahead = ahead && (fam != kFamKeyCorridor || steps - s >= kCorridorsAhead);
+        draw_missing<kTogether>(next, have_next, do_reset, ahead ? active : do_reset, meta, seed, rid, episode + 1u,
+                                stage_words + lane);
         const bool kept = filled && keeps_base(fam);
         if (most_balls != 0 && do_reset && kept && fam == kFamDynObs) {   // the old balls leave
           const uint32_t balls = (opaque(meta) >> 16) & 255u;

@@ -83,20 +83,28 @@ inline int32_t reset_tile_envs(int64_t n_envs) {
 }
 
 // Cells of the largest tile of a batch, for each number of envs a tile can be
-// given by the rules above; envs are added in order.
+// given by the rules above: add() every env's in order, then finish().
 struct TileCells {
   static constexpr int32_t kSizes[5] = {4, 8, 16, 32, 64};
   int32_t sum[5] = {}, most[5] = {};
-  void add(int64_t env, int32_t cells) {
-    for (int i = 0; i < 5; ++i) {
-      sum[i] = env & (kSizes[i] - 1) ? sum[i] + cells : cells;
-      most[i] = sum[i] > most[i] ? sum[i] : most[i];
-    }
+  void add(int32_t env, int32_t cells) {
+    sum[0] += cells;
+    for (int i = 0; i < 5 && (env & (kSizes[i] - 1)) == kSizes[i] - 1; ++i) close(i);
+  }
+  void finish() {
+    for (int i = 0; i < 5; ++i) close(i);
   }
   int32_t of(int32_t envs) const {
     for (int i = 0; i < 5; ++i)
       if (kSizes[i] == envs) return most[i];
     return 0;
+  }
+
+ private:
+  void close(int i) {   // a tile of size i ends and counts for the next size
+    most[i] = sum[i] > most[i] ? sum[i] : most[i];
+    if (i < 4) sum[i + 1] += sum[i];
+    sum[i] = 0;
   }
 };
 

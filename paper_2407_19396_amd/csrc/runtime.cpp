@@ -304,13 +304,14 @@ int env_create(const gx_config* cfg, gx_ctx** out) {
   } catch (const std::bad_alloc&) {
     rc = GX_ENOMEM;
   }
-  for (int32_t i = 0; i < n; ++i) {
-    c->balls += cfg->family[i] == GX_FAMILY_DYNOBS ? cfg->param[i] : 0;
-    c->n_cells += (int64_t)cfg->side[i] * cfg->side[i];
-    c->corridors = c->corridors || cfg->family[i] == GX_FAMILY_KEYCORRIDOR;
-    c->calm = c->calm && cfg->family[i] <= GX_FAMILY_FOURROOMS;
+  for (int32_t i = 0; rc == GX_OK && i < n; ++i) {
+    const int fam = cfg->family[i];
+    c->cells[i] = (int32_t)cfg->side[i] * (int32_t)cfg->side[i];
+    c->balls += fam == GX_FAMILY_DYNOBS ? cfg->param[i] : 0;
+    c->corridors = c->corridors || fam == GX_FAMILY_KEYCORRIDOR;
+    c->calm = c->calm && fam <= GX_FAMILY_FOURROOMS;
   }
-  for (int32_t i = 0; rc == GX_OK && i < n; ++i) c->cells[i] = (int32_t)cfg->side[i] * (int32_t)cfg->side[i];
+  c->n_cells = (int64_t)(off / 3);
   if (rc == GX_OK) rc = upload(&c->d_meta, meta);
   if (rc == GX_OK) rc = upload(&c->d_max_steps, max_steps);
   if (rc == GX_OK) rc = upload(&c->d_seed, seed);
@@ -346,6 +347,7 @@ int env_create(const gx_config* cfg, gx_ctx** out) {
   set_tiling(c, kTileEnvs);
   gx::TileCells cells;
   for (int32_t i = 0; i < n; ++i) cells.add(i, c->cells[i]);
+  cells.finish();
   const auto tiles_of = [&](int32_t E) {
     return gx::TileTables{(n + E - 1) / E, cells.of(E), nullptr, E, 0, c->corridors};
   };

@@ -101,6 +101,7 @@ extern "C" int env_rollout_static(const gx_config* cfg, const gx_state* st, int3
     off += 3ull * (uint64_t)S * (uint64_t)S;
     cells.add(i, S * S);
   }
+  cells.finish();
 
   int device = -1;
   if (hipGetDevice(&device) != hipSuccess) return GX_EDEVICE;
