@@ -2181,12 +2181,9 @@ __global__ __launch_bounds__(kSplit ? 2 * kWave : kWave) void k_fused(FusedArgs 
   extern __shared__ __align__(16) uint8_t grids[];
   uint8_t* codes = grids + kMargin;
   const int lane = kSplit ? threadIdx.x & (kWave - 1) : threadIdx.x;
-  bool renders = false;
   __shared__ Claim claim;
-  if (kSplit) {
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    renders = wave == (kLong ? claim_renderer(claim, wave, lane) : 0);
-  }
+  const int wave = kSplit ? __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)) : 0;
+  const bool renders = kSplit && wave == (kLong ? claim_renderer(claim, wave, lane) : 0);
   const int N = a.env.n;
   if (renders) __builtin_amdgcn_s_setprio(1);
 
