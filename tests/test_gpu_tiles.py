@@ -135,3 +135,96 @@ def test_long_rollouts_beside_other_kernels():
         P.assert_rows_equal(traj, ref, what="beside other kernels")
         P.assert_state_equal(env, s, "beside other kernels")
         env.close()
+
+
+def largest_table(n_odd=64):
+    """64 envs of side 32 (the most cells a tile can hold), 64 of side 31 of the
+    families that need an odd side, 5 more of side 32; short episodes."""
+    big = ([(wl.FAMILY_EMPTY, 32, 0), (wl.FAMILY_TWOROOM, 32, 0), (wl.FAMILY_LAVAGAP, 32, 0),
+            (wl.FAMILY_DISTSHIFT, 32, 1), (wl.FAMILY_GOTODOOR, 32, 0)] +
+           [(wl.FAMILY_DYNOBS, 32, k) for k in range(1, 9)])
+    odd = ([(wl.FAMILY_FOURROOMS, 31, 0)] + [(wl.FAMILY_CROSSINGS, 31, k) for k in range(1, 9)] +
+           [(wl.FAMILY_KEYCORRIDOR, 31, r) for r in (1, 2, 3)])
+    tasks = [big[i % len(big)] for i in range(64)] + [odd[i % len(odd)] for i in range(n_odd)] + big[:5]
+    fam, side, par = (np.array(c, np.uint8) for c in zip(*tasks))
+    n = len(tasks)
+    return wl.EnvTable(fam, side, np.random.default_rng(n).integers(3, 40, n).astype(np.int32),
+                       np.full(n, 61, np.uint64), np.arange(n, dtype=np.uint32), "largest tiles", par)
+
+
+@pytest.mark.parametrize("obs_mode", [0, 1, 2, 3])
+@pytest.mark.parametrize("tile_envs", [64, 0])
+def test_largest_tiles_as_launched(tile_envs, obs_mode):
+    """64 grids of side 32 in one workgroup: 64 KB of codes and a table of blocks
+    to write back that spans them, in pairs of waves and alone (whole grids);
+    beside it the tiles the library chooses."""
+    table = largest_table()
+    assert int((table.side[:64].astype(int) ** 2).sum()) == 65536
+    check_rollout(table, 45, 16, obs_mode, tile_envs, what=f"largest tiles of {tile_envs or 'any'}, mode {obs_mode}")
+
+
+@pytest.mark.parametrize("obs_mode", [0, 2])
+def test_largest_reset_and_step_tiles(obs_mode):
+    """Resets and one-step launches of a large batch of the largest grids, in the
+    tiles that 16 384 cells allow them (16 grids of side 32)."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    n = 16400
+    some = largest_table(0).subset(np.arange(64))
+    table = some.subset(np.arange(n) % 64)
+    table.rng_id[:] = np.arange(n)
+    table.max_steps[:] = 2
+    b, s, first = P.oracle_reset(table, 0, obs_mode)
+    env = ge.GridEnv(table, obs_mode=obs_mode)
+    row = env.traj(1)
+    env.reset(row)
+    P.assert_rows_equal(row, first, what="first timestep")
+    ref = ox.rollout(b, s, 4, None, nthreads=8)
+    traj = env.traj(4)
+    for k in range(4):
+        env.step(traj.row(k))
+    torch.cuda.synchronize()
+    P.assert_rows_equal(traj, ref, what=f"{n} envs of side 32, mode {obs_mode}")
+    P.assert_state_equal(env, s, f"{n} envs of side 32, mode {obs_mode}")
+    env.close()
+
+
+def test_serving_in_whole_tiles():
+    """More than 1024 live tiles, most of them full: launches whose tiles run
+    whole, in single waves; a second wave of requests is admitted between
+    launches, so that fresh and running tiles share one, and every family with
+    layouts that reset, draw or move balls is among them."""
+    import torch
+    from paper_2407_19396_amd import gridenv as ge
+    steps, K = 24, 9
+    sizes = [30000, 20001, 15000, 700, 64, 1, 4000]
+    srv = ge.Server(sum(-(-n // 64) for n in sizes), 32)
+    reqs, live = [], {}
+
+    def admit(k):
+        table = busy_table(sizes[k], corridors=True, seed=40 + k)
+        table.seed[:] = 40 + k
+        stride = ge.padded_stride(table.n)
+        out = ge.Traj.alloc(steps, stride)
+        live[srv.admit(table, steps, out, stride)] = len(reqs)
+        reqs.append((table, out))
+
+    for k in range(5):
+        admit(k)
+    fin = srv.step(K)
+    assert not fin
+    admit(5)
+    admit(6)
+    while live:
+        for h in srv.step(K):
+            torch.cuda.synchronize()
+            srv.release(h)
+            live.pop(h)
+    torch.cuda.synchronize()
+    srv.close()
+    for table, out in reqs:
+        b, s, _ = P.oracle_reset(table)
+        ref = ox.rollout(b, s, steps, None, nthreads=8)
+        n = table.n
+        P.assert_rows_equal(ge.Traj(out.obs[:, :n], out.reward[:, :n], out.flags[:, :n], out.action[:, :n]), ref,
+                            what=f"request of {n} envs")
