@@ -280,14 +280,14 @@ int env_rollout(gx_ctx* ctx, const gx_state* st, int32_t n_steps, const uint8_t*
 int env_set_launch(gx_ctx* ctx, int32_t K, int32_t blocks);
 
 /* Set the rollouts' tiling (steps and resets keep the library's own): tiles
- * of tile_envs (1..64, default 64) consecutive envs, one env per lane on a wave's first tile_envs lanes, the
- * tile's grids in the workgroup's LDS.  Fewer envs per tile leave lanes
- * idle but need less LDS per workgroup, so more workgroups fit a compute
- * unit: the trade for large grids (Sec. 4.2 scales the batch; this picks
- * how a batch maps onto waves).  Resets the workgroup count to the
- * default.  Multiples of 16 keep the observation records' stores 16-byte
- * aligned; other values fall back to byte stores.  Results do not depend
- * on the tiling. */
+ * of tile_envs (1..64) consecutive envs, one env per lane on a wave's first
+ * tile_envs lanes, the tile's grids in the workgroup's LDS.  Fewer envs per
+ * tile leave lanes idle but need less LDS per workgroup, so more workgroups
+ * fit a compute unit: the trade for large grids (Sec. 4.2 scales the batch;
+ * this picks how a batch maps onto waves).  Resets the workgroup count to the
+ * default.  Records may start at any byte; tiles of 64 of a batch of a
+ * multiple of 64 envs fill whole lines of HBM.  Results do not depend on the
+ * tiling. */
 int env_set_tiling(gx_ctx* ctx, int32_t tile_envs);
 
 /* Free the context and its device tables (after the stream is idle). */
@@ -306,7 +306,7 @@ int env_destroy(gx_ctx* ctx);
  * env_rollout(n_steps, random policy) on its own envs, whatever else is
  * being served: its env ids and its policy's call counter are its own.
  * Step s of the request writes row s of its outputs (row stride `stride`
- * envs; a multiple of 16 keeps the record stores vectorised).
+ * envs).
  * ---------------------------------------------------------------------- */
 typedef struct gx_server gx_server;
 

@@ -9,7 +9,8 @@
 //
 // Three kernels share the device functions below:
 //   k_plain  -- one launch per step; one env per lane; state, grid and
-//               outputs in HBM; the view's rows read straight from the grid.
+//               outputs in HBM; the view's rows read straight from the grid,
+//               and moving balls' surroundings too.
 //   k_fused  -- each workgroup takes tiles of up to 64 envs of any mix of
 //               sizes, stages their grids in LDS as one code byte per cell,
 //               runs K steps with the pose in registers, writes one
@@ -676,10 +677,10 @@ __device__ __forceinline__ uint32_t mission_of(uint32_t fam, uint32_t ob0) {
   return fam == kFamGoToDoor ? (ob0 & 0xFFu) : 0xFFu;
 }
 
-// Every kernel's workgroups are single waves and all the data its lanes
-// exchange lives in LDS, whose operations a wave performs in issue order: a
-// wavefront-scope fence (no wait instruction) plus a compiler barrier is
-// enough to make one lane's LDS writes visible to the others' later reads.
+// All the data that the lanes of one wave exchange lives in LDS, whose
+// operations a wave performs in issue order: a wavefront-scope fence (no wait
+// instruction) plus a compiler barrier is enough to make one lane's LDS writes
+// visible to the others' later reads.
 __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
   __builtin_amdgcn_wave_barrier();

@@ -182,7 +182,7 @@ struct alignas(64) ServeTile {
   float* reward;       // [n_steps][stride]
   uint8_t* flags;
   uint8_t* action;
-  uint32_t stride;     // envs per output row of the request (multiple of 16)
+  uint32_t stride;     // envs per output row of the request
   uint32_t local0;     // request-local index of the tile's first env
   uint32_t n_steps;    // steps the request asked for
 };

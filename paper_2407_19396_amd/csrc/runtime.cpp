@@ -103,10 +103,11 @@ int32_t largest_tile(const gx_ctx* c, int32_t E) {
   return most;
 }
 
-// Tiles of E consecutive envs, one single-wave workgroup per tile: the
-// hardware starts a tile's workgroup wherever an earlier one has finished,
-// which balances tiles of uneven work better than persistent workgroups
-// that take their tiles in a fixed order (env_set_launch can ask for fewer).
+// Tiles of E consecutive envs, one workgroup (a wave or a pair of them) per
+// tile: the hardware starts a tile's workgroup wherever an earlier one has
+// finished, which balances tiles of uneven work better than persistent
+// workgroups that take their tiles in a fixed order (env_set_launch can ask for
+// fewer, and rollout_blocks does where the work is even).
 void set_tiling(gx_ctx* c, int32_t E) {
   c->tile_envs = E;
   c->n_tiles = (c->n + E - 1) / E;

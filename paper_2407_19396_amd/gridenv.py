@@ -459,8 +459,8 @@ class GridEnv:
 
 # --------------------------------------------------------------- serving
 def padded_stride(n_envs: int) -> int:
-    """Row stride (envs) of a request's outputs: a multiple of 16 keeps every
-    64-env tile's records 16-byte aligned."""
+    """Row stride (envs) of a request's outputs, a multiple of 16 as the native
+    serving loop rounds it."""
     return -(-n_envs // 16) * 16
 
 
