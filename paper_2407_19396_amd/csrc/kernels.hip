@@ -2151,16 +2151,16 @@ struct FusedArgs {
 // kSplit: a workgroup of two waves.  The second takes the steps (policy,
 // actions, resets, balls, the step's scalars), the first writes the records:
 // it is handed each lane's pose in LDS, reads the views' rows out of the
-// grids, lets the second go on, and computes and stores the records meanwhile.  Two barriers a step, one after the step is taken and one
-// after the rows are read; both waves pass each `steps` times per tile.  Only
-// LDS is shared, so neither wave waits for device memory at them.  Which wave
-// is the longer one changes from step to step: the renderer runs at priority
-// 1, the other at 0, and at 2 while layouts are drawn and filled or balls
-// move.  65 536 TwoRoom 8x8 envs:
-// 2.45 -> 1.92 us a step, 5.3 TB/s of records; 4096 Empty
-// 8x8 1.61 -> 1.16 (0.95 with views_of_few), 30 011 envs of all families 6.4 -> 4.95, 65 536
-// Dynamic-Obstacles envs as type ids 5.7 -> 4.6.  Without the priorities
-// 2.0 / 1.24 / 5.3 / 4.95.
+// grids, lets the second go on, and computes and stores the records meanwhile.
+// Two barriers a step, one after the step is taken and one after the rows are
+// read; both waves pass each `steps` times per tile.  Only LDS is shared, so
+// neither wave waits for device memory at them.  Which wave is the longer one
+// changes from step to step: the renderer runs at priority 1, the other at 0,
+// and at 2 while layouts are drawn and filled or balls move.  65 536 TwoRoom
+// 8x8 envs: 2.45 -> 1.92 us a step, 5.3 TB/s of records; 4096 Empty 8x8
+// 1.61 -> 1.16 (0.95 with views_of_few), 30 011 envs of all families
+// 6.4 -> 4.95, 65 536 Dynamic-Obstacles envs as type ids 5.7 -> 4.6.  Without
+// the priorities 2.0 / 1.24 / 5.3 / 4.95.
 // On this GPU one counter tracks both outstanding loads and stores, so a
 // load consumed in the same step would also wait for every earlier record
 // store: the action of step s + 1 is therefore fetched during step s, and

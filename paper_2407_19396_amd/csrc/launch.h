@@ -130,9 +130,9 @@ inline bool in_pairs(int32_t blocks, int32_t obs_mode) { return blocks <= 1024 &
 
 // Workgroups of a launch of k steps under the random policy, writing symbolic
 // first-person records of a batch of Empty, DoorKey and FourRooms, whose caller
-// has chosen none.  Long
-// launches of many tiles drift apart and are bound by their record stores, which
-// 1024 workgroups of two waves that take the tiles in turn write in better step.
+// has chosen none.  Long launches of many tiles drift apart and are bound by
+// their record stores, which 1024 workgroups of two waves that take the tiles in
+// turn write in better step.
 // That holds from 128 steps on, where the turns come out even and where resets
 // are rare; steps that lay out grids or move balls want the more tiles in
 // flight.  ms, one workgroup per tile / 1024 in turn: 262 144 mixed envs, 128 steps
